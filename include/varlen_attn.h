@@ -78,9 +78,10 @@ typedef struct {
                               where it must decide before the device has seen the lengths: the automatic
                               kv_splits choice, and the tile shape for batches of short samples only
                               (see varlen_attn_fwd).  Must be >= 0. */
-    int32_t kv_splits;     /* an extension, forward only; a tuning hint that never changes results beyond
-                              rounding: 0 = automatic, 1 = never split, 2..VA_MAX_KV_SPLITS = that many
-                              workgroups share the keys of each query tile (see varlen_attn_fwd) */
+    int32_t kv_splits;     /* an extension; a tuning hint that never changes results beyond rounding:
+                              0 = automatic, 1 = never split, 2..VA_MAX_KV_SPLITS = that many workgroups
+                              share the keys of each query tile (forward only; see varlen_attn_fwd and,
+                              for 0 and 1, varlen_attn_bwd) */
 } varlen_attn_params;
 enum { VA_MAX_KV_SPLITS = 8, VA_MAX_MERGE_PARTS = 64 };
 
@@ -92,10 +93,14 @@ size_t varlen_attn_bwd_workspace_bytes(const varlen_attn_params *p);
  * Forward: writes o and lse.  Steps (all on the device): a length-aware scheduler turns
  * cu_seqlens into a list of 128-row query tiles ordered by decreasing cost; one workgroup per
  * (tile, head) streams the sample's K/V through LDS, S = QK^T and PV on bf16 MFMA, online softmax.
- * A launch too small to fill the GPU (few heads, one mid-length sample: what a rank sees in the
- * sequence-parallel state of Section 4.1.1) is split further: kv_splits workgroups share the keys of
- * each query tile, write fp32 partial results into the workspace, and a merge kernel combines them
- * (same formula as varlen_attn_merge).  The workspace size accounts for it.
+ * A launch too small to fill the GPU (at most 64 samples and fewer (tile, head) pairs than workgroups fit on the
+ * chip: what a rank sees in the sequence-parallel state of Section 4.1.1, or a handful of short samples) goes without
+ * the scheduler: every workgroup finds its tile from cu_seqlens.  With kv_splits = 0 the keys of its query tiles are
+ * cut into up to 8 chunks of about equal length, one workgroup each, which write fp32 partial results into the
+ * workspace, and a merge kernel combines them (same formula as varlen_attn_merge); how many is chosen from the sizes
+ * (max_seqlen where given, else the average length), so that a sample's result then depends, to rounding, on what it
+ * is launched with.  kv_splits = 1 cuts nothing, 2..8 forces that many chunks per tile.  The workspace size accounts
+ * for it.
  * A batch of short samples only (0 < max_seqlen <= 1024, keys not split) takes a leaner form of the same
  * kernel, which issues no load past a tile list's end: there a workgroup lives for one to a few tile steps
  * and its time is a chain of memory round trips, so the two spare ones matter (measured 1.1-1.3x at 64..256
@@ -110,7 +115,8 @@ int varlen_attn_fwd(const varlen_attn_params *p,
 /*
  * The forward for callers that can neither allocate device memory nor hand over a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and
- * results as varlen_attn_fwd, bit for bit, minus the workspace: the scratch the call needs (the
+ * results as varlen_attn_fwd, bit for bit, minus the workspace (with one exception: where max_seqlen is given and
+ * the automatic chunks of a small launch would not fit the array, it makes fewer of them): the scratch the call needs (the
  * scheduler's work list and, when the keys of a query tile are split, the fp32 partial results) lives in
  * an array of VA_STATIC_SCRATCH_BYTES that is part of the library's device code.  Every GPU the library
  * runs on holds its own copy of it from the first call there until the process ends.  The call allocates
@@ -137,6 +143,9 @@ int varlen_attn_fwd_static_scratch(const varlen_attn_params *p,
  * Delta_i = <dout_i, o_i> from `o` as stored, in bf16, and leaves it with lse in the workspace),
  * then dK and dV per key tile.  Rows whose softmax is nearly one-hot feel the rounding of `o`
  * through Delta: dS = P (dP - Delta) is a small difference of large terms there.
+ * A launch that does not fill the GPU (see varlen_attn_fwd) has its walks cut into chunks, summed in fp32 in a fixed
+ * order by a third kernel, where the caller names samples longer than 1024 tokens (max_seqlen) and kv_splits = 0.
+ * Without max_seqlen, or with kv_splits = 1, a sample's gradients are the same bits whatever it is launched with.
  */
 int varlen_attn_bwd(const varlen_attn_params *p,
                     const void *dout, const void *q, const void *k, const void *v,

@@ -7,6 +7,7 @@
 
 #include "../../include/varlen_attn.h"
 #include "va_internal.h"
+#include "va_small.h"
 
 // Scratch of varlen_attn_fwd_static_scratch: device memory that belongs to the library's code object, one
 // copy per GPU.  In host code this name is only a handle for hipGetSymbolAddress, never an address.
@@ -92,44 +93,132 @@ int check_device() {
     return checked_rc;
 }
 
-// How many workgroups share the keys of one query tile in the forward.  Splitting only pays when the
-// launch cannot fill the chip: fewer workgroups than the 256 CUs can hold at once (3 per CU at
-// head_dim <= 80, else 2), and samples long enough that every chunk still gets two key tiles (judged by
-// the caller's max_seqlen if it gave one, else by the average sample).
 bool short_batch(const varlen_attn_params* p) { return p->max_seqlen > 0 && p->max_seqlen <= va::kShortBatchMaxSeqlen; }
 
+// Sample length to reckon with before the device has seen the lengths: the caller's max_seqlen if it gave one, else
+// the average.
+int64_t expected_len(const varlen_attn_params* p) {
+    return p->max_seqlen > 0 ? std::min(p->max_seqlen, p->total_tokens) : p->total_tokens / p->num_seqs;
+}
+
+// A launch whose (tile, head) pairs do not fill the `slots` workgroups the chip holds at once (va_small.h).
+bool small_launch(const varlen_attn_params* p, int tile_rows, int heads, int slots) {
+    return p->num_seqs <= va::VA_SMALL_MAX_SEQS &&
+           ((int64_t)p->total_tokens / tile_rows + p->num_seqs) * heads <= slots;
+}
+
+// What a small launch's kernel costs, in the time of one of its steps on a CU that runs nothing else.
+struct SmallCost {
+    int wgs_per_cu;  // workgroups of the kernel a CU holds
+    float share;     // with w workgroups on a CU a step takes 1 + share * (w - 1)
+    float fixed;     // prologue and epilogue
+    float parts;     // fp32 results of 256 chunks, written and read again
+    int others;      // workgroups of the launch that do something else
+};
+
+// How the walks of a small launch are cut: for the samples the caller's sizes lead to expect, the number of workgroups
+// per CU, up to twice what it holds at a time, for which the chunks come out cheapest.
+va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner_rows, va::CostMode mode, int heads,
+                         int per_pair, const SmallCost& cost) {
+    const int len = (int)expected_len(p), R = tile_rows / partner_rows;
+    const int nu = (len + partner_rows - 1) / partner_rows, n = (len + tile_rows - 1) / tile_rows;
+    const int samples = std::max(p->total_tokens / std::max(len, 1), 1);
+    va::SmallPlan best{1, 0, 0};
+    if (nu * per_pair < 8 || len <= va::kShortBatchMaxSeqlen / 2) return best;
+    const int longest = nu * per_pair, least = (longest + va::VA_SMALL_CHUNKS - 1) / va::VA_SMALL_CHUNKS;
+    auto workgroups = [&](int chunk) {
+        int64_t k = 0;
+        for (int ch = 0; ch < va::VA_SMALL_CHUNKS && ch * chunk < longest; ++ch)
+            k += va::tiles_with_chunk(n, nu, R, mode, ch * chunk / per_pair);
+        return k * samples * heads;
+    };
+    // w workgroups per CU: as many as it holds side by side, then one round after the other
+    auto time = [&](int w, int chunk) {
+        const int beside = std::min(w, cost.wgs_per_cu);
+        return (1.f + cost.share * (beside - 1)) * (chunk + cost.fixed) * w / beside;
+    };
+    float least_time = time((int)((workgroups(longest) + 255) / 256), longest);
+    for (int w = 1; w <= 2 * cost.wgs_per_cu; ++w) {
+        const int target = 256 * w - cost.others;
+        int lo = least, hi = longest;  // smallest chunk that gives at most that many workgroups
+        if (workgroups(hi) > target) continue;
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (workgroups(mid) <= target) hi = mid; else lo = mid + 1;
+        }
+        if (lo == longest) continue;
+        const float t = time(w, lo) + cost.parts * w;
+        if (t < least_time) {
+            least_time = t;
+            best.target = target;
+            best.chunk = p->num_seqs == 1 ? lo : 0;
+            const int k = va::chunk_count(longest, lo, va::VA_SMALL_CHUNKS);
+            best.max_chunks = p->num_seqs == 1 ? k : std::min(k + 1, (int)va::VA_SMALL_CHUNKS);
+        }
+    }
+    return best;
+}
+// Time stamps inside the kernels, samples of 4096 and 8192 tokens: a step of the forward at head_dim 128 (32 keys) takes
+// 0.8 / 1.1 / 1.4 us with one, two, three workgroups on the CU, of dQ 1.6 / 2.8 us, of dK/dV 1.5-2 us; prologue and
+// epilogue together 6-8 us each; parts at 5 TB/s.
+SmallCost fwd_cost(int head_dim) {
+    return head_dim == 128 ? SmallCost{va::fwd_small_slots(128) / 256, 0.37f, 8.f, 8.f, 0}
+                           : SmallCost{va::fwd_small_slots(head_dim) / 256, 0.37f, 6.f, 4.f, 0};
+}
+SmallCost dq_cost(int head_dim) { return SmallCost{va::bwd_dq_slots(head_dim) / 256, 0.5f, 5.f, 4.f, 2}; }
+SmallCost dkdv_cost(int head_dim) { return SmallCost{va::bwd_dkdv_slots(head_dim) / 256, 0.5f, 5.f, 8.f, 0}; }
+
+// How many workgroups share the keys of one query tile in the forward when the launch goes by a work list.
+// Splitting only pays when the launch cannot fill the chip: fewer workgroups than the 256 CUs can hold at once (3 per
+// CU at head_dim <= 80, else 2), and samples long enough that every chunk still gets two key tiles.
 int fwd_kv_splits(const varlen_attn_params* p) {
     if (p->kv_splits >= 1) return p->kv_splits;
     const int64_t wgs = ((int64_t)p->total_tokens / va::FWD_TILE_Q + p->num_seqs) * p->num_q_heads;
     const int64_t slots = 256 * (p->head_dim <= 80 ? 3 : 2);
-    const int64_t sample_len = p->max_seqlen > 0 ? std::min(p->max_seqlen, p->total_tokens) : p->total_tokens / p->num_seqs;
-    const int64_t tiles_per_sample = sample_len / va::FWD_TILE_KV;
+    const int64_t tiles_per_sample = expected_len(p) / va::FWD_TILE_KV;
     int64_t s = std::min<int64_t>(std::min<int64_t>(slots / std::max<int64_t>(wgs, 1), tiles_per_sample / 2), VA_MAX_KV_SPLITS);
     return (int)std::max<int64_t>(s, 1);
 }
 
 struct FwdLayout {
     va::SchedLayout sched;
+    bool small;
     int splits;
+    va::SmallPlan plan;
     size_t part_o_ofs, part_lse_ofs, end;
 };
 
-FwdLayout fwd_layout(const varlen_attn_params* p) {
+// A small launch takes fewer chunks rather than more room than the static scratch array has, in the entry point that
+// uses that array and, so that the two give the same bits, wherever the caller names no max_seqlen.
+FwdLayout fwd_layout(const varlen_attn_params* p, bool static_scratch = false) {
+    const size_t max_bytes = static_scratch || p->max_seqlen == 0 ? (size_t)VA_STATIC_SCRATCH_BYTES : SIZE_MAX;
     FwdLayout f;
     f.sched = va::sched_layout(p->total_tokens, p->num_seqs, va::FWD_TILE_Q);
-    f.splits = fwd_kv_splits(p);
-    f.part_o_ofs = f.part_lse_ofs = f.end = f.sched.end_ofs;
-    if (f.splits > 1) {
-        const size_t rows = (size_t)p->total_tokens * p->num_q_heads;
-        f.part_lse_ofs = f.part_o_ofs + (size_t)f.splits * rows * p->head_dim * sizeof(float);
-        f.end = (f.part_lse_ofs + (size_t)f.splits * rows * sizeof(float) + 255) / 256 * 256;
+    f.small = p->kv_splits == 0 && small_launch(p, va::FWD_TILE_Q, p->num_q_heads, va::fwd_small_slots(p->head_dim));
+    f.plan = va::SmallPlan{1, 0, 0};
+    if (f.small)
+        f.plan = small_plan(p, va::FWD_TILE_Q, va::fwd_tile_kv(p->head_dim), p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL,
+                            p->num_q_heads, 1, fwd_cost(p->head_dim));
+    f.splits = f.small ? f.plan.max_chunks : fwd_kv_splits(p);
+    const size_t rows = (size_t)p->total_tokens * p->num_q_heads;
+    f.part_o_ofs = f.sched.end_ofs;
+    for (;; --f.splits) {
+        f.part_lse_ofs = f.end = f.sched.end_ofs;
+        if (f.splits > 1) {
+            f.part_lse_ofs = f.part_o_ofs + (size_t)f.splits * rows * p->head_dim * sizeof(float);
+            f.end = (f.part_lse_ofs + (size_t)f.splits * rows * sizeof(float) + 255) / 256 * 256;
+        }
+        if (f.end <= max_bytes || !f.small || f.splits == 1) break;
     }
+    if (f.splits < f.plan.max_chunks) f.plan = va::SmallPlan{f.splits, f.plan.target, 0};
     return f;
 }
 
 struct BwdLayout {
     va::SchedLayout kv, q;
-    size_t kv_ofs, q_ofs, stats_ofs, end;
+    bool small;
+    va::SmallPlan plan_q, plan_kv;
+    size_t kv_ofs, q_ofs, stats_ofs, part_dq_ofs, part_dk_ofs, part_dv_ofs, end;
 };
 
 BwdLayout bwd_layout(const varlen_attn_params* p) {
@@ -140,6 +229,23 @@ BwdLayout bwd_layout(const varlen_attn_params* p) {
     b.q_ofs = b.kv.end_ofs;
     b.stats_ofs = b.q_ofs + b.q.end_ofs;
     b.end = b.stats_ofs + ((size_t)p->total_tokens * p->num_q_heads * 2 * sizeof(float) + 255) / 256 * 256;
+    b.small = p->num_seqs > 0 && small_launch(p, va::BWD_TILE_Q, p->num_q_heads, va::bwd_dq_slots(p->head_dim));
+    b.plan_q = b.plan_kv = va::SmallPlan{1, 0, 0};
+    // Tiles are cut only where the caller has said that samples are long: without max_seqlen (or kv_splits = 1) a
+    // sample's gradients are the same bits whatever it is launched with.
+    if (b.small && p->kv_splits == 0 && p->max_seqlen > va::kShortBatchMaxSeqlen) {
+        b.plan_q = small_plan(p, va::BWD_TILE_Q, va::BWD_STEP_KV, p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL,
+                              p->num_q_heads, 1, dq_cost(p->head_dim));
+        b.plan_kv = small_plan(p, va::BWD_TILE_KV, va::BWD_STEP_Q, p->causal ? va::COST_CAUSAL_KEY : va::COST_FULL,
+                               p->num_kv_heads, p->num_q_heads / p->num_kv_heads, dkdv_cost(p->head_dim));
+    }
+    auto part = [&](int splits, int heads) {
+        return splits > 1 ? ((size_t)splits * p->total_tokens * heads * p->head_dim * sizeof(float) + 255) / 256 * 256 : 0;
+    };
+    b.part_dq_ofs = b.end;
+    b.part_dk_ofs = b.part_dq_ofs + part(b.plan_q.max_chunks, p->num_q_heads);
+    b.part_dv_ofs = b.part_dk_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
+    b.end = b.part_dv_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
     return b;
 }
 
@@ -177,25 +283,21 @@ int64_t varlen_attn_schedule_host(const varlen_attn_params* p, int which, const 
                                 (va::WorkItem*)items);
 }
 
-int varlen_attn_fwd(const varlen_attn_params* p, const void* q, const void* k, const void* v,
-                    const int32_t* cu_seqlens, void* o, float* lse, void* workspace,
-                    size_t workspace_bytes, void* hip_stream) {
-    int rc = check_params(p);
-    if (rc != VA_OK) return rc;
-    if (p->total_tokens == 0 || p->num_seqs == 0) return VA_OK;
+namespace {
+int fwd_impl(const varlen_attn_params* p, const void* q, const void* k, const void* v, const int32_t* cu_seqlens, void* o,
+             float* lse, const FwdLayout& fl, void* workspace, size_t workspace_bytes, void* hip_stream) {
     if (!q || !k || !v || !cu_seqlens || !o || !lse || !workspace) return VA_ERR_NULL_PTR;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(workspace) ||
         ((uintptr_t)lse & 3u) || ((uintptr_t)cu_seqlens & 3u))
         return VA_ERR_MISALIGNED;
-    const FwdLayout fl = fwd_layout(p);
     const va::SchedLayout& lay = fl.sched;
     if (workspace_bytes < fl.end) return VA_ERR_WORKSPACE_TOO_SMALL;
-    rc = check_device();
+    const int rc = check_device();
     if (rc != VA_OK) return rc;
     hipStream_t stream = (hipStream_t)hip_stream;
 
-    hipError_t e;
-    {
+    hipError_t e = hipSuccess;
+    if (!fl.small) {
         ProfScope ps(VA_KERNEL_SCHED, stream);
         e = va::launch_scheduler(cu_seqlens, p->num_seqs, p->total_tokens, va::FWD_TILE_Q, va::FWD_TILE_KV,
                                  p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL, workspace, lay, stream);
@@ -213,6 +315,10 @@ int varlen_attn_fwd(const varlen_attn_params* p, const void* q, const void* k, c
     a.part_lse = (float*)((char*)workspace + fl.part_lse_ofs);
     a.clock_probe = clock_probe_slot(0);
     a.lean = short_batch(p) && fl.splits == 1;
+    a.small = fl.small;
+    a.cu_seqlens = cu_seqlens;
+    a.num_seqs = p->num_seqs;
+    a.plan = fl.plan;
     {
         ProfScope ps(VA_KERNEL_FWD, stream);
         e = va::launch_fwd(a, stream);
@@ -220,11 +326,22 @@ int varlen_attn_fwd(const varlen_attn_params* p, const void* q, const void* k, c
     if (e != hipSuccess) return hip_fail(e);
     if (fl.splits > 1) {
         ProfScope ps(VA_KERNEL_MERGE, stream);
-        e = va::launch_merge(a.part_o, true, a.part_lse, fl.splits, p->total_tokens, p->num_q_heads, p->head_dim,
-                             o, lse, stream);
+        e = fl.small ? va::launch_fwd_merge_small(a, stream)
+                     : va::launch_merge(a.part_o, true, a.part_lse, fl.splits, p->total_tokens, p->num_q_heads,
+                                        p->head_dim, o, lse, stream);
         if (e != hipSuccess) return hip_fail(e);
     }
     return VA_OK;
+}
+}  // namespace
+
+int varlen_attn_fwd(const varlen_attn_params* p, const void* q, const void* k, const void* v,
+                    const int32_t* cu_seqlens, void* o, float* lse, void* workspace,
+                    size_t workspace_bytes, void* hip_stream) {
+    const int rc = check_params(p);
+    if (rc != VA_OK) return rc;
+    if (p->total_tokens == 0 || p->num_seqs == 0) return VA_OK;
+    return fwd_impl(p, q, k, v, cu_seqlens, o, lse, fwd_layout(p), workspace, workspace_bytes, hip_stream);
 }
 
 namespace {
@@ -256,13 +373,14 @@ int varlen_attn_fwd_static_scratch(const varlen_attn_params* p, const void* q, c
     int rc = check_params(p);
     if (rc != VA_OK) return rc;
     if (p->total_tokens == 0 || p->num_seqs == 0) return VA_OK;
-    if (fwd_layout(p).end > (size_t)VA_STATIC_SCRATCH_BYTES) return VA_ERR_SCRATCH_LIMIT;
+    const FwdLayout fl = fwd_layout(p, true);
+    if (fl.end > (size_t)VA_STATIC_SCRATCH_BYTES) return VA_ERR_SCRATCH_LIMIT;
     rc = check_device();
     if (rc != VA_OK) return rc;
     void* ptr = nullptr;
     rc = static_scratch_ptr(&ptr);
     if (rc != VA_OK) return rc;
-    return varlen_attn_fwd(p, q, k, v, cu_seqlens, o, lse, ptr, (size_t)VA_STATIC_SCRATCH_BYTES, hip_stream);
+    return fwd_impl(p, q, k, v, cu_seqlens, o, lse, fl, ptr, (size_t)VA_STATIC_SCRATCH_BYTES, hip_stream);
 }
 
 int varlen_attn_merge(const varlen_attn_params* p, int32_t num_parts, const void* o_parts, const float* lse_parts,
@@ -325,8 +443,8 @@ int varlen_attn_bwd(const varlen_attn_params* p, const void* dout, const void* q
     hipStream_t stream = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
 
-    hipError_t e;
-    {   // both work lists (key tiles for dK/dV, query tiles for dQ) in one launch, one workgroup each
+    hipError_t e = hipSuccess;
+    if (!lay.small) {   // both work lists (key tiles for dK/dV, query tiles for dQ) in one launch, one workgroup each
         ProfScope ps(VA_KERNEL_SCHED, stream);
         e = va::launch_scheduler_pair(cu_seqlens, p->num_seqs, p->total_tokens, va::BWD_TILE_KV, va::BWD_STEP_Q,
                                       p->causal ? va::COST_CAUSAL_KEY : va::COST_FULL, ws + lay.kv_ofs, lay.kv,
@@ -347,6 +465,15 @@ int varlen_attn_bwd(const varlen_attn_params* p, const void* dout, const void* q
     a.max_items_q = lay.q.max_items;
     a.total_tokens = p->total_tokens; a.num_q_heads = p->num_q_heads; a.num_kv_heads = p->num_kv_heads;
     a.head_dim = p->head_dim; a.causal = p->causal; a.scale = p->softmax_scale;
+    a.small = lay.small;
+    a.cu_seqlens = cu_seqlens;
+    a.num_seqs = p->num_seqs;
+    a.plan_q = lay.plan_q; a.plan_kv = lay.plan_kv;
+    a.part_dq = (float*)(ws + lay.part_dq_ofs);
+    a.part_dk = (float*)(ws + lay.part_dk_ofs);
+    a.part_dv = (float*)(ws + lay.part_dv_ofs);
+    a.ws_kv = ws + lay.kv_ofs; a.ws_q = ws + lay.q_ofs;
+    a.lay_kv = lay.kv; a.lay_q = lay.q;
     a.clock_probe_dkdv = clock_probe_slot(1);
     a.clock_probe_dq = clock_probe_slot(2);
     // dQ first: it also writes the row statistics {LSE * log2 e, -Delta} that dK/dV reads
@@ -360,6 +487,11 @@ int varlen_attn_bwd(const varlen_attn_params* p, const void* dout, const void* q
         e = va::launch_bwd_dkdv(a, stream);
     }
     if (e != hipSuccess) return hip_fail(e);
+    if (lay.plan_q.max_chunks > 1 || lay.plan_kv.max_chunks > 1) {
+        ProfScope ps(VA_KERNEL_MERGE, stream);
+        e = va::launch_bwd_sum_small(a, stream);
+        if (e != hipSuccess) return hip_fail(e);
+    }
     return VA_OK;
 }
 

@@ -26,6 +26,8 @@
 // MFMA results in ordinary vector registers, see build.py).
 #include "va_device.h"
 #include "va_internal.h"
+#include "va_sched.h"
+#include "va_small.h"
 
 #ifndef VA_BWD_PART
 #define VA_BWD_PART 0
@@ -289,12 +291,29 @@ __device__ __forceinline__ void dkdv_issue_part(bool ragged, const TileDma<D, 64
     }
 }
 
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, (D <= 80 ? 2 : 1))
+// Chunks of the walks of a small launch (va_small.h).
+struct DkdvSmall {
+    const int32_t* cu;
+    int num_seqs;
+    SmallPlan plan;
+    float *part_dk, *part_dv;  // fp32 [chunks, T, Hkv, D]
+};
+template <int D>
+constexpr int kDkdvWgsPerCu = D <= 80 ? 2 : 1;
+
+template <bool CAUSAL>
+__device__ __forceinline__ SmallShape dkdv_small_shape(int Hq, int Hkv, const SmallPlan& plan) {
+    return SmallShape{BWD_TILE_KV, BWD_STEP_Q, CAUSAL ? COST_CAUSAL_KEY : COST_FULL, Hkv, Hq / Hkv, plan};
+}
+
+// SMALL: the walk of a key tile (the steps of all query heads of its group, one after the other) may be cut into
+// chunks, one workgroup each, which leave fp32 results for bwd_sum_small.
+template <int D, bool CAUSAL, bool SMALL>
+__global__ void __launch_bounds__(256, (kDkdvWgsPerCu<D>))
 dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
             const __bf16* __restrict__ dO, const float2* __restrict__ stats,
             __bf16* __restrict__ dK, __bf16* __restrict__ dV, const int32_t* __restrict__ hdr,
-            const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale,
+            const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale, DkdvSmall small,
             unsigned long long* __restrict__ clock_probe) {
     using C = BwdCfg<D>;
     using LT = LdsTile<D>;
@@ -306,19 +325,29 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
 
     int item, c;  // work item and kv head (see xcd_item_head)
-    xcd_item_head(blockIdx.x, max_items, Hkv, Hkv, hdr[1], item, c);
-    // (integer division runs on the vector ALU: without this, everything derived from the two, the
-    // staging pointers included, would be kept in vector registers and advanced there)
-    item = __builtin_amdgcn_readfirstlane(item); c = __builtin_amdgcn_readfirstlane(c);
-    if (item >= hdr[0]) return;
+    WorkItem it;
+    SmallTile tl = {};
+    if constexpr (SMALL) {
+        c = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)Hkv));
+        if (!small_tile(small.cu, small.num_seqs, T, dkdv_small_shape<CAUSAL>(Hq, Hkv, small.plan),
+                        __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)Hkv)), tl))
+            return;
+    } else {
+        xcd_item_head(blockIdx.x, max_items, Hkv, Hkv, hdr[1], item, c);
+        // (integer division runs on the vector ALU: without this, everything derived from the two, the
+        // staging pointers included, would be kept in vector registers and advanced there)
+        item = __builtin_amdgcn_readfirstlane(item); c = __builtin_amdgcn_readfirstlane(c);
+        if (item >= hdr[0]) return;
+    }
     ClockProbe wg_clock;
     wg_clock.begin(clock_probe);
     stagger_wave_priority();
     const int g = Hq / Hkv;
-    const WorkItem it = items[item];
+    if constexpr (!SMALL) it = items[item];
     // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
-    const int sb = __builtin_amdgcn_readfirstlane(it.y), L = __builtin_amdgcn_readfirstlane(it.z - it.y),
-              kv0 = __builtin_amdgcn_readfirstlane(it.x - it.y);
+    const int sb = SMALL ? tl.begin : __builtin_amdgcn_readfirstlane(it.y),
+              L = SMALL ? tl.len : __builtin_amdgcn_readfirstlane(it.z - it.y),
+              kv0 = SMALL ? tl.tile * BWD_TILE_KV : __builtin_amdgcn_readfirstlane(it.x - it.y);
 
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
     const int kv = kv0 + 32 * w + ln;  // this lane's key row inside the sample
@@ -347,16 +376,24 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     const uint32_t stat_full = (uint32_t)srow * 8 + ((l >> 4) & 1) * 4;
     const uint32_t stat_last = (uint32_t)min(srow, L - 1 - last_q0) * 8 + ((l >> 4) & 1) * 4;
     const uint32_t lds0 = lds_address(lds);
-    const int total = g * nsteps;
+    // this workgroup's part of the g * nsteps steps: all of them, or one chunk
+    int total = g * nsteps, head0 = 0, step0 = 0;
+    const int ch = tl.ch, nch = SMALL ? tl.nch : 1;
+    if constexpr (SMALL) {
+        const int nb = tl.first_step();
+        total = tl.end_step() - nb;
+        head0 = __builtin_amdgcn_readfirstlane(nb / nsteps);
+        step0 = nb - head0 * nsteps;
+    }
     const bool ragged_sample = (L % BWD_STEP_Q) != 0;
     const int64_t step_q = (int64_t)BWD_STEP_Q * q_row_bytes, step_st = (int64_t)BWD_STEP_Q * 8;
     const int64_t wrap_q = (int64_t)D * 2 - (int64_t)(nsteps - 1) * step_q;       // last step of a head -> first of the next
     const int64_t wrap_st = (int64_t)T * 8 - (int64_t)(nsteps - 1) * step_st;
-    const size_t qoff0 = ((size_t)(sb + first * BWD_STEP_Q) * Hq + (size_t)c * g) * D * 2;
+    const size_t qoff0 = ((size_t)(sb + (first + step0) * BWD_STEP_Q) * Hq + (size_t)c * g + head0) * D * 2;
     const unsigned char* nxt_q = (const unsigned char*)Q + qoff0;
     const unsigned char* nxt_do = (const unsigned char*)dO + qoff0;
-    const unsigned char* nxt_st = (const unsigned char*)(stats + (size_t)c * g * T + sb + first * BWD_STEP_Q);
-    int nxt_s = 0, nxt_n = 0, iss_stage = 0;
+    const unsigned char* nxt_st = (const unsigned char*)(stats + ((size_t)c * g + head0) * T + sb + (first + step0) * BWD_STEP_Q);
+    int nxt_s = step0, nxt_n = 0, iss_stage = 0;
     // the step the current round of loads belongs to (set by begin_issue)
     bool iss_ragged = false;
     const unsigned char *iss_q = nullptr, *iss_do = nullptr, *iss_st = nullptr;
@@ -505,24 +542,28 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
 
     // Masked steps (the causal diagonal, the one that holds the sample's end) take the simple form: in
     // phases, with the mask and the lo parts on top, they were measured no faster even at one wave per SIMD.
-    for (int hg = 0; hg < g; ++hg) {
-        int st = 0;
-        for (; st < n_head; ++st) VA_DKDV_CAREFUL(st)
-        if (st < n_tail) {
+    int left = total;
+    for (int hg = 0; SMALL ? left > 0 : hg < g; ++hg) {
+        int st = SMALL && hg == 0 ? step0 : 0;
+        const int end = SMALL ? min(nsteps, st + left) : nsteps;  // (a chunk may end inside a head)
+        left -= end - st;
+        const int head_end = SMALL ? min(n_head, end) : n_head, plain_end = SMALL ? min(n_tail, end) : n_tail;
+        for (; st < head_end; ++st) VA_DKDV_CAREFUL(st)
+        if (st < plain_end) {
             dkdv_load_A<D, 0>(lds + stage_i * STAGE, aaddr, fa, dpa, hh);
             using Unknown = std::integral_constant<int, -1>;
             if constexpr (D == 64) {  // (elsewhere the four copies of the step cost registers the kernel does not have)
-                for (; st < n_tail && stage_i != 0; ++st) phased(Unknown{});
-                for (; st + NST <= n_tail; st += NST) {  // whole rounds of the stages, each stage a constant
+                for (; st < plain_end && stage_i != 0; ++st) phased(Unknown{});
+                for (; st + NST <= plain_end; st += NST) {  // whole rounds of the stages, each stage a constant
                     phased(std::integral_constant<int, 0>{});
                     phased(std::integral_constant<int, 1>{});
                     phased(std::integral_constant<int, 2>{});
                     phased(std::integral_constant<int, 3>{});
                 }
             }
-            for (; st < n_tail; ++st) phased(Unknown{});
+            for (; st < plain_end; ++st) phased(Unknown{});
         }
-        for (; st < nsteps; ++st) VA_DKDV_CAREFUL(st)
+        for (; st < end; ++st) VA_DKDV_CAREFUL(st)
     }
     wait_vmcnt<0>();  // the surplus loads issued near the end must land before this LDS is given away
 #undef VA_DKDV_SYNC
@@ -530,7 +571,23 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
 #undef VA_DKDV_ADVANCE
 #undef VA_DKDV_CAREFUL
 
-    if (kvalid) {
+    if (SMALL && nch > 1) {
+        if (kvalid) {
+            const size_t off = (((size_t)ch * T + sb + kv) * Hkv + c) * D;
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const int d0 = 32 * db + 8 * r4 + 4 * hh;
+                    if (d0 < D) {
+                        *(float4*)(small.part_dk + off + d0) = make_float4(dkacc[db][4 * r4 + 0], dkacc[db][4 * r4 + 1],
+                                                                           dkacc[db][4 * r4 + 2], dkacc[db][4 * r4 + 3]);
+                        *(float4*)(small.part_dv + off + d0) = make_float4(dvacc[db][4 * r4 + 0], dvacc[db][4 * r4 + 1],
+                                                                           dvacc[db][4 * r4 + 2], dvacc[db][4 * r4 + 3]);
+                    }
+                }
+        }
+    } else if (kvalid) {
         __bf16* dkp = dK + ((size_t)(sb + kv) * Hkv + c) * D;
         __bf16* dvp = dV + ((size_t)(sb + kv) * Hkv + c) * D;
 #pragma unroll
@@ -553,24 +610,31 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     wg_clock.end(clock_probe);
 }
 
-template <int D>
-static hipError_t launch_dkdv_d(const BwdArgs& a, hipStream_t stream) {
-    dim3 grid((unsigned)(a.max_items_kv * a.num_kv_heads)), block(256);
+template <int D, bool CAUSAL>
+static hipError_t launch_dkdv_dc(const BwdArgs& a, hipStream_t stream) {
+    dim3 grid((unsigned)(a.max_items_kv * a.num_kv_heads * a.plan_kv.max_chunks)), block(256);
     auto q = (const __bf16*)a.q; auto k = (const __bf16*)a.k; auto v = (const __bf16*)a.v;
     auto dO = (const __bf16*)a.dout;
     auto st = (const float2*)a.stats;
-    if (a.causal)
-        hipLaunchKernelGGL((dkdv_kernel<D, true>), grid, block, 0, stream, q, k, v, dO, st,
-                           (__bf16*)a.dk, (__bf16*)a.dv, a.sched_hdr_kv, a.items_kv, (int)a.max_items_kv, a.total_tokens,
-                           a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dkdv);
+    auto dk = (__bf16*)a.dk; auto dv = (__bf16*)a.dv;
+    const DkdvSmall sm{a.cu_seqlens, a.num_seqs, a.plan_kv, a.part_dk, a.part_dv};
+    if (a.small)
+        hipLaunchKernelGGL((dkdv_kernel<D, CAUSAL, true>), grid, block, 0, stream, q, k, v, dO, st, dk, dv, a.sched_hdr_kv,
+                           a.items_kv, (int)a.max_items_kv, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale, sm,
+                           a.clock_probe_dkdv);
     else
-        hipLaunchKernelGGL((dkdv_kernel<D, false>), grid, block, 0, stream, q, k, v, dO, st,
-                           (__bf16*)a.dk, (__bf16*)a.dv, a.sched_hdr_kv, a.items_kv, (int)a.max_items_kv, a.total_tokens,
-                           a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dkdv);
+        hipLaunchKernelGGL((dkdv_kernel<D, CAUSAL, false>), grid, block, 0, stream, q, k, v, dO, st, dk, dv, a.sched_hdr_kv,
+                           a.items_kv, (int)a.max_items_kv, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale, sm,
+                           a.clock_probe_dkdv);
     return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_dkdv_d(const BwdArgs& a, hipStream_t stream) {
+    return a.causal ? launch_dkdv_dc<D, true>(a, stream) : launch_dkdv_dc<D, false>(a, stream);
 }
 
 #if VA_BWD_PART == 0
+int bwd_dkdv_slots(int head_dim) { return 256 * (head_dim <= 80 ? kDkdvWgsPerCu<80> : kDkdvWgsPerCu<128>); }
 hipError_t launch_bwd_dkdv(const BwdArgs& a, hipStream_t stream) {
     switch (a.head_dim) {
         case 64: return launch_dkdv_d<64>(a, stream);
@@ -677,12 +741,82 @@ __device__ __forceinline__ void dq_run_A(const DqOpsA<D>& f, const bf16x8 (&frag
         for (int b = 0; b < 2; ++b) acc[b] = mfma32(f.a[b][ks], frag[ks], ks == 0 ? init : acc[b]);
 }
 
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, (D <= 80 ? 2 : 1))
+// A small launch's dQ (va_small.h): every workgroup finds its tile, or chunk of a tile, from cu_seqlens.  The first two
+// build the call's work lists on the side, which the workspace holds after every backward.
+struct DqSmall {
+    const int32_t* cu;
+    int num_seqs;
+    SmallPlan plan;
+    float* part;  // fp32 [chunks, T, Hq, D], without the scale
+    SchedJob kv, q;
+};
+template <int D>
+constexpr int kDqWgsPerCu = D == 64 ? 3 : 2;
+template <bool CAUSAL>
+__device__ __forceinline__ SmallShape dq_small_shape(int Hq, const SmallPlan& plan) {
+    return SmallShape{BWD_TILE_Q, BWD_STEP_KV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, Hq, 1, plan};
+}
+// What a dQ workgroup works on: false if there is nothing left for it to do.
+struct DqWork {
+    int sb, L, q0, h, kvh;
+    int ch, nch, jb, je;  // chunk, chunks of the tile, key steps [jb, je) of this one
+};
+template <bool CAUSAL, bool SMALL>
+__device__ __forceinline__ bool dq_find_work(const int32_t* __restrict__ hdr, const WorkItem* __restrict__ items,
+                                             int max_items, int T, int Hq, int Hkv, const DqSmall& small,
+                                             unsigned char* lds, DqWork& wk) {
+    int item, hp;
+    wk.ch = 0;
+    if constexpr (SMALL) {
+        if (blockIdx.x < 2) {
+            build_work_list(small.cu, small.num_seqs, T, blockIdx.x == 0 ? small.kv : small.q,
+                            *(SchedLds<256, VA_SMALL_MAX_SEQS>*)lds);
+            return false;
+        }
+        const unsigned bid = blockIdx.x - 2;
+        hp = __builtin_amdgcn_readfirstlane((int)(bid % (unsigned)Hq));
+        SmallTile tl;
+        if (!small_tile(small.cu, small.num_seqs, T, dq_small_shape<CAUSAL>(Hq, small.plan),
+                        __builtin_amdgcn_readfirstlane((int)(bid / (unsigned)Hq)), tl))
+            return false;
+        wk.sb = tl.begin; wk.L = tl.len; wk.q0 = tl.tile * BWD_TILE_Q;
+        wk.ch = tl.ch; wk.nch = tl.nch;
+        wk.jb = tl.first_step(); wk.je = tl.end_step();
+    } else {
+        xcd_item_head(blockIdx.x, max_items, Hq, Hkv, hdr[1], item, hp);
+        item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);  // see dkdv_kernel
+        if (item >= hdr[0]) return false;
+        const WorkItem it = items[item];
+        // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
+        wk.sb = __builtin_amdgcn_readfirstlane(it.y); wk.L = __builtin_amdgcn_readfirstlane(it.z - it.y);
+        wk.q0 = __builtin_amdgcn_readfirstlane(it.x - it.y);
+        wk.nch = 1; wk.jb = 0;
+        wk.je = ((CAUSAL ? min(wk.L, wk.q0 + BWD_TILE_Q) : wk.L) + BWD_STEP_KV - 1) / BWD_STEP_KV;
+    }
+    wk.kvh = hp % Hkv;
+    wk.h = wk.kvh * (Hq / Hkv) + hp / Hkv;
+    return true;
+}
+// A chunk's fp32 results of this lane's query row.
+template <int D>
+__device__ __forceinline__ void dq_store_part(const f32x16 (&dqacc)[BwdCfg<D>::DB], float* __restrict__ dst, int hh) {
+#pragma unroll
+    for (int db = 0; db < BwdCfg<D>::DB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int d0 = 32 * db + 8 * r4 + 4 * hh;
+            if (d0 < D)
+                *(float4*)(dst + d0) = make_float4(dqacc[db][4 * r4 + 0], dqacc[db][4 * r4 + 1], dqacc[db][4 * r4 + 2],
+                                                   dqacc[db][4 * r4 + 3]);
+        }
+}
+
+template <int D, bool CAUSAL, bool SMALL>
+__global__ void __launch_bounds__(256, (kDqWgsPerCu<D>))
 dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
           const __bf16* __restrict__ dO, const __bf16* __restrict__ O, const float* __restrict__ LSE,
           float2* __restrict__ stats, __bf16* __restrict__ dQ, const int32_t* __restrict__ hdr, const WorkItem* __restrict__ items,
-          int max_items, int T, int Hq, int Hkv, float scale, unsigned long long* __restrict__ clock_probe) {
+          int max_items, int T, int Hq, int Hkv, float scale, DqSmall small, unsigned long long* __restrict__ clock_probe) {
     using C = BwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr int STAGE = 2 * C::TILE;  // K tile, V tile
@@ -690,26 +824,18 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     constexpr int PER = 2 * C::NI;      // loads per wave per step
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
 
-    int item, hp;
-    xcd_item_head(blockIdx.x, max_items, Hq, Hkv, hdr[1], item, hp);
-    item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);  // see dkdv_kernel
-    if (item >= hdr[0]) return;
+    DqWork wk;
     ClockProbe wg_clock;
     wg_clock.begin(clock_probe);
-    const int kvh = hp % Hkv;
-    const int h = kvh * (Hq / Hkv) + hp / Hkv;
-    const WorkItem it = items[item];
-    // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
-    const int sb = __builtin_amdgcn_readfirstlane(it.y), L = __builtin_amdgcn_readfirstlane(it.z - it.y),
-              q0 = __builtin_amdgcn_readfirstlane(it.x - it.y);
+    if (!dq_find_work<CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
+    const int sb = wk.sb, L = wk.L, q0 = wk.q0, h = wk.h, kvh = wk.kvh;
 
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
     const int qrow = q0 + 32 * w + ln;
     const bool qvalid = qrow < L;
 
-    const int kv_end = CAUSAL ? min(L, q0 + BWD_TILE_Q) : L;
-    const int nsteps = (kv_end + BWD_STEP_KV - 1) / BWD_STEP_KV;
-    const int n_plain = CAUSAL ? min(L, q0 + 1) / BWD_STEP_KV : L / BWD_STEP_KV;
+    const int je = wk.je;  // key steps [wk.jb, je)
+    const int n_plain = min(je, (CAUSAL ? min(L, q0 + 1) : L) / BWD_STEP_KV);
     const unsigned char* kbase = (const unsigned char*)(K + ((size_t)sb * Hkv + kvh) * D);
     const unsigned char* vbase = (const unsigned char*)(V + ((size_t)sb * Hkv + kvh) * D);
     const uint32_t row_bytes = (uint32_t)Hkv * D * 2;
@@ -722,8 +848,8 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     const int64_t step_bytes = (int64_t)BWD_STEP_KV * row_bytes;
     const bool ragged_sample = (L % BWD_STEP_KV) != 0;
     const int last_step = (L + BWD_STEP_KV - 1) / BWD_STEP_KV - 1;  // the one holding the sample's end
-    const unsigned char *nxt_k = kbase, *nxt_v = vbase;
-    int nxt_j = 0, iss_stage = 0;
+    const unsigned char *nxt_k = kbase + wk.jb * step_bytes, *nxt_v = vbase + wk.jb * step_bytes;
+    int nxt_j = wk.jb, iss_stage = 0;
     bool iss_ragged = false;
     const unsigned char *iss_k = nullptr, *iss_v = nullptr;
     uint32_t iss_lds = 0;
@@ -732,7 +858,7 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
         iss_ragged = ragged_sample && nxt_j == last_step;
         iss_lds = lds0 + iss_stage * STAGE;
         iss_stage = iss_stage == NST - 1 ? 0 : iss_stage + 1;
-        const bool more = nxt_j + 1 < nsteps;
+        const bool more = nxt_j + 1 < je;
         const int64_t adv = more ? step_bytes : 0;
         nxt_k += adv; nxt_v += adv;
         nxt_j += more ? 1 : 0;
@@ -778,7 +904,7 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
         ndelta = -xhalf_sum(part);
         if (qvalid) {
             lse2 = LSE[(size_t)h * T + sb + qrow] * kLog2e;
-            if (hh == 0) stats[(size_t)h * T + sb + qrow] = make_float2(lse2, ndelta);
+            if (hh == 0 && wk.ch == 0) stats[(size_t)h * T + sb + qrow] = make_float2(lse2, ndelta);
         }
     }
     wait_vmcnt<0>();
@@ -801,7 +927,7 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     // waits until step i + 1 has landed (step i + 2 may stay in flight) and passes the barrier, after
     // which every wave is done with step i - 1, whose stage this step's loads refill.
     int stage_i = 0;
-    int j = 0;
+    int j = wk.jb;
     f32x16 nd16, zero16;  // -Delta of this lane's row as the starting value of dP; 0 for S
 #pragma unroll
     for (int r = 0; r < 16; ++r) { nd16[r] = ndelta; zero16[r] = 0.f; }
@@ -870,12 +996,12 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     };
     for (; j < n_plain; ++j) step(std::false_type{});
     if constexpr (CAUSAL) {
-        for (; j < nsteps; ++j) step(std::true_type{});
+        for (; j < je; ++j) step(std::true_type{});
     } else {
         // Without the causal mask the only masked step is the one holding the sample's end: it takes the
         // simple form (the phased one with hi + lo in every such step needs more registers than there are).
         // Its sync sits at its end: the step's own stage was published by the sync before.
-        for (; j < nsteps; ++j) {
+        for (; j < je; ++j) {
             dq_end_step<D>(lds + stage_i * STAGE, lds + stage_i * STAGE + C::TILE, aaddr, taddr, qf, dof,
                            dqacc, c2, lse2, ndelta, j * BWD_STEP_KV, qrow, L, hh);
             wait_vmcnt<PER>();
@@ -886,7 +1012,9 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     }
     wait_vmcnt<0>();  // the surplus loads issued near the end must land before this LDS is given away
 
-    if (qvalid) {
+    if (SMALL && wk.nch > 1) {
+        if (qvalid) dq_store_part<D>(dqacc, small.part + (((size_t)wk.ch * T + sb + qrow) * Hq + h) * D, hh);
+    } else if (qvalid) {
         __bf16* dqp = dQ + ((size_t)(sb + qrow) * Hq + h) * D;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
@@ -981,12 +1109,12 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
     }
 }
 
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, (D <= 80 ? 3 : 2))
+template <int D, bool CAUSAL, bool SMALL>
+__global__ void __launch_bounds__(256, (kDqWgsPerCu<D>))
 dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
               const __bf16* __restrict__ dO, const __bf16* __restrict__ O, const float* __restrict__ LSE,
               float2* __restrict__ stats, __bf16* __restrict__ dQ, const int32_t* __restrict__ hdr,
-              const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale,
+              const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale, DqSmall small,
               unsigned long long* __restrict__ clock_probe) {
     using C = BwdCfg<D>;
     using LT = LdsTile<D>;
@@ -995,33 +1123,27 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
     // 16 more registers for nothing that the other workgroups on the CU do not already cover)
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * STAGE];
 
-    int item, hp;
-    xcd_item_head(blockIdx.x, max_items, Hq, Hkv, hdr[1], item, hp);
-    item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);
-    if (item >= hdr[0]) return;
+    DqWork wk;
     ClockProbe wg_clock;
     wg_clock.begin(clock_probe);
-    const int kvh = hp % Hkv;
-    const int h = kvh * (Hq / Hkv) + hp / Hkv;
-    const WorkItem it = items[item];
-    const int sb = __builtin_amdgcn_readfirstlane(it.y), L = __builtin_amdgcn_readfirstlane(it.z - it.y),
-              q0 = __builtin_amdgcn_readfirstlane(it.x - it.y);
+    if (!dq_find_work<CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
+    const int sb = wk.sb, L = wk.L, q0 = wk.q0, h = wk.h, kvh = wk.kvh;
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
     const int qrow = q0 + 32 * w + ln;
     const bool qvalid = qrow < L;
 
-    const int kv_end = CAUSAL ? min(L, q0 + BWD_TILE_Q) : L;
-    const int nsteps = (kv_end + BWD_STEP_KV - 1) / BWD_STEP_KV;
-    const int n_plain = CAUSAL ? min(L, q0 + 1) / BWD_STEP_KV : L / BWD_STEP_KV;
-    const unsigned char* kbase = (const unsigned char*)(K + ((size_t)sb * Hkv + kvh) * D);
-    const unsigned char* vbase = (const unsigned char*)(V + ((size_t)sb * Hkv + kvh) * D);
+    // Steps are counted from the first of this workgroup's: step j holds keys (jb + j) * BWD_STEP_KV and on.
+    const int jb = wk.jb, nsteps = wk.je - jb;
+    const int n_plain = min(nsteps, (CAUSAL ? min(L, q0 + 1) : L) / BWD_STEP_KV - jb);
+    const unsigned char* kbase = (const unsigned char*)(K + ((size_t)(sb + jb * BWD_STEP_KV) * Hkv + kvh) * D);
+    const unsigned char* vbase = (const unsigned char*)(V + ((size_t)(sb + jb * BWD_STEP_KV) * Hkv + kvh) * D);
     const uint32_t row_bytes = (uint32_t)Hkv * D * 2;
     TileDma<D, 64> dma;
     dma.init(row_bytes, L, w, l);
     const uint32_t lds0 = lds_address(lds);
     const int64_t step_bytes = (int64_t)BWD_STEP_KV * row_bytes;
     const bool ragged_sample = (L % BWD_STEP_KV) != 0;
-    const int last_step = (L + BWD_STEP_KV - 1) / BWD_STEP_KV - 1;  // the one holding the sample's end
+    const int last_step = (L + BWD_STEP_KV - 1) / BWD_STEP_KV - 1 - jb;  // the one holding the sample's end
     // loads of step j into stage j % 2; a step past the item's last one is not loaded
     // (the ragged step in a branch of its own, with the flag a constant on either side: a select between the two
     // offset tables on a run-time flag makes the compiler index them through memory, and it then moves them into
@@ -1070,7 +1192,7 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
         ndelta = -xhalf_sum(part);
         if (qvalid) {
             lse2 = LSE[(size_t)h * T + sb + qrow] * kLog2e;
-            if (hh == 0) stats[(size_t)h * T + sb + qrow] = make_float2(lse2, ndelta);
+            if (hh == 0 && wk.ch == 0) stats[(size_t)h * T + sb + qrow] = make_float2(lse2, ndelta);
         }
     }
     // (everything waited for here, once: see the forward kernel for why the register loads must not be left
@@ -1107,7 +1229,7 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
         issue_step(j + 1);
         const unsigned char* st = lds + (PARITY >= 0 ? PARITY : (j & 1)) * STAGE;
         dq_plain_step<D, CAUSAL, MASKED>(st, st + C::TILE, aaddr, taddr, qf, dof, dqacc, c2, lse2, ndelta16,
-                                         j * BWD_STEP_KV, qrow, L, hh, lo_steps);
+                                         (jb + j) * BWD_STEP_KV, qrow, L, hh, lo_steps);
     };
     using Unknown = std::integral_constant<int, -1>;
     int j = 0;
@@ -1119,7 +1241,9 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
     for (; j < nsteps; ++j) step(j, std::true_type{}, Unknown{});
     wait_vmcnt<0>();
 
-    if (qvalid) {
+    if (SMALL && wk.nch > 1) {
+        if (qvalid) dq_store_part<D>(dqacc, small.part + (((size_t)wk.ch * T + sb + qrow) * Hq + h) * D, hh);
+    } else if (qvalid) {
         __bf16* dqp = dQ + ((size_t)(sb + qrow) * Hq + h) * D;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
@@ -1137,38 +1261,119 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
     wg_clock.end(clock_probe);
 }
 
-template <int D>
-static hipError_t launch_dq_d(const BwdArgs& a, hipStream_t stream) {
-    dim3 grid((unsigned)(a.max_items_q * a.num_q_heads)), block(256);
+static SchedJob small_job(int tile_rows, int partner_rows, CostMode mode, void* ws, const SchedLayout& lay) {
+    char* base = (char*)ws;
+    return SchedJob{tile_rows, partner_rows, (int)mode, (int)lay.max_items, (int32_t*)base,
+                    (int32_t*)(base + lay.tile_off_ofs), (WorkItem*)(base + lay.items_ofs)};
+}
+template <int D, bool CAUSAL>
+static hipError_t launch_dq_dc(const BwdArgs& a, hipStream_t stream) {
     auto q = (const __bf16*)a.q; auto k = (const __bf16*)a.k; auto v = (const __bf16*)a.v;
     auto dO = (const __bf16*)a.dout;
     auto o = (const __bf16*)a.o;
     auto st = (float2*)a.stats;
-    if constexpr (D != 80) {  // (head_dim 80 keeps the phased dq_kernel: see dq_kernel_direct)
-        if (a.causal)
-            hipLaunchKernelGGL((dq_kernel_direct<D, true>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st,
-                               (__bf16*)a.dq, a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens,
-                               a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dq);
-        else
-            hipLaunchKernelGGL((dq_kernel_direct<D, false>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st,
-                               (__bf16*)a.dq, a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens,
-                               a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dq);
-    } else {
-        if (a.causal)
-            hipLaunchKernelGGL((dq_kernel<D, true>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st,
-                               (__bf16*)a.dq, a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens,
-                               a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dq);
-        else
-            hipLaunchKernelGGL((dq_kernel<D, false>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st,
-                               (__bf16*)a.dq, a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens,
-                               a.num_q_heads, a.num_kv_heads, a.scale, a.clock_probe_dq);
+    DqSmall sm = {};
+    if (a.small) {
+        sm = DqSmall{a.cu_seqlens, a.num_seqs, a.plan_q, a.part_dq,
+                     small_job(BWD_TILE_KV, BWD_STEP_Q, CAUSAL ? COST_CAUSAL_KEY : COST_FULL, a.ws_kv, a.lay_kv),
+                     small_job(BWD_TILE_Q, BWD_STEP_KV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, a.ws_q, a.lay_q)};
     }
+    dim3 grid((unsigned)(a.max_items_q * a.num_q_heads * a.plan_q.max_chunks + (a.small ? 2 : 0))), block(256);
+#define VA_DQ_LAUNCH(KERNEL, SMALL)                                                                                      \
+    hipLaunchKernelGGL((KERNEL<D, CAUSAL, SMALL>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st, (__bf16*)a.dq,     \
+                       a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens, a.num_q_heads, a.num_kv_heads,      \
+                       a.scale, sm, a.clock_probe_dq)
+    if constexpr (D != 80) {  // (head_dim 80 keeps the phased dq_kernel: see dq_kernel_direct)
+        if (a.small) VA_DQ_LAUNCH(dq_kernel_direct, true); else VA_DQ_LAUNCH(dq_kernel_direct, false);
+    } else {
+        if (a.small) VA_DQ_LAUNCH(dq_kernel, true); else VA_DQ_LAUNCH(dq_kernel, false);
+    }
+#undef VA_DQ_LAUNCH
     return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_dq_d(const BwdArgs& a, hipStream_t stream) {
+    return a.causal ? launch_dq_dc<D, true>(a, stream) : launch_dq_dc<D, false>(a, stream);
 }
 
 #if VA_BWD_PART == 2
 hipError_t launch_dq_128(const BwdArgs& a, hipStream_t stream) { return launch_dq_d<128>(a, stream); }
 #elif VA_BWD_PART == 0
+int bwd_dq_slots(int head_dim) { return 256 * (head_dim == 64 ? kDqWgsPerCu<64> : kDqWgsPerCu<128>); }
+
+// Sum of the chunks the small-launch backward left (fp32, in chunk order): one workgroup per (tile, quarter of its
+// rows, head), the query tiles' dQ first, then the key tiles' dK and dV; tiles that were not split are already done.
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256)
+bwd_sum_small(const float* __restrict__ part_dq, const float* __restrict__ part_dk, const float* __restrict__ part_dv,
+              __bf16* __restrict__ dQ, __bf16* __restrict__ dK, __bf16* __restrict__ dV, const int32_t* __restrict__ cu,
+              int num_seqs, int wgs_q, int T, int Hq, int Hkv, float scale, SmallPlan plan_q, SmallPlan plan_kv) {
+    constexpr int CPR = D / 8, ROWS = 32;  // 16-byte output pieces per row; rows per workgroup
+    static_assert(BWD_TILE_Q == 4 * ROWS && BWD_TILE_KV == 4 * ROWS, "quarters of a tile");
+    const bool is_q = (int)blockIdx.x < wgs_q;
+    const unsigned bid = is_q ? blockIdx.x : blockIdx.x - wgs_q;
+    const int H = is_q ? Hq : Hkv;
+    const int h = __builtin_amdgcn_readfirstlane((int)(bid % (unsigned)H));
+    const int quarter = __builtin_amdgcn_readfirstlane((int)(bid / (unsigned)H & 3));
+    // (one workgroup per tile, not per chunk: only the chunk-0 entries, which come first, are asked for)
+    SmallTile tl;
+    if (!small_tile(cu, num_seqs, T, is_q ? dq_small_shape<CAUSAL>(Hq, plan_q) : dkdv_small_shape<CAUSAL>(Hq, Hkv, plan_kv),
+                    __builtin_amdgcn_readfirstlane((int)(bid / (unsigned)(4 * H))), tl) ||
+        tl.ch > 0 || tl.nch == 1)
+        return;
+    const int L = tl.len, r0 = tl.tile * BWD_TILE_Q, nch = tl.nch;
+    const size_t stride = (size_t)T * H * D;
+    for (int u = threadIdx.x; u < ROWS * CPR * (is_q ? 1 : 2); u += 256) {
+        const bool second = u >= ROWS * CPR;  // dV
+        const int x = second ? u - ROWS * CPR : u;
+        const int row = r0 + quarter * ROWS + x / CPR;
+        if (row >= L) continue;
+        const size_t off = ((size_t)(tl.begin + row) * H + h) * D + 8 * (x % CPR);
+        const float* p = (is_q ? part_dq : second ? part_dv : part_dk) + off;
+        float4 v[VA_SMALL_CHUNKS][2];
+#pragma unroll
+        for (int i = 0; i < VA_SMALL_CHUNKS; ++i)  // (all loads in flight together)
+            if (i < nch) { v[i][0] = *(const float4*)(p + i * stride); v[i][1] = *(const float4*)(p + i * stride + 4); }
+        float acc[8] = {v[0][0].x, v[0][0].y, v[0][0].z, v[0][0].w, v[0][1].x, v[0][1].y, v[0][1].z, v[0][1].w};
+#pragma unroll
+        for (int i = 1; i < VA_SMALL_CHUNKS; ++i)
+            if (i < nch) {
+                acc[0] += v[i][0].x; acc[1] += v[i][0].y; acc[2] += v[i][0].z; acc[3] += v[i][0].w;
+                acc[4] += v[i][1].x; acc[5] += v[i][1].y; acc[6] += v[i][1].z; acc[7] += v[i][1].w;
+            }
+        const float f = second ? 1.f : scale;
+        bf16x8 out;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] = (__bf16)(acc[e] * f);
+        *(bf16x8*)((is_q ? dQ : second ? dV : dK) + off) = out;
+    }
+}
+
+template <int D>
+static hipError_t launch_sum_d(const BwdArgs& a, hipStream_t stream) {
+    const int wgs_q = a.plan_q.max_chunks > 1 ? (int)(a.max_items_q * a.num_q_heads * 4) : 0;
+    const int wgs_kv = a.plan_kv.max_chunks > 1 ? (int)(a.max_items_kv * a.num_kv_heads * 4) : 0;
+    auto dq = (__bf16*)a.dq; auto dk = (__bf16*)a.dk; auto dv = (__bf16*)a.dv;
+    if (a.causal)
+        hipLaunchKernelGGL((bwd_sum_small<D, true>), dim3(wgs_q + wgs_kv), dim3(256), 0, stream, a.part_dq, a.part_dk,
+                           a.part_dv, dq, dk, dv, a.cu_seqlens, a.num_seqs, wgs_q, a.total_tokens,
+                           a.num_q_heads, a.num_kv_heads, a.scale, a.plan_q, a.plan_kv);
+    else
+        hipLaunchKernelGGL((bwd_sum_small<D, false>), dim3(wgs_q + wgs_kv), dim3(256), 0, stream, a.part_dq, a.part_dk,
+                           a.part_dv, dq, dk, dv, a.cu_seqlens, a.num_seqs, wgs_q, a.total_tokens,
+                           a.num_q_heads, a.num_kv_heads, a.scale, a.plan_q, a.plan_kv);
+    return hipGetLastError();
+}
+hipError_t launch_bwd_sum_small(const BwdArgs& a, hipStream_t stream) {
+    switch (a.head_dim) {
+        case 64: return launch_sum_d<64>(a, stream);
+        case 80: return launch_sum_d<80>(a, stream);
+        case 96: return launch_sum_d<96>(a, stream);
+        case 128: return launch_sum_d<128>(a, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_bwd_dq(const BwdArgs& a, hipStream_t stream) {
     switch (a.head_dim) {
         case 64: return launch_dq_d<64>(a, stream);

@@ -13,6 +13,7 @@
 // prefetch was measured to expose (about a third of the kernel time).
 #include "va_device.h"
 #include "va_internal.h"
+#include "va_small.h"
 
 namespace va {
 
@@ -21,7 +22,7 @@ struct FwdCfg {
     using T = LdsTile<D>;
     // Key tiles of 64 rows; 32 at head_dim 128, where the smaller tiles (and the 16 score registers they save)
     // are what lets three workgroups share a CU instead of two.
-    static constexpr int BQ = FWD_TILE_Q, BKV = D == 128 ? 32 : FWD_TILE_KV;
+    static constexpr int BQ = FWD_TILE_Q, BKV = fwd_tile_kv(D);
     static constexpr int NB = BKV / 32;                // 32-key blocks of S^T per tile
     static constexpr int KS = D / 16;                  // 16-deep steps of QK^T
     static constexpr int DB = (D + 31) / 32;           // 32-wide blocks of O^T rows
@@ -216,49 +217,81 @@ constexpr int kFwdWgsPerCu = D == 64 ? 4 : (D <= 80 || D == 128) ? 3 : 2;
 template <int D>
 constexpr int kFwdLeanWgsPerCu = (D <= 80 || D == 128) ? 3 : 2;
 
+// How a workgroup comes by its work, and what it loads.
+//   FWD_GENERAL  the tile its work-list entry names; loads past the item's last tile are issued all the same (they
+//                re-fetch the last tile into a free slot), which keeps the loop free of branches and its wait counts
+//                constant.
+//   FWD_LEAN     (batches of short samples) the same without the loads past the last tile: an item of one or two tiles
+//                would wait for two more memory round trips than it has use for, and in that regime the round trips
+//                are all there is.
+//   FWD_SMALL    (launches that do not fill the chip) the tile and the chunk of its keys found from cu_seqlens, see
+//                va_small.h; loads as FWD_LEAN.
+enum FwdMode { FWD_GENERAL, FWD_LEAN, FWD_SMALL };
+
+struct FwdSmall {  // FWD_SMALL only
+    const int32_t* cu;
+    int num_seqs;
+    SmallPlan plan;
+};
+template <int D, bool CAUSAL>
+__device__ __forceinline__ SmallShape fwd_small_shape(const FwdSmall& sm, int heads) {
+    return SmallShape{FwdCfg<D>::BQ, FwdCfg<D>::BKV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, heads, 1, sm.plan};
+}
+
 // One work item: the query tile `wid` names (see xcd_item_head), all its key tiles.  `lds` is the workgroup's
 // staging memory, 5 tiles (K x3, then V x2).
-// LEAN (batches of short samples): loads past the item's last tile are not issued.  The general form
-// issues them regardless (they re-fetch the last tile into a free slot), which keeps its loop free of
-// branches and its wait counts constant; an item of one or two tiles, though, then waits for two more
-// memory round trips than it has use for, and in that regime the round trips are all there is.
-template <int D, bool CAUSAL, bool LEAN = false>
+template <int D, bool CAUSAL, FwdMode MODE>
 __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, const __bf16* __restrict__ Q,
                                               const __bf16* __restrict__ K, const __bf16* __restrict__ V,
                                               __bf16* __restrict__ O, float* __restrict__ LSE,
                                               const int32_t* __restrict__ hdr, const WorkItem* __restrict__ items,
                                               int max_items, int T, int Hq, int Hkv, float scale, int S,
                                               float* __restrict__ part_o, float* __restrict__ part_lse,
-                                              unsigned long long* __restrict__ clock_probe) {
+                                              const FwdSmall& small, unsigned long long* __restrict__ clock_probe) {
     using C = FwdCfg<D>;
     using LT = LdsTile<D>;
+    constexpr bool LEAN = MODE != FWD_GENERAL;
 
-    // S > 1: the key tiles of every query tile are split into S consecutive chunks, one workgroup
-    // each, which write partial results (fp32 O and LSE per chunk) that a merge kernel combines.  Used
-    // for launches too small to fill the chip (few heads, one mid-length sample).
-    const int ch = S > 1 ? (int)(wid % S) : 0;
-    const unsigned bid = S > 1 ? wid / S : wid;
-    int item, hp;
-    // (LEAN: always the item-major order, which is what the scheduler picks for short samples anyway; not
-    // reading it from the header lets the work item's own load start at once, next to the header's)
-    xcd_item_head(bid, max_items, Hq, Hkv, LEAN ? 1 : hdr[1], item, hp);
-    // (integer division runs on the vector ALU; make the results scalar again, so that what is derived
-    // from them stays in scalar registers)
-    item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);
-    if (!LEAN && item >= hdr[0]) return;
+    // S > 1: the key tiles of every query tile are split into S consecutive chunks (FWD_SMALL: into as many as its
+    // plan gives), one workgroup each, which write partial results (fp32 O and LSE per
+    // chunk) that a merge kernel combines.  Used for launches too small to fill the chip (few heads, one
+    // mid-length sample).
+    int ch, hp;
+    SmallTile tl = {};
+    WorkItem it;
     ClockProbe wg_clock;
-    wg_clock.begin(clock_probe);
+    if constexpr (MODE == FWD_SMALL) {
+        hp = __builtin_amdgcn_readfirstlane((int)(wid % (unsigned)Hq));
+        if (!small_tile(small.cu, small.num_seqs, T, fwd_small_shape<D, CAUSAL>(small, Hq),
+                        __builtin_amdgcn_readfirstlane((int)(wid / (unsigned)Hq)), tl))
+            return;
+        ch = tl.ch;
+        wg_clock.begin(clock_probe);
+    } else {
+        int item;
+        ch = S > 1 ? (int)(wid % S) : 0;
+        const unsigned bid = S > 1 ? wid / S : wid;
+        // (LEAN: always the item-major order, which is what the scheduler picks for short samples anyway; not
+        // reading it from the header lets the work item's own load start at once, next to the header's)
+        xcd_item_head(bid, max_items, Hq, Hkv, LEAN ? 1 : hdr[1], item, hp);
+        // (integer division runs on the vector ALU; make the results scalar again, so that what is derived
+        // from them stays in scalar registers)
+        item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);
+        if (!LEAN && item >= hdr[0]) return;
+        wg_clock.begin(clock_probe);
+        // (LEAN: an entry past the live ones is inside the list's memory, whatever it holds; it is only looked at
+        // after the check)
+        it = items[item];
+        if (LEAN && item >= hdr[0]) return;
+    }
     // Head slots count the kv heads first, so that (with Hkv a multiple of the 8 XCDs) every XCD's L2
     // only ever sees its own kv heads.
     const int kvh = hp % Hkv;
     const int h = kvh * (Hq / Hkv) + hp / Hkv;
-    // (LEAN: an entry past the live ones is inside the list's memory, whatever it holds; it is only looked at
-    // after the check)
-    const WorkItem it = items[item];
-    if (LEAN && item >= hdr[0]) return;
     // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
-    const int sb = __builtin_amdgcn_readfirstlane(it.y), L = __builtin_amdgcn_readfirstlane(it.z - it.y),
-              q0 = __builtin_amdgcn_readfirstlane(it.x - it.y);  // q0: tile start inside the sample
+    const int sb = MODE == FWD_SMALL ? tl.begin : __builtin_amdgcn_readfirstlane(it.y),
+              L = MODE == FWD_SMALL ? tl.len : __builtin_amdgcn_readfirstlane(it.z - it.y),
+              q0 = MODE == FWD_SMALL ? tl.tile * C::BQ : __builtin_amdgcn_readfirstlane(it.x - it.y);  // tile start inside the sample
 
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
     const int qrow = q0 + 32 * w + ln;  // this lane's query row inside the sample
@@ -274,8 +307,10 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     const bool few_keys = keys_unmasked < 64;
     const int n_plain = few_keys ? 0 : keys_unmasked / C::BKV;
     const int n_lo = few_keys ? 64 / C::BKV : 0;
-    const int jb = S > 1 ? ntiles * ch / S : 0, je = S > 1 ? ntiles * (ch + 1) / S : ntiles;  // this chunk's tiles
-    if (jb >= je) {  // fewer tiles than chunks: an empty part (its O is never read)
+    const int nch = MODE == FWD_SMALL ? tl.nch : S;  // chunks of this tile
+    const bool split = nch > 1;
+    const int jb = split ? ntiles * ch / nch : 0, je = split ? ntiles * (ch + 1) / nch : ntiles;  // this chunk's tiles
+    if (MODE != FWD_SMALL && jb >= je) {  // fewer tiles than chunks: an empty part (its O is never read)
         if (qvalid && hh == 0) part_lse[((size_t)ch * Hq + h) * T + sb + qrow] = -INFINITY;
         return;
     }
@@ -420,7 +455,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     const float row_lse = ltot > 0.f ? m * scale + __logf(ltot) : -INFINITY;
     if (qvalid) {
-        if (S > 1) {
+        if (split) {
             float* op = part_o + (((size_t)ch * T + sb + qrow) * Hq + h) * D;
 #pragma unroll
             for (int db = 0; db < C::DB; ++db)
@@ -460,8 +495,8 @@ fwd_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __b
            const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale, int S,
            float* __restrict__ part_o, float* __restrict__ part_lse, unsigned long long* __restrict__ clock_probe) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[5 * FwdCfg<D>::TILE];  // K x3, then V x2
-    fwd_work_item<D, CAUSAL>(blockIdx.x, lds, Q, K, V, O, LSE, hdr, items, max_items, T, Hq, Hkv, scale, S, part_o,
-                             part_lse, clock_probe);
+    fwd_work_item<D, CAUSAL, FWD_GENERAL>(blockIdx.x, lds, Q, K, V, O, LSE, hdr, items, max_items, T, Hq, Hkv, scale, S,
+                                          part_o, part_lse, FwdSmall{}, clock_probe);
 }
 
 // The same for batches of short samples only (the caller's max_seqlen says so): the LEAN form of the work
@@ -478,34 +513,127 @@ fwd_kernel_lean(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, cons
                 const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale,
                 unsigned long long* __restrict__ clock_probe) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[5 * FwdCfg<D>::TILE];
-    fwd_work_item<D, CAUSAL, true>(blockIdx.x, lds, Q, K, V, O, LSE, hdr, items, max_items, T, Hq, Hkv, scale, 1,
-                                   nullptr, nullptr, clock_probe);
+    fwd_work_item<D, CAUSAL, FWD_LEAN>(blockIdx.x, lds, Q, K, V, O, LSE, hdr, items, max_items, T, Hq, Hkv, scale, 1,
+                                       nullptr, nullptr, FwdSmall{}, clock_probe);
+}
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, (kFwdLeanWgsPerCu<D>))
+fwd_kernel_small(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+                 __bf16* __restrict__ O, float* __restrict__ LSE, FwdSmall small, int T, int Hq, int Hkv, float scale,
+                 float* __restrict__ part_o, float* __restrict__ part_lse,
+                 unsigned long long* __restrict__ clock_probe) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[5 * FwdCfg<D>::TILE];
+    fwd_work_item<D, CAUSAL, FWD_SMALL>(blockIdx.x, lds, Q, K, V, O, LSE, nullptr, nullptr, 0, T, Hq, Hkv, scale, 1,
+                                        part_o, part_lse, small, clock_probe);
+}
+
+// Merge of the chunks fwd_kernel_small left: one workgroup per (query tile, quarter of its rows, head); tiles that were
+// not split are already done.  Eight output channels per thread.
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256)
+fwd_merge_small(const float* __restrict__ part_o, const float* __restrict__ part_lse, __bf16* __restrict__ O,
+                float* __restrict__ LSE, FwdSmall small, int T, int Hq) {
+    using C = FwdCfg<D>;
+    constexpr int CPR = D / 8, ROWS = C::BQ / 4;
+    const int h = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)Hq));
+    const int q = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)Hq));
+    SmallTile tl;
+    // (one workgroup per tile, not per chunk: only the chunk-0 entries, which come first, are asked for)
+    if (!small_tile(small.cu, small.num_seqs, T, fwd_small_shape<D, CAUSAL>(small, Hq), q / 4, tl) || tl.ch > 0) return;
+    const int q0 = tl.tile * C::BQ, nch = tl.nch;
+    if (nch == 1) return;
+    const size_t o_stride = (size_t)T * Hq * D, lse_stride = (size_t)Hq * T;
+    for (int u = threadIdx.x; u < ROWS * CPR; u += 256) {
+        const int row = q0 + (q & 3) * ROWS + u / CPR, c = u % CPR;
+        if (row >= tl.len) return;
+        const size_t t = (size_t)tl.begin + row;
+        const float* lp = part_lse + (size_t)h * T + t;
+        const float* op = part_o + (t * Hq + h) * D + 8 * c;
+        float lv[VA_SMALL_CHUNKS];
+        float4 v[VA_SMALL_CHUNKS][2];
+#pragma unroll
+        for (int p = 0; p < VA_SMALL_CHUNKS; ++p) {  // (all loads in flight together)
+            lv[p] = -INFINITY;
+            if (p < nch) {
+                lv[p] = lp[p * lse_stride];
+                v[p][0] = *(const float4*)(op + p * o_stride);
+                v[p][1] = *(const float4*)(op + p * o_stride + 4);
+            }
+        }
+        float mx = lv[0];
+#pragma unroll
+        for (int p = 1; p < VA_SMALL_CHUNKS; ++p) mx = fmaxf(mx, lv[p]);
+        float den = 0.f, acc[8] = {};
+#pragma unroll
+        for (int p = 0; p < VA_SMALL_CHUNKS; ++p)
+            if (p < nch) {  // (a chunk beyond the row under the causal mask: LSE -inf, weight 0, O finite)
+                const float wgt = __expf(lv[p] - mx);
+                den += wgt;
+                acc[0] += wgt * v[p][0].x; acc[1] += wgt * v[p][0].y; acc[2] += wgt * v[p][0].z; acc[3] += wgt * v[p][0].w;
+                acc[4] += wgt * v[p][1].x; acc[5] += wgt * v[p][1].y; acc[6] += wgt * v[p][1].z; acc[7] += wgt * v[p][1].w;
+            }
+        const float inv = 1.f / den;
+        bf16x8 out;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] = (__bf16)(acc[e] * inv);
+        *(bf16x8*)(O + (t * Hq + h) * D + 8 * c) = out;
+        if (c == 0) LSE[(size_t)h * T + t] = mx + __logf(den);
+    }
+}
+
+template <int D, bool CAUSAL>
+static hipError_t launch_dc(const FwdArgs& a, hipStream_t stream) {
+    dim3 grid((unsigned)(a.max_items * a.num_q_heads * a.kv_splits)), block(256);
+    auto q = (const __bf16*)a.q; auto k = (const __bf16*)a.k; auto v = (const __bf16*)a.v;
+    auto o = (__bf16*)a.o;
+    const int T = a.total_tokens, Hq = a.num_q_heads, Hkv = a.num_kv_heads, S = a.kv_splits;
+    if (a.small) {
+        const FwdSmall sm{a.cu_seqlens, a.num_seqs, a.plan};
+        hipLaunchKernelGGL((fwd_kernel_small<D, CAUSAL>), grid, block, 0, stream, q, k, v, o, a.lse, sm, T, Hq, Hkv,
+                           a.scale, a.part_o, a.part_lse, a.clock_probe);
+    } else if (a.lean) {  // batches of short samples (see fwd_kernel_lean); never with split keys
+        hipLaunchKernelGGL((fwd_kernel_lean<D, CAUSAL>), grid, block, 0, stream, q, k, v, o, a.lse, a.sched_hdr,
+                           a.items, (int)a.max_items, T, Hq, Hkv, a.scale, a.clock_probe);
+    } else {
+        hipLaunchKernelGGL((fwd_kernel<D, CAUSAL>), grid, block, 0, stream, q, k, v, o, a.lse, a.sched_hdr, a.items,
+                           (int)a.max_items, T, Hq, Hkv, a.scale, S, a.part_o, a.part_lse, a.clock_probe);
+    }
+    return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_d(const FwdArgs& a, hipStream_t stream) {
-    dim3 grid((unsigned)(a.max_items * a.num_q_heads * a.kv_splits)), block(256);
-    auto q = (const __bf16*)a.q; auto k = (const __bf16*)a.k; auto v = (const __bf16*)a.v;
-    if (a.lean) {  // batches of short samples (see fwd_kernel_lean); never with split keys
-        if (a.causal)
-            hipLaunchKernelGGL((fwd_kernel_lean<D, true>), grid, block, 0, stream, q, k, v, (__bf16*)a.o, a.lse,
-                               a.sched_hdr, a.items, (int)a.max_items, a.total_tokens, a.num_q_heads, a.num_kv_heads,
-                               a.scale, a.clock_probe);
-        else
-            hipLaunchKernelGGL((fwd_kernel_lean<D, false>), grid, block, 0, stream, q, k, v, (__bf16*)a.o, a.lse,
-                               a.sched_hdr, a.items, (int)a.max_items, a.total_tokens, a.num_q_heads, a.num_kv_heads,
-                               a.scale, a.clock_probe);
-        return hipGetLastError();
-    }
+    return a.causal ? launch_dc<D, true>(a, stream) : launch_dc<D, false>(a, stream);
+}
+
+template <int D>
+static hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream) {
+    const FwdSmall sm{a.cu_seqlens, a.num_seqs, a.plan};
+    dim3 grid((unsigned)(a.max_items * a.num_q_heads * 4)), block(256);
     if (a.causal)
-        hipLaunchKernelGGL((fwd_kernel<D, true>), grid, block, 0, stream, q, k, v, (__bf16*)a.o, a.lse,
-                           a.sched_hdr, a.items, (int)a.max_items, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale,
-                           a.kv_splits, a.part_o, a.part_lse, a.clock_probe);
+        hipLaunchKernelGGL((fwd_merge_small<D, true>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
+                           sm, a.total_tokens, a.num_q_heads);
     else
-        hipLaunchKernelGGL((fwd_kernel<D, false>), grid, block, 0, stream, q, k, v, (__bf16*)a.o, a.lse,
-                           a.sched_hdr, a.items, (int)a.max_items, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale,
-                           a.kv_splits, a.part_o, a.part_lse, a.clock_probe);
+        hipLaunchKernelGGL((fwd_merge_small<D, false>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
+                           sm, a.total_tokens, a.num_q_heads);
     return hipGetLastError();
+}
+
+hipError_t launch_fwd_merge_small(const FwdArgs& a, hipStream_t stream) {
+    switch (a.head_dim) {
+        case 64: return launch_merge_d<64>(a, stream);
+        case 80: return launch_merge_d<80>(a, stream);
+        case 96: return launch_merge_d<96>(a, stream);
+        case 128: return launch_merge_d<128>(a, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// Workgroups of fwd_kernel_small the chip runs at a time.
+int fwd_small_slots(int head_dim) {
+    return 256 * (head_dim == 64 ? kFwdLeanWgsPerCu<64> : head_dim == 80 ? kFwdLeanWgsPerCu<80>
+                  : head_dim == 96 ? kFwdLeanWgsPerCu<96> : kFwdLeanWgsPerCu<128>);
 }
 
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t stream) {

@@ -65,6 +65,13 @@ hipError_t launch_scheduler_pair(const int32_t* cu_seqlens, int num_seqs, int to
 hipError_t launch_check_cu_seqlens(const int32_t* cu_seqlens, int num_seqs, int total_tokens, int32_t* verdict,
                                    hipStream_t stream);
 
+// How the walks of a small launch (va_small.h) are cut.
+struct SmallPlan {
+    int max_chunks;  // per tile; 1: not at all
+    int target;      // workgroups to come to
+    int chunk;       // partner tiles per chunk, 0: worked out on the device from `target` and the samples' lengths
+};
+
 struct FwdArgs {
     const void *q, *k, *v;
     void* o;
@@ -79,11 +86,20 @@ struct FwdArgs {
     float* part_lse;  // kv_splits > 1: fp32 [kv_splits, Hq, T]
     unsigned long long* clock_probe;  // null, or 2 counters (see ClockProbe)
     bool lean;  // batches of short samples (the caller's max_seqlen says so), kv_splits == 1: the lean kernel form
+    bool small;  // launches that do not fill the chip (va_small.h): no work list, kv_splits = most chunks per tile
+    const int32_t* cu_seqlens;
+    int num_seqs;
+    SmallPlan plan;
 };
+constexpr int VA_SMALL_CHUNKS = 8;     // most chunks a tile of a small launch is cut into
+constexpr int VA_SMALL_MAX_SEQS = 64;  // a small launch has one lane per sample
 constexpr int kShortBatchMaxSeqlen = 1024;  // max_seqlen hint up to which a batch counts as "short samples only"
 constexpr int FWD_TILE_Q = 128;
 constexpr int FWD_TILE_KV = 64;
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t stream);
+hipError_t launch_fwd_merge_small(const FwdArgs& a, hipStream_t stream);
+int fwd_small_slots(int head_dim);  // workgroups of the small-launch forward the chip runs at a time
+constexpr int fwd_tile_kv(int head_dim) { return head_dim == 128 ? 32 : FWD_TILE_KV; }  // key rows per step
 
 struct BwdArgs {
     const void *dout, *q, *k, *v, *o;
@@ -99,7 +115,20 @@ struct BwdArgs {
     int total_tokens, num_q_heads, num_kv_heads, head_dim, causal;
     float scale;
     unsigned long long *clock_probe_dkdv, *clock_probe_dq;  // null, or 2 counters each (see ClockProbe)
+    // Launches that do not fill the chip (va_small.h): dQ finds its tiles from cu_seqlens and its launch builds the
+    // work lists on the side (dK/dV and the sum of the chunks go by them); a tile may be cut into chunks.
+    bool small;
+    const int32_t* cu_seqlens;
+    int num_seqs;
+    SmallPlan plan_q, plan_kv;
+    float *part_dq;            // plan_q.max_chunks > 1: fp32 [max_chunks, T, Hq, D], without the softmax scale
+    float *part_dk, *part_dv;  // plan_kv.max_chunks > 1: fp32 [max_chunks, T, Hkv, D] each, dK without the scale
+    void *ws_kv, *ws_q;        // where the lists go
+    SchedLayout lay_kv, lay_q;
 };
+int bwd_dq_slots(int head_dim);    // workgroups of the dQ / dK/dV kernel the chip runs at a time
+int bwd_dkdv_slots(int head_dim);
+hipError_t launch_bwd_sum_small(const BwdArgs& a, hipStream_t stream);
 constexpr int BWD_TILE_KV = 128;  // rows of K/V one dK/dV workgroup owns
 constexpr int BWD_STEP_Q = 64;    // query rows it stages per step
 constexpr int BWD_TILE_Q = 128;   // rows of Q one dQ workgroup owns

@@ -1,0 +1,118 @@
+// Launches too small to fill the chip (few heads of one sample, a handful of short samples): every workgroup works out
+// its own tile from cu_seqlens instead of reading it from a work list, which saves the scheduler launch in front
+// (4-5 us of work and the gap behind it, a third of a call on a few hundred tokens), and a tile's walk over its
+// partner tiles is cut into chunks of equal length, so that the launch has as many workgroups as the chip has room for.
+//
+// The path is taken when a batch has at most 64 samples (one lane per sample) and fewer (tile, head) pairs than
+// workgroups fit on the chip.  Beyond that the order of the list matters (heaviest tiles first) and its launch is
+// lost in the noise.
+//
+// What bounds such a launch: the walk of the longest tile, while most of the chip idles; then, once cut, the memory
+// round trips and the fragments of each chunk's start (3-9 us), its fp32 results (64 or 128 KB written and read again
+// at 5 TB/s), and that a workgroup alone on its CU steps no faster than 1.5-2 times the rate two of them have together.
+// Measured, forward + backward: one sample of 4096 tokens, 2 heads of 128, causal, 223 -> 92 us (dQ 84 -> 27, dK/dV
+// 102 -> 31 us, 10 us for their sums); 8191 tokens, 4 query heads on one kv head, 1000 -> 361 us (forward 107 -> 97, dQ
+// 167 -> 122, dK/dV 717 -> 146 us); four samples of 246 tokens in all, forward, 16.6 -> 13.3 us.
+#pragma once
+#include "va_device.h"
+#include "va_internal.h"
+
+namespace va {
+
+// Inclusive prefix sum / maximum over the 64 lanes (all of them active; values >= 0) on DPP row shifts.
+template <bool MAX>
+__device__ __forceinline__ int wave_incl_scan(int x) {
+    auto join = [](int a, int b) { return MAX ? max(a, b) : a + b; };
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+    x = join(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Partner tiles a chunk holds at most so that `total` partner tiles in `tiles` (tile, head) pairs, the longest walk being
+// `longest`, come to at most `target` workgroups: sum ceil(steps / C) <= total / C + tiles.
+__host__ __device__ inline int chunk_steps(int total, int tiles, int longest, int target, int max_chunks) {
+    const int least = (longest + max_chunks - 1) / max_chunks;
+    if (target <= tiles) return longest > 1 ? longest : 1;
+    const int c = (total + target - tiles - 1) / (target - tiles);
+    return c > least ? c : (least > 1 ? least : 1);
+}
+// Chunks of a tile with `steps` partner tiles; chunk i covers [steps * i / n, steps * (i + 1) / n).
+__host__ __device__ inline int chunk_count(int steps, int chunk, int max_chunks) {
+    const int n = (steps + chunk - 1) / chunk;
+    return n < max_chunks ? (n > 0 ? n : 1) : max_chunks;
+}
+
+// Tiles, of a sample of n tiles of r partner tiles each (nu partner tiles in all), that meet more than `past` of them.
+__host__ __device__ inline int tiles_with_chunk(int n, int nu, int r, int mode, int past) {
+    if (nu <= past) return 0;
+    if (mode == COST_FULL) return n;
+    const int k = mode == COST_CAUSAL_QUERY ? n - past / r : (nu - past + r - 1) / r;
+    return k < 1 ? 1 : (k < n ? k : n);
+}
+
+struct SmallShape {  // of a launch
+    int rows, partner_rows;  // R, U: rows per tile and per partner tile
+    int mode;                // CostMode
+    int heads, per_pair;     // `heads` workgroups walk each tile, `per_pair` times its partner tiles each
+    SmallPlan plan;
+};
+struct SmallTile {
+    int begin, len;  // first packed row and length of the sample
+    int tile;        // tile index inside the sample
+    int steps;       // partner tiles it meets, times per_pair
+    int ch, nch;     // chunk, chunks of the tile
+    __device__ __forceinline__ int first_step() const { return (int)((int64_t)steps * ch / nch); }
+    __device__ __forceinline__ int end_step() const { return (int)((int64_t)steps * (ch + 1) / nch); }
+};
+// The idx-th (tile, chunk) of a batch of B <= 64 samples; false if there are not that many.
+// First every tile's chunk 0, then the chunks 1 of the tiles that have one, and so on: no index in between is without
+// work.  (Workgroup ids go round-robin over the XCDs and their shader engines, wherever there is room; a launch
+// with holes in it leaves some of them with two workgroups per CU, one after the other, and others with none: measured
+// twice the time.)  Inside a sample the heaviest tiles come first.
+// Must be reached by all 64 lanes; every result is wave-uniform.
+__device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B, int T, const SmallShape& p, int idx,
+                                           SmallTile& out) {
+    const int lane = threadIdx.x & 63;
+    int begin = 0, end = 0;
+    if (lane < B) sched_sample_rows(cu[lane], cu[lane + 1], T, begin, end);
+    const int len = end - begin, R = p.rows, r = p.rows / p.partner_rows;
+    const int n = (len + R - 1) / R, nu = (len + p.partner_rows - 1) / p.partner_rows;
+    int chunk = 1 << 30, count = n, incl = 0, ch = 0;
+    for (;; ++ch) {  // count: this lane's tiles that have a chunk ch
+        incl = wave_incl_scan<false>(count);
+        const int here = __builtin_amdgcn_readlane(incl, 63);
+        if (ch == 0 && p.plan.max_chunks > 1) {
+            chunk = p.plan.chunk;
+            if (chunk == 0) {
+                // partner tiles of a sample: n tiles of nu, minus what the causal masks take off (r of them per tile)
+                const int off = p.mode == COST_FULL ? 0 : n * (n - 1) / 2 * r;
+                const int sum = p.mode == COST_CAUSAL_QUERY ? (n > 0 ? off + nu : 0) : n * nu - off;
+                const int total = __builtin_amdgcn_readlane(wave_incl_scan<false>(sum), 63) * p.heads * p.per_pair;
+                const int longest = __builtin_amdgcn_readlane(wave_incl_scan<true>(nu), 63) * p.per_pair;
+                chunk = __builtin_amdgcn_readfirstlane(
+                    chunk_steps(total, here * p.heads, longest, p.plan.target, p.plan.max_chunks));
+            }
+        }
+        if (idx < here) break;
+        if (ch + 1 >= p.plan.max_chunks) return false;
+        idx -= here;
+        count = tiles_with_chunk(n, nu, r, p.mode, (ch + 1) * chunk / p.per_pair);
+    }
+    const int s = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= idx));  // samples before the one that holds idx
+    const int t = idx - (__builtin_amdgcn_readlane(incl, s) - __builtin_amdgcn_readlane(count, s));
+    const int ns = __builtin_amdgcn_readlane(n, s), us = __builtin_amdgcn_readlane(nu, s);
+    out.begin = __builtin_amdgcn_readlane(begin, s);
+    out.len = __builtin_amdgcn_readlane(len, s);
+    out.tile = p.mode == COST_CAUSAL_QUERY ? ns - 1 - t : t;
+    out.steps = (p.mode == COST_FULL ? us : p.mode == COST_CAUSAL_QUERY ? min(us, (out.tile + 1) * r) : us - out.tile * r) *
+                p.per_pair;
+    out.ch = ch;
+    out.nch = chunk_count(out.steps, chunk, p.plan.max_chunks);
+    return true;
+}
+
+}  // namespace va
