@@ -540,6 +540,15 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         VA_DKDV_ADVANCE()
     };
 
+    // A wave whose keys all lie beyond the sample keeps up the loads and the barriers only (see the forward kernel).
+    if (wk_lo >= L) {
+        for (int i = 0; i < total; ++i) {
+            VA_DKDV_SYNC()
+            issue_all();
+        }
+        wait_vmcnt<0>();
+        return;
+    }
     // Masked steps (the causal diagonal, the one that holds the sample's end) take the simple form: in
     // phases, with the mask and the lo parts on top, they were measured no faster even at one wave per SIMD.
     int left = total;
@@ -928,6 +937,15 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     // which every wave is done with step i - 1, whose stage this step's loads refill.
     int stage_i = 0;
     int j = wk.jb;
+    if (q0 + 32 * w >= L) {  // no row of this wave exists: loads and barriers only (see the forward kernel)
+        for (; j < je; ++j) {
+            wait_vmcnt<PER>();
+            wg_barrier();
+            issue_all();
+        }
+        wait_vmcnt<0>();
+        return;
+    }
     f32x16 nd16, zero16;  // -Delta of this lane's row as the starting value of dP; 0 for S
 #pragma unroll
     for (int r = 0; r < 16; ++r) { nd16[r] = ndelta; zero16[r] = 0.f; }
@@ -1216,6 +1234,15 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
     asm volatile("" : "+s"(always));
     const bool lo_steps = CAUSAL ? q0 == 0 : always != 0;
 
+    if (q0 + 32 * w >= L) {  // no row of this wave exists: loads and barriers only (see the forward kernel)
+        for (int j = 0; j < nsteps; ++j) {
+            wait_vmcnt<0>();
+            wg_barrier();
+            issue_step(j + 1);
+        }
+        wait_vmcnt<0>();
+        return;
+    }
     // Step j: its loads (issued during step j - 1) have landed; the barrier publishes them and tells that every
     // wave is done with step j - 1, whose stage the loads of step j + 1 may now overwrite.
     // PARITY: j % 2 where the caller knows it (-1 otherwise).  The mask-free loop runs two steps per iteration with
