@@ -333,7 +333,8 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
                         __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)Hkv)), tl))
             return;
     } else {
-        xcd_item_head(blockIdx.x, max_items, Hkv, Hkv, hdr[1], item, c);
+        if (hdr[1] == 1) short_item_head(blockIdx.x, max_items, Hkv, Hkv, D, item, c);
+        else xcd_item_head(blockIdx.x, max_items, Hkv, Hkv, kXcdChunk, item, c);
         // (integer division runs on the vector ALU: without this, everything derived from the two, the
         // staging pointers included, would be kept in vector registers and advanced there)
         item = __builtin_amdgcn_readfirstlane(item); c = __builtin_amdgcn_readfirstlane(c);
@@ -343,7 +344,12 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     wg_clock.begin(clock_probe);
     stagger_wave_priority();
     const int g = Hq / Hkv;
-    if constexpr (!SMALL) it = items[item];
+    if constexpr (!SMALL) {
+        it = items[item];
+        if (hdr[1] == 1)
+            c = __builtin_amdgcn_readfirstlane(
+                short_rotated_head(c, item, __builtin_amdgcn_readfirstlane(it.y), Hkv, Hkv, D));
+    }
     // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
     const int sb = SMALL ? tl.begin : __builtin_amdgcn_readfirstlane(it.y),
               L = SMALL ? tl.len : __builtin_amdgcn_readfirstlane(it.z - it.y),
@@ -770,7 +776,7 @@ struct DqWork {
     int sb, L, q0, h, kvh;
     int ch, nch, jb, je;  // chunk, chunks of the tile, key steps [jb, je) of this one
 };
-template <bool CAUSAL, bool SMALL>
+template <int D, bool CAUSAL, bool SMALL>
 __device__ __forceinline__ bool dq_find_work(const int32_t* __restrict__ hdr, const WorkItem* __restrict__ items,
                                              int max_items, int T, int Hq, int Hkv, const DqSmall& small,
                                              unsigned char* lds, DqWork& wk) {
@@ -792,13 +798,16 @@ __device__ __forceinline__ bool dq_find_work(const int32_t* __restrict__ hdr, co
         wk.ch = tl.ch; wk.nch = tl.nch;
         wk.jb = tl.first_step(); wk.je = tl.end_step();
     } else {
-        xcd_item_head(blockIdx.x, max_items, Hq, Hkv, hdr[1], item, hp);
+        const bool short_order = hdr[1] == 1;
+        if (short_order) short_item_head(blockIdx.x, max_items, Hq, Hkv, D, item, hp);
+        else xcd_item_head(blockIdx.x, max_items, Hq, Hkv, kXcdChunk, item, hp);
         item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);  // see dkdv_kernel
         if (item >= hdr[0]) return false;
         const WorkItem it = items[item];
         // same for the whole workgroup: tell the compiler, so that everything derived stays in SGPRs
         wk.sb = __builtin_amdgcn_readfirstlane(it.y); wk.L = __builtin_amdgcn_readfirstlane(it.z - it.y);
         wk.q0 = __builtin_amdgcn_readfirstlane(it.x - it.y);
+        if (short_order) hp = __builtin_amdgcn_readfirstlane(short_rotated_head(hp, item, wk.sb, Hq, Hkv, D));
         wk.nch = 1; wk.jb = 0;
         wk.je = ((CAUSAL ? min(wk.L, wk.q0 + BWD_TILE_Q) : wk.L) + BWD_STEP_KV - 1) / BWD_STEP_KV;
     }
@@ -836,7 +845,7 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     DqWork wk;
     ClockProbe wg_clock;
     wg_clock.begin(clock_probe);
-    if (!dq_find_work<CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
+    if (!dq_find_work<D, CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
     const int sb = wk.sb, L = wk.L, q0 = wk.q0, h = wk.h, kvh = wk.kvh;
 
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
@@ -1144,7 +1153,7 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
     DqWork wk;
     ClockProbe wg_clock;
     wg_clock.begin(clock_probe);
-    if (!dq_find_work<CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
+    if (!dq_find_work<D, CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
     const int sb = wk.sb, L = wk.L, q0 = wk.q0, h = wk.h, kvh = wk.kvh;
     const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
     const int qrow = q0 + 32 * w + ln;

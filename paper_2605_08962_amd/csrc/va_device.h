@@ -224,7 +224,8 @@ struct ClockProbe {
 //     pair of heads per XCD all its requests have the same two byte offsets inside the token rows, and the
 //     memory side serves them 5-25 % slower (measured: 64-token samples at head_dim 64, forward 193 -> 155 us,
 //     dQ 311 -> 237 us, dK/dV 339 -> 289 us; no difference in the chunked order, where L2 serves the reads).
-// The scheduler kernel picks the chunk from the longest sample and leaves it in its header.
+// The scheduler kernel picks the chunk from the longest sample and leaves it in its header; the compute kernels go
+// through short_item_head / short_rotated_head in the second case.
 constexpr int kXcdChunk = 128;
 constexpr int kXcdChunkMinLen = 1024;  // longest sample from which the chunked order is used
 __host__ __device__ __forceinline__ void xcd_item_head(unsigned bid, int n_items, int heads, int kv_heads, int chunk,
@@ -255,6 +256,47 @@ __host__ __device__ __forceinline__ void xcd_item_head(unsigned bid, int n_items
     item = (int)i;
     hp = (int)(x + 8 * kvslot + (unsigned)kv_heads * gq);
     if (C == 1) hp = (int)(((unsigned)hp + i) % (unsigned)heads);
+}
+
+// The order of a batch of short samples (header: chunk = 1).  What counts there is which L2 the tiles of one sample
+// meet in: the 2..8 tiles of a sample stand next to each other in the work list and read the same K/V (dK/dV: the same
+// Q/dO), which in the order above, rotated by the item, came from another XCD's L2 each time.
+//   Rows of whole 128-byte lines (head_dim 64, 128) and kv_heads a multiple of 8: the order above, but rotated by a
+//     hash of the sample's first row, which all tiles of a sample share, instead of by the item: short_rotated_head,
+//     once the item is loaded.
+//   Otherwise: XCD x takes kShortRun items in turn with all their heads.  At head_dim 80 and 96 a head's 160 or 192
+//     bytes of a token share lines with its neighbours', which the order above fetches into two L2s; and with
+//     another number of kv heads it gives a head no XCD of its own anyway.
+// Measured, forward / dQ / dK/dV, 83k..130k tokens, 16 heads, order above -> this one, and the choice not taken:
+//   head_dim 64, 64..384 tokens    212/331/438 -> 204/316/433 us (whole items 212/328/424)
+//   head_dim 128, 64..1000 tokens  583/844/1395 -> 528/795/1344 us (whole items 543/812/1356)
+//   head_dim 80, 64..384 tokens    323/567/648 -> 296/507/596 us (rotated by sample 310/554/631)
+//   head_dim 96, 64..1000 tokens   524/716/1234 -> 489/674/1166 us (rotated by sample 491/673/1183)
+//   12 heads of 80, 64..1000 tokens  303/449/536 -> 263/411/501 us
+//   64-token samples, head_dim 64  154/245/296 -> 148/229/280 us (whole items 163/262/314)
+// Runs of 1, 4 or 8 items instead of 2: 0..5 % slower at head_dim 80.
+constexpr unsigned kShortRun = 2;
+__host__ __device__ __forceinline__ bool short_whole_items(int head_dim, int kv_heads) {
+    return head_dim * 2 % 128 != 0 || kv_heads % 8 != 0;
+}
+__host__ __device__ __forceinline__ void short_item_head(unsigned bid, int n_items, int heads, int kv_heads, int head_dim,
+                                                         int& item, int& hp) {
+    if (!short_whole_items(head_dim, kv_heads)) return xcd_item_head(bid, n_items, heads, kv_heads, 1, item, hp);
+    const unsigned H = (unsigned)heads, full = (unsigned)n_items / (8 * kShortRun) * (8 * kShortRun);  // items in whole rounds
+    if (bid < full * H) {
+        const unsigned x = bid % 8, k = bid / 8, rem = k % (kShortRun * H);
+        item = (int)((k / (kShortRun * H) * 8 + x) * kShortRun + rem / H);
+        hp = (int)(rem % H);
+    } else {
+        item = (int)(bid / H);
+        hp = (int)(bid % H);
+    }
+}
+// sample: the packed row the item's sample starts at.
+__host__ __device__ __forceinline__ int short_rotated_head(int hp, int item, int sample, int heads, int kv_heads, int head_dim) {
+    if (short_whole_items(head_dim, kv_heads)) return hp;
+    const unsigned H = (unsigned)heads;  // (takes the rotation by the item off again)
+    return (int)(((unsigned)hp + ((unsigned)sample * 2654435761u >> 16) % H + H - (unsigned)item % H) % H);
 }
 
 // Index of this wave inside its workgroup, as a value the compiler knows to be wave-uniform.

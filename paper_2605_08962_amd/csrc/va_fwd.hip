@@ -271,9 +271,11 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         int item;
         ch = S > 1 ? (int)(wid % S) : 0;
         const unsigned bid = S > 1 ? wid / S : wid;
-        // (LEAN: always the item-major order, which is what the scheduler picks for short samples anyway; not
+        // (LEAN: always the order of short samples, which is what the scheduler picks for them anyway; not
         // reading it from the header lets the work item's own load start at once, next to the header's)
-        xcd_item_head(bid, max_items, Hq, Hkv, LEAN ? 1 : hdr[1], item, hp);
+        const bool short_order = LEAN || hdr[1] == 1;
+        if (short_order) short_item_head(bid, max_items, Hq, Hkv, D, item, hp);
+        else xcd_item_head(bid, max_items, Hq, Hkv, kXcdChunk, item, hp);
         // (integer division runs on the vector ALU; make the results scalar again, so that what is derived
         // from them stays in scalar registers)
         item = __builtin_amdgcn_readfirstlane(item); hp = __builtin_amdgcn_readfirstlane(hp);
@@ -283,6 +285,9 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         // after the check)
         it = items[item];
         if (LEAN && item >= hdr[0]) return;
+        if (short_order)
+            hp = __builtin_amdgcn_readfirstlane(
+                short_rotated_head(hp, item, __builtin_amdgcn_readfirstlane(it.y), Hq, Hkv, D));
     }
     // Head slots count the kv heads first, so that (with Hkv a multiple of the 8 XCDs) every XCD's L2
     // only ever sees its own kv heads.
