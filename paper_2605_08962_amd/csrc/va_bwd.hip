@@ -65,12 +65,12 @@ __device__ __forceinline__ bf16x8 pack_regs_lo(const f32x16& x, int st, bf16x8 h
 // `lo` is set (wave-uniform), carry P and dS as bf16 hi + lo (see the forward kernel for why).
 //   qt, dot : LDS tiles of Q and dO (64 rows);  stat: per 16 rows {16 x lse2, 16 x delta}
 //   aaddr   : per-lane offsets of the row-wise 16-byte reads, taddr: of the transposing reads
-template <int D, bool CAUSAL, bool MASKED>
+template <int D, bool CAUSAL, bool MASKED, int OB>
 __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigned char* dot,
                                           const unsigned char* stat, const int (&aaddr)[BwdCfg<D>::KS],
-                                          const int (&taddr)[BwdCfg<D>::DB][2],
+                                          const int (&taddr)[OB][2],
                                           const bf16x8 (&kf)[BwdCfg<D>::KS], const bf16x8 (&vf)[BwdCfg<D>::KS],
-                                          f32x16 (&dkacc)[BwdCfg<D>::DB], f32x16 (&dvacc)[BwdCfg<D>::DB],
+                                          f32x16 (&dkacc)[OB], f32x16 (&dvacc)[OB],
                                           float c2, int q0, int kv, int L, int hh, bool lo = MASKED) {
     using C = BwdCfg<D>;
     constexpr int ROWB = C::T::ROWB;
@@ -83,7 +83,8 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
     for (int qb = 0; qb < 2; ++qb) {
         // keep the instruction scheduler from hoisting the second half's LDS reads over the first
         // half: it would hold both halves' operands in registers and spill
-        if (qb) __builtin_amdgcn_sched_barrier(0);
+        // (a slice has the registers, and nothing else on its SIMD to hide one half's latencies behind)
+        if (qb && OB == C::DB) __builtin_amdgcn_sched_barrier(0);
         f32x16 s, dp;
         float lv[16];
 #pragma unroll
@@ -124,7 +125,7 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
             if (LO_INLINE) { pl = pack_regs_lo(s, st, pb); dsl = pack_regs_lo(dp, st, dsb); }
             const int rowoff = (32 * qb + 16 * st) * ROWB;
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db) {
+            for (int db = 0; db < OB; ++db) {
                 bf16x8 ado = cat4(lds_read_tr(dot + rowoff + taddr[db][0]), lds_read_tr(dot + rowoff + taddr[db][1]));
                 dvacc[db] = mfma32(ado, pb, dvacc[db]);
                 if (LO_INLINE) dvacc[db] = mfma32(ado, pl, dvacc[db]);
@@ -140,7 +141,7 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
                 const bf16x8 dsl = pack_regs_lo(dp, st, pack_regs(dp, st));
                 const int rowoff = (32 * qb + 16 * st) * ROWB;
 #pragma unroll
-                for (int db = 0; db < C::DB; ++db) {
+                for (int db = 0; db < OB; ++db) {
                     bf16x8 ado = cat4(lds_read_tr(dot + rowoff + taddr[db][0]), lds_read_tr(dot + rowoff + taddr[db][1]));
                     dvacc[db] = mfma32(ado, pl, dvacc[db]);
                     bf16x8 aq = cat4(lds_read_tr(qt + rowoff + taddr[db][0]), lds_read_tr(qt + rowoff + taddr[db][1]));
@@ -161,9 +162,9 @@ template <int D>
 struct DkdvOpsA {  // operands of S = Q K^T and dP = dO V^T for one 32-query half
     bf16x8 q[BwdCfg<D>::KS], d[BwdCfg<D>::KS];
 };
-template <int D>
+template <int D, int OB>
 struct DkdvOpsC {  // operands of dV^T += dO^T P and dK^T += Q^T dS for one half
-    bf16x8 o[2][BwdCfg<D>::DB], q[2][BwdCfg<D>::DB];
+    bf16x8 o[2][OB], q[2][OB];
 };
 template <int D, int HALF>
 __device__ __forceinline__ void dkdv_load_A(const unsigned char* stage, const int (&aaddr)[BwdCfg<D>::KS],
@@ -193,9 +194,9 @@ __device__ __forceinline__ void dkdv_load_lse(const unsigned char* stage, float 
         lv[4 * r4 + 0] = l4.x; lv[4 * r4 + 1] = l4.y; lv[4 * r4 + 2] = l4.z; lv[4 * r4 + 3] = l4.w;
     }
 }
-template <int D, int HALF>
-__device__ __forceinline__ void dkdv_load_C(const unsigned char* stage, const int (&taddr)[BwdCfg<D>::DB][2],
-                                            DkdvOpsC<D>& f) {
+template <int D, int HALF, int OB>
+__device__ __forceinline__ void dkdv_load_C(const unsigned char* stage, const int (&taddr)[OB][2],
+                                            DkdvOpsC<D, OB>& f) {
     using C = BwdCfg<D>;
     constexpr int ROWB = C::T::ROWB;
 #pragma unroll
@@ -203,7 +204,7 @@ __device__ __forceinline__ void dkdv_load_C(const unsigned char* stage, const in
         const unsigned char* qt = stage + (32 * HALF + 16 * st) * ROWB;
         const unsigned char* dot = qt + C::TILE;
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
+        for (int db = 0; db < OB; ++db) {
             f.o[st][db] = cat4(lds_read_tr(dot + taddr[db][0]), lds_read_tr(dot + taddr[db][1]));
             f.q[st][db] = cat4(lds_read_tr(qt + taddr[db][0]), lds_read_tr(qt + taddr[db][1]));
         }
@@ -235,13 +236,13 @@ __device__ __forceinline__ void dkdv_run_B(const f32x16& s, const f32x16& dp, co
         dsb[st] = pack_regs(ds, st);
     }
 }
-template <int D>
-__device__ __forceinline__ void dkdv_run_C(const DkdvOpsC<D>& f, const bf16x8 (&pb)[2], const bf16x8 (&dsb)[2],
-                                           f32x16 (&dkacc)[BwdCfg<D>::DB], f32x16 (&dvacc)[BwdCfg<D>::DB]) {
+template <int D, int OB>
+__device__ __forceinline__ void dkdv_run_C(const DkdvOpsC<D, OB>& f, const bf16x8 (&pb)[2], const bf16x8 (&dsb)[2],
+                                           f32x16 (&dkacc)[OB], f32x16 (&dvacc)[OB]) {
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
-        for (int db = 0; db < BwdCfg<D>::DB; ++db) {
+        for (int db = 0; db < OB; ++db) {
             dvacc[db] = mfma32(f.o[st][db], pb[st], dvacc[db]);
             dkacc[db] = mfma32(f.q[st][db], dsb[st], dkacc[db]);
         }
@@ -306,9 +307,14 @@ __device__ __forceinline__ SmallShape dkdv_small_shape(int Hq, int Hkv, const Sm
     return SmallShape{BWD_TILE_KV, BWD_STEP_Q, CAUSAL ? COST_CAUSAL_KEY : COST_FULL, Hkv, Hq / Hkv, plan};
 }
 
+// OB: 32-column blocks of dK and dV a workgroup computes.  All of them, or one (SMALL only): then C::DB workgroups share
+// a tile, each forms S and dP in full and its own columns of the results, in the same order of additions (the same
+// bits).  More work in all, for launches that leave most CUs idle while one wave walks a tile alone: it is for such
+// walks that are not cut into chunks (dkdv_sliced).  Six causal samples of 30..200 tokens, 4 query heads on one kv head of
+// 128, forward + backward: 65.0 -> 53.7 us (dK/dV, 16 steps one after the other, 43 -> 31 us).
 // SMALL: the walk of a key tile (the steps of all query heads of its group, one after the other) may be cut into
 // chunks, one workgroup each, which leave fp32 results for bwd_sum_small.
-template <int D, bool CAUSAL, bool SMALL>
+template <int D, bool CAUSAL, bool SMALL, int OB = BwdCfg<D>::DB>
 __global__ void __launch_bounds__(256, (kDkdvWgsPerCu<D>))
 dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
             const __bf16* __restrict__ dO, const float2* __restrict__ stats,
@@ -324,13 +330,17 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     constexpr int NST = D == 80 ? 3 : 4;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
 
+    constexpr unsigned SLICES = C::DB / OB;
+    static_assert(SLICES == 1 || (SMALL && OB == 1), "slices of one 32-column block, of small launches");
+    const int db0 = SLICES > 1 ? (int)(blockIdx.x % SLICES) : 0;  // first of this workgroup's 32-column blocks
     int item, c;  // work item and kv head (see xcd_item_head)
     WorkItem it;
     SmallTile tl = {};
     if constexpr (SMALL) {
-        c = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)Hkv));
+        const unsigned bid = blockIdx.x / SLICES;
+        c = __builtin_amdgcn_readfirstlane((int)(bid % (unsigned)Hkv));
         if (!small_tile(small.cu, small.num_seqs, T, dkdv_small_shape<CAUSAL>(Hq, Hkv, small.plan),
-                        __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)Hkv)), tl))
+                        __builtin_amdgcn_readfirstlane((int)(bid / (unsigned)Hkv)), tl))
             return;
     } else {
         if (hdr[1] == 1) short_item_head(blockIdx.x, max_items, Hkv, Hkv, D, item, c);
@@ -431,13 +441,13 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         dma.issue_tile(iss_do, iss_ragged, iss_lds + C::TILE, w);
     };
 
-    int aaddr[C::KS], taddr[C::DB][2];
+    int aaddr[C::KS], taddr[OB][2];
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) aaddr[ks] = LT::off(ln, 2 * ks + hh);
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db) {
-        taddr[db][0] = LT::tr_off(l, 0, db);
-        taddr[db][1] = LT::tr_off(l, 8, db);
+    for (int db = 0; db < OB; ++db) {
+        taddr[db][0] = LT::tr_off(l, 0, db0 + db);
+        taddr[db][1] = LT::tr_off(l, 8, db0 + db);
     }
 
     // prologue: NST - 1 steps in flight plus this lane's K and V fragments; all waited for once (see the
@@ -461,9 +471,9 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         for (int ks = 0; ks < C::KS; ++ks) { park_in_acc_registers(kf[ks]); park_in_acc_registers(vf[ks]); }
     }
 
-    f32x16 dkacc[C::DB], dvacc[C::DB];
+    f32x16 dkacc[OB], dvacc[OB];
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db)
+    for (int db = 0; db < OB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dkacc[db][r] = 0.f; dvacc[db][r] = 0.f; }
     const float c2 = scale * kLog2e;
@@ -488,7 +498,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         /* causal: a query step entirely above this wave's keys sees none of them; every other  \
            step here takes the masked variant (a superset of the plain one) to keep code small */ \
         if (!CAUSAL || q0 + BWD_STEP_Q - 1 >= wk_lo)                                     \
-            dkdv_step<D, CAUSAL, true>(b, b + C::TILE, b + 2 * C::TILE, aaddr, taddr, kf, vf, dkacc, dvacc, \
+            dkdv_step<D, CAUSAL, true, OB>(b, b + C::TILE, b + 2 * C::TILE, aaddr, taddr, kf, vf, dkacc, dvacc, \
                                        c2, q0, kv, L, hh, lo_steps);                     \
         VA_DKDV_SYNC()                                                                   \
         issue_all();                                                                     \
@@ -500,7 +510,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     // sits at its start: it only has to retire stage idx - 1, and having stage idx + 1
     // published early lets the last phase fetch the next step's first operands.
     DkdvOpsA<D> fa;
-    DkdvOpsC<D> fc;
+    DkdvOpsC<D, OB> fc;
     f32x16 s, dpa, dpb;  // dP accumulators of the even / odd half, preloaded with -Delta
     float lv[16];
     bf16x8 pb[2], dsb[2];
@@ -519,13 +529,13 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(0)
         VA_DKDV_ISSUE_SLOT(1)
-        dkdv_load_C<D, 0>(cur, taddr, fc);
+        dkdv_load_C<D, 0, OB>(cur, taddr, fc);
         dkdv_run_dP<D>(fa, vf, dpa);
         dkdv_run_B(s, dpa, lv, c2, pb, dsb);
-        dkdv_run_C<D>(fc, pb, dsb, dkacc, dvacc);
+        dkdv_run_C<D, OB>(fc, pb, dsb, dkacc, dvacc);
         dkdv_load_A<D, 1>(cur, aaddr, fa, dpb, hh);
-        dkdv_interleave<C::KS, 8 * C::DB / C::KS, 14>();   // dP; dV/dK operand reads; P
-        dkdv_interleave<4 * C::DB, 2, 2>();                // dV, dK; next half's S/dP operand reads; dS
+        dkdv_interleave<C::KS, 8 * OB / C::KS, 14>();   // dP; dV/dK operand reads; P
+        dkdv_interleave<4 * OB, 2, 2>();                // dV, dK; next half's S/dP operand reads; dS
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(2)
         // half 1
@@ -534,13 +544,13 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(3)
         VA_DKDV_ISSUE_SLOT(4)
-        dkdv_load_C<D, 1>(cur, taddr, fc);
+        dkdv_load_C<D, 1, OB>(cur, taddr, fc);
         dkdv_run_dP<D>(fa, vf, dpb);
         dkdv_run_B(s, dpb, lv, c2, pb, dsb);
-        dkdv_run_C<D>(fc, pb, dsb, dkacc, dvacc);
+        dkdv_run_C<D, OB>(fc, pb, dsb, dkacc, dvacc);
         dkdv_load_A<D, 0>(nxt, aaddr, fa, dpa, hh);  // next step (dropped after the last one)
-        dkdv_interleave<C::KS, 8 * C::DB / C::KS, 14>();   // dP; dV/dK operand reads; P
-        dkdv_interleave<4 * C::DB, 2, 2>();                // dV, dK; next half's S/dP operand reads; dS
+        dkdv_interleave<C::KS, 8 * OB / C::KS, 14>();   // dP; dV/dK operand reads; P
+        dkdv_interleave<4 * OB, 2, 2>();                // dV, dK; next half's S/dP operand reads; dS
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(5)
         VA_DKDV_ADVANCE()
@@ -590,10 +600,10 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         if (kvalid) {
             const size_t off = (((size_t)ch * T + sb + kv) * Hkv + c) * D;
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db)
+            for (int db = 0; db < OB; ++db)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const int d0 = 32 * db + 8 * r4 + 4 * hh;
+                    const int d0 = 32 * (db0 + db) + 8 * r4 + 4 * hh;
                     if (d0 < D) {
                         *(float4*)(small.part_dk + off + d0) = make_float4(dkacc[db][4 * r4 + 0], dkacc[db][4 * r4 + 1],
                                                                            dkacc[db][4 * r4 + 2], dkacc[db][4 * r4 + 3]);
@@ -606,10 +616,10 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         __bf16* dkp = dK + ((size_t)(sb + kv) * Hkv + c) * D;
         __bf16* dvp = dV + ((size_t)(sb + kv) * Hkv + c) * D;
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
+        for (int db = 0; db < OB; ++db)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const int d0 = 32 * db + 8 * r4 + 4 * hh;
+                const int d0 = 32 * (db0 + db) + 8 * r4 + 4 * hh;
                 if (d0 < D) {
                     bf16x4 a, b;
 #pragma unroll
@@ -625,6 +635,11 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     wg_clock.end(clock_probe);
 }
 
+// Slices (see dkdv_kernel) where every one of them still finds a CU of its own and the walks are not cut.
+template <int D>
+static bool dkdv_sliced(const BwdArgs& a) {
+    return a.plan_kv.max_chunks == 1 && a.max_items_kv * a.num_kv_heads * BwdCfg<D>::DB <= 256;
+}
 template <int D, bool CAUSAL>
 static hipError_t launch_dkdv_dc(const BwdArgs& a, hipStream_t stream) {
     dim3 grid((unsigned)(a.max_items_kv * a.num_kv_heads * a.plan_kv.max_chunks)), block(256);
@@ -633,7 +648,12 @@ static hipError_t launch_dkdv_dc(const BwdArgs& a, hipStream_t stream) {
     auto st = (const float2*)a.stats;
     auto dk = (__bf16*)a.dk; auto dv = (__bf16*)a.dv;
     const DkdvSmall sm{a.cu_seqlens, a.num_seqs, a.plan_kv, a.part_dk, a.part_dv};
-    if (a.small)
+    if (a.small && dkdv_sliced<D>(a)) {
+        grid.x *= BwdCfg<D>::DB;
+        hipLaunchKernelGGL((dkdv_kernel<D, CAUSAL, true, 1>), grid, block, 0, stream, q, k, v, dO, st, dk, dv, a.sched_hdr_kv,
+                           a.items_kv, (int)a.max_items_kv, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale, sm,
+                           a.clock_probe_dkdv);
+    } else if (a.small)
         hipLaunchKernelGGL((dkdv_kernel<D, CAUSAL, true>), grid, block, 0, stream, q, k, v, dO, st, dk, dv, a.sched_hdr_kv,
                            a.items_kv, (int)a.max_items_kv, a.total_tokens, a.num_q_heads, a.num_kv_heads, a.scale, sm,
                            a.clock_probe_dkdv);
