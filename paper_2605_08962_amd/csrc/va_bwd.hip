@@ -83,7 +83,7 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
     for (int qb = 0; qb < 2; ++qb) {
         // The sample ends in the first half: the second adds zeros (half of all samples end so).  With the same in dQ:
         // 256 samples of 64..1024 tokens, 16 heads of 80, forward + backward 1796 -> 1756 us (dK/dV 3 %), the ViT batch
-        // 11834 -> 11715 us.  (In the forward the second form of the masked tile cost 20-60 registers: not kept.)
+        // 11834 -> 11715 us.
         if (MASKED && qb && q0 + 32 >= L) break;
         // keep the instruction scheduler from hoisting the second half's LDS reads over the first
         // half: it would hold both halves' operands in registers and spill

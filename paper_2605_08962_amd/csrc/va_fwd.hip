@@ -45,7 +45,7 @@ constexpr float kRescaleLog2 = 8.0f;
 // has already run the earlier ones): the caller hangs the tile loads of the iterations ahead on
 // them, so that they trickle into the memory pipeline between the MFMAs instead of queueing up
 // behind every other wave's right after the barrier.
-template <int D, bool CAUSAL, bool BOUNDARY, int FIRST_SLOT = 0, bool LO = false, typename Issue>
+template <int D, bool CAUSAL, bool BOUNDARY, int FIRST_SLOT = 0, bool LO = false, bool SKIP = true, typename Issue>
 __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigned char* vb,
                                           const int (&kaddr)[FwdCfg<D>::KS],
                                           const int (&vaddr)[FwdCfg<D>::DB][2],
@@ -55,15 +55,26 @@ __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigne
     using C = FwdCfg<D>;
     constexpr int ROWB = C::T::ROWB;
     constexpr int NB = C::NB;
+    // SKIP: blocks of 32 keys that no row of this wave sees, past the sample's end or above the diagonal, leave out their
+    // products, which would be of zeros, each behind a wave-uniform branch (with two blocks to a tile the first is always
+    // computed: a branch around it cost the head_dim 64 kernel 7 spilled registers).  Measured: 64 ViT samples, 16 heads
+    // of 64, 2959 -> 2923 us; causal, 64..600 tokens, 16 heads of 64, lean form, 249 -> 232 us (four workgroups per CU
+    // now instead of three); no difference to the lean form at head_dim 64 without the causal mask, which goes without.
+    bool dead[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        dead[b] = BOUNDARY && SKIP && (NB == 1 || b) && (kv0 + 32 * b >= L || (CAUSAL && kv0 + 32 * b > __builtin_amdgcn_readfirstlane(qrow) + 31));
     f32x16 s[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[b][r] = 0.f;
+        if (!dead[b]) {
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 a = *(const bf16x8*)(kb + kaddr[ks] + b * 32 * ROWB);
-            s[b] = mfma32(a, qf[ks], s[b]);
+            for (int ks = 0; ks < C::KS; ++ks) {
+                bf16x8 a = *(const bf16x8*)(kb + kaddr[ks] + b * 32 * ROWB);
+                s[b] = mfma32(a, qf[ks], s[b]);
+            }
         }
         if (FIRST_SLOT <= b) issue(b);
     }
@@ -132,6 +143,26 @@ __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigne
                 plo[b][st][e] = LO ? (__bf16)(s[b][8 * st + e] - (float)pb[b][st][e]) : (__bf16)0.f;
         }
     issue(2);
+    if (BOUNDARY && SKIP) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (!dead[b]) {
+#pragma unroll
+                for (int db = 0; db < C::DB; ++db) {
+#pragma unroll
+                    for (int st = 0; st < 2; ++st) {
+                        const unsigned char* p0 = vb + (32 * b + 16 * st) * ROWB;
+                        bf16x8 a = cat4(lds_read_tr(p0 + vaddr[db][0]), lds_read_tr(p0 + vaddr[db][1]));
+                        oacc[db] = mfma32(a, pb[b][st], oacc[db]);
+                        if (LO) oacc[db] = mfma32(a, plo[b][st], oacc[db]);
+                    }
+                    if (NB > 1 && b == 0 && db == 0) issue(3);
+                }
+            }
+        }
+        if (NB == 1) issue(3);
+        return;
+    }
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) {
 #pragma unroll
@@ -210,12 +241,14 @@ __device__ __forceinline__ bool tile_step_trusting(const unsigned char* kb, cons
 
 // Workgroups per CU the kernel is compiled for (registers) and its LDS allows.  At head_dim 64 the general
 // form fits four (126 registers, 40 KB) and needs them: held to three by LDS padding it measured 12 % slower on
-// 8192-token samples, to two 18 %.  The lean form is compiled for three: under the causal mask it takes 149 registers
-// and spills at 128.
+// 8192-token samples, to two 18 %.  So does the lean form (126 registers; 128 and one spilled under the causal mask,
+// where it measured 7 % faster than three workgroups with 149).
 template <int D, bool CAUSAL>
 constexpr int kFwdWgsPerCu = D == 64 ? 4 : (D <= 80 || D == 128) ? 3 : 2;
 template <int D>
-constexpr int kFwdLeanWgsPerCu = (D <= 80 || D == 128) ? 3 : 2;
+constexpr int kFwdLeanWgsPerCu = D == 64 ? 4 : (D <= 80 || D == 128) ? 3 : 2;
+template <int D>
+constexpr int kFwdSmallWgsPerCu = (D <= 80 || D == 128) ? 3 : 2;
 
 // How a workgroup comes by its work, and what it loads.
 //   FWD_GENERAL  the tile its work-list entry names; loads past the item's last tile are issued all the same (they
@@ -251,6 +284,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     using C = FwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr bool LEAN = MODE != FWD_GENERAL;
+    constexpr bool SKIP = !(MODE == FWD_LEAN && D == 64 && !CAUSAL);  // see tile_step
 
     // S > 1: the key tiles of every query tile are split into S consecutive chunks (FWD_SMALL: into as many as its
     // plan gives), one workgroup each, which write partial results (fp32 O and LSE per
@@ -430,14 +464,14 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     if constexpr (C::BKV == 64) {
         if (few_keys && j == 0) {
             VA_FWD_ITER_BEGIN()
-            tile_step<D, CAUSAL, true, 0, true>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
+            tile_step<D, CAUSAL, true, 0, true, SKIP>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
             VA_FWD_ITER_END()
             ++j;
         }
     } else {
         for (; j < min(n_lo, je); ++j) {
             VA_FWD_ITER_BEGIN()
-            tile_step<D, CAUSAL, true, 0, true>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
+            tile_step<D, CAUSAL, true, 0, true, SKIP>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
             VA_FWD_ITER_END()
         }
     }
@@ -461,7 +495,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         // makes the compiler keep two sets of accumulator registers, and letting the idle wave skip the
         // step costs 30 to 60 registers for the branch around it (one workgroup per CU less at head_dim
         // 64): it has to wait at the barrier for the other waves anyway.
-        tile_step<D, CAUSAL, true>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
+        tile_step<D, CAUSAL, true, 0, false, SKIP>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
         VA_FWD_ITER_END()
     }
     wait_vmcnt<0>();  // the surplus loads issued near the end must land before this LDS is given away
@@ -539,7 +573,7 @@ fwd_kernel_lean(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, cons
 }
 
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, (kFwdLeanWgsPerCu<D>))
+__global__ void __launch_bounds__(256, (kFwdSmallWgsPerCu<D>))
 fwd_kernel_small(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
                  __bf16* __restrict__ O, float* __restrict__ LSE, FwdSmall small, int T, int Hq, int Hkv, float scale,
                  float* __restrict__ part_o, float* __restrict__ part_lse,
@@ -653,8 +687,8 @@ hipError_t launch_fwd_merge_small(const FwdArgs& a, hipStream_t stream) {
 
 // Workgroups of fwd_kernel_small the chip runs at a time.
 int fwd_small_slots(int head_dim) {
-    return 256 * (head_dim == 64 ? kFwdLeanWgsPerCu<64> : head_dim == 80 ? kFwdLeanWgsPerCu<80>
-                  : head_dim == 96 ? kFwdLeanWgsPerCu<96> : kFwdLeanWgsPerCu<128>);
+    return 256 * (head_dim == 64 ? kFwdSmallWgsPerCu<64> : head_dim == 80 ? kFwdSmallWgsPerCu<80>
+                  : head_dim == 96 ? kFwdSmallWgsPerCu<96> : kFwdSmallWgsPerCu<128>);
 }
 
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t stream) {
