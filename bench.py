@@ -92,13 +92,14 @@ def record_traffic(paths):
     kernels = {}
     for (counter, name), (v, ids) in val.items():
         for sym in KERNEL_SYMBOLS_ALL:
-            # demangled "va::fwd_kernel<64, false>(...)", or, where the profiler's demangler gave up, the
-            # mangled "_ZN2va11dkdv_kernelILi64ELb0EEEv..."
-            m = re.search(r"va::%s<(\d+), (true|false)>" % sym, name)
+            # demangled "va::fwd_kernel<64, false>(...)" or "va::dq_kernel_direct<64, false, false>(...)" (the third:
+            # the form for launches that do not fill the chip, which is not counted here), or, where the profiler's
+            # demangler gave up, the mangled "_ZN2va11dkdv_kernelILi64ELb0ELb0ELi2EEEv..."
+            m = re.search(r"va::%s<(\d+), (true|false)(?:, false(?:, \d+)?)?>" % sym, name)
             if m:
                 inst = f"{sym}<{m.group(1)}, {m.group(2)}>"
             else:
-                m = re.search(r"\d+%sILi(\d+)ELb([01])E" % sym, name)
+                m = re.search(r"\d+%sILi(\d+)ELb([01])E(?:Lb0E(?:Li\d+E)?)?E" % sym, name)
                 if not m:
                     continue
                 inst = f"{sym}<{m.group(1)}, {'true' if m.group(2) == '1' else 'false'}>"

@@ -115,8 +115,8 @@ struct BwdArgs {
     int total_tokens, num_q_heads, num_kv_heads, head_dim, causal;
     float scale;
     unsigned long long *clock_probe_dkdv, *clock_probe_dq;  // null, or 2 counters each (see ClockProbe)
-    // Launches that do not fill the chip (va_small.h): dQ finds its tiles from cu_seqlens and its launch builds the
-    // work lists on the side (dK/dV and the sum of the chunks go by them); a tile may be cut into chunks.
+    // Launches that do not fill the chip (va_small.h): every kernel finds its tiles from cu_seqlens, and the dQ launch
+    // builds the work lists on the side, which the workspace holds after every backward; a tile may be cut into chunks.
     bool small;
     const int32_t* cu_seqlens;
     int num_seqs;
