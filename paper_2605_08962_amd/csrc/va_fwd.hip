@@ -622,13 +622,13 @@ fwd_merge_small(const float* __restrict__ part_o, const float* __restrict__ part
         float den = 0.f, acc[8] = {};
 #pragma unroll
         for (int p = 0; p < VA_SMALL_CHUNKS; ++p)
-            if (p < nch) {  // (a chunk beyond the row under the causal mask: LSE -inf, weight 0, O finite)
+            if (p < nch && lv[p] != -INFINITY) {  // (a chunk without a key for the row, or of scores of -inf: its O is not used)
                 const float wgt = __expf(lv[p] - mx);
                 den += wgt;
                 acc[0] += wgt * v[p][0].x; acc[1] += wgt * v[p][0].y; acc[2] += wgt * v[p][0].z; acc[3] += wgt * v[p][0].w;
                 acc[4] += wgt * v[p][1].x; acc[5] += wgt * v[p][1].y; acc[6] += wgt * v[p][1].z; acc[7] += wgt * v[p][1].w;
             }
-        const float inv = 1.f / den;
+        const float inv = den > 0.f ? 1.f / den : 0.f;  // (all scores -inf: O = 0, LSE = -inf, as without the cut)
         bf16x8 out;
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = (__bf16)(acc[e] * inv);
