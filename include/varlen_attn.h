@@ -73,11 +73,12 @@ typedef struct {
     int32_t causal;        /* 0: full attention inside a sample; 1: j <= i inside a sample */
     float softmax_scale;   /* finite, >= 0 (0 is legal: uniform attention) */
     int32_t max_seqlen;    /* optional hint, 0 = unknown: the caller's promise that no sample is longer than
-                              this.  The work list is built on the device from cu_seqlens, so nothing is
-                              sized by it and a wrong value never makes a result wrong; the host uses it
-                              where it must decide before the device has seen the lengths: the automatic
-                              kv_splits choice, and the tile shape for batches of short samples only
-                              (see varlen_attn_fwd).  Must be >= 0. */
+                              this.  Tiles are found on the device from cu_seqlens, so a wrong value never
+                              makes a result wrong; the host uses it where it must decide before the device
+                              has seen the lengths: into how many chunks a small launch cuts its tiles (and
+                              so how much workspace it makes use of), forward and backward, and the tile
+                              shape for batches of short samples only (see varlen_attn_fwd and
+                              varlen_attn_bwd).  Must be >= 0. */
     int32_t kv_splits;     /* an extension; a tuning hint that never changes results beyond rounding:
                               0 = automatic, 1 = never split, 2..VA_MAX_KV_SPLITS = that many workgroups
                               share the keys of each query tile (forward only; see varlen_attn_fwd and,
@@ -85,7 +86,14 @@ typedef struct {
 } varlen_attn_params;
 enum { VA_MAX_KV_SPLITS = 8, VA_MAX_MERGE_PARTS = 64 };
 
-/* Bytes of device scratch the forward / backward call needs for these sizes (0 on bad params). */
+/*
+ * Bytes of device scratch the forward / backward call makes use of for these sizes (0 on bad params).  Launches too small
+ * to fill the GPU use far more of it than large ones, for the fp32 results of the chunks their tiles are cut into, and
+ * how much depends on all of the parameters.  Where the chunks are chosen automatically a call also runs with less: it
+ * makes as many as fit, down to none.  What every call needs is the size with kv_splits = 1, which grows with
+ * total_tokens, num_seqs and num_q_heads only: a workspace of that size for the largest batch does for every smaller one.
+ * Results then agree to rounding, not to the bit, with those of a call that had room for all its chunks.
+ */
 size_t varlen_attn_fwd_workspace_bytes(const varlen_attn_params *p);
 size_t varlen_attn_bwd_workspace_bytes(const varlen_attn_params *p);
 
@@ -100,7 +108,7 @@ size_t varlen_attn_bwd_workspace_bytes(const varlen_attn_params *p);
  * workspace, and a merge kernel combines them (same formula as varlen_attn_merge); how many is chosen from the sizes
  * (max_seqlen where given, else the average length), so that a sample's result then depends, to rounding, on what it
  * is launched with.  kv_splits = 1 cuts nothing, 2..8 forces that many chunks per tile.  The workspace size accounts
- * for it.
+ * for it; a smaller workspace gets fewer of the automatic chunks.
  * A batch of short samples only (0 < max_seqlen <= 1024, keys not split) takes a leaner form of the same
  * kernel, which issues no load past a tile list's end: there a workgroup lives for one to a few tile steps
  * and its time is a chain of memory round trips, so the two spare ones matter (measured 1.1-1.3x at 64..256
@@ -144,7 +152,8 @@ int varlen_attn_fwd_static_scratch(const varlen_attn_params *p,
  * then dK and dV per key tile.  Rows whose softmax is nearly one-hot feel the rounding of `o`
  * through Delta: dS = P (dP - Delta) is a small difference of large terms there.
  * A launch that does not fill the GPU (see varlen_attn_fwd) has its walks cut into chunks, summed in fp32 in a fixed
- * order by a third kernel, where the caller names samples longer than 1024 tokens (max_seqlen) and kv_splits = 0.
+ * order by a third kernel, where the caller names samples longer than 1024 tokens (max_seqlen) and kv_splits = 0;
+ * how often depends on the sizes and on the workspace handed over (varlen_attn_bwd_workspace_bytes).
  * Without max_seqlen, or with kv_splits = 1, a sample's gradients are the same bits whatever it is launched with.
  */
 int varlen_attn_bwd(const varlen_attn_params *p,

@@ -188,10 +188,10 @@ struct FwdLayout {
     size_t part_o_ofs, part_lse_ofs, end;
 };
 
-// A small launch takes fewer chunks rather than more room than the static scratch array has, in the entry point that
-// uses that array and, so that the two give the same bits, wherever the caller names no max_seqlen.
-FwdLayout fwd_layout(const varlen_attn_params* p, bool static_scratch = false) {
-    const size_t max_bytes = static_scratch || p->max_seqlen == 0 ? (size_t)VA_STATIC_SCRATCH_BYTES : SIZE_MAX;
+// `room`: bytes the work list and the parts may take.  Automatic chunks become fewer, down to none, until they fit; what
+// does not fit then, or is asked for by kv_splits, is the caller's error.  In a small launch without max_seqlen they never
+// take more than the static scratch array has, so that the entry point that uses it gives the same bits.
+FwdLayout fwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
     FwdLayout f;
     f.sched = va::sched_layout(p->total_tokens, p->num_seqs, va::FWD_TILE_Q);
     f.small = p->kv_splits == 0 && small_launch(p, va::FWD_TILE_Q, p->num_q_heads, va::fwd_small_slots(p->head_dim));
@@ -200,6 +200,7 @@ FwdLayout fwd_layout(const varlen_attn_params* p, bool static_scratch = false) {
         f.plan = small_plan(p, va::FWD_TILE_Q, va::fwd_tile_kv(p->head_dim), p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL,
                             p->num_q_heads, 1, fwd_cost(p->head_dim));
     f.splits = f.small ? f.plan.max_chunks : fwd_kv_splits(p);
+    if (f.small && p->max_seqlen == 0) room = std::min(room, (size_t)VA_STATIC_SCRATCH_BYTES);
     const size_t rows = (size_t)p->total_tokens * p->num_q_heads;
     f.part_o_ofs = f.sched.end_ofs;
     for (;; --f.splits) {
@@ -208,7 +209,7 @@ FwdLayout fwd_layout(const varlen_attn_params* p, bool static_scratch = false) {
             f.part_lse_ofs = f.part_o_ofs + (size_t)f.splits * rows * p->head_dim * sizeof(float);
             f.end = (f.part_lse_ofs + (size_t)f.splits * rows * sizeof(float) + 255) / 256 * 256;
         }
-        if (f.end <= max_bytes || !f.small || f.splits == 1) break;
+        if (f.end <= room || p->kv_splits != 0 || f.splits == 1) break;
     }
     if (f.splits < f.plan.max_chunks) f.plan = va::SmallPlan{f.splits, f.plan.target, 0};
     return f;
@@ -221,7 +222,8 @@ struct BwdLayout {
     size_t kv_ofs, q_ofs, stats_ofs, part_dq_ofs, part_dk_ofs, part_dv_ofs, end;
 };
 
-BwdLayout bwd_layout(const varlen_attn_params* p) {
+// `room`: bytes the workspace may take; the chunks become fewer, down to none, until they fit (see fwd_layout).
+BwdLayout bwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
     BwdLayout b;
     b.kv = va::sched_layout(p->total_tokens, p->num_seqs, va::BWD_TILE_KV);
     b.q = va::sched_layout(p->total_tokens, p->num_seqs, va::BWD_TILE_Q);
@@ -243,10 +245,14 @@ BwdLayout bwd_layout(const varlen_attn_params* p) {
         return splits > 1 ? ((size_t)splits * p->total_tokens * heads * p->head_dim * sizeof(float) + 255) / 256 * 256 : 0;
     };
     b.part_dq_ofs = b.end;
-    b.part_dk_ofs = b.part_dq_ofs + part(b.plan_q.max_chunks, p->num_q_heads);
-    b.part_dv_ofs = b.part_dk_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
-    b.end = b.part_dv_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
-    return b;
+    for (;;) {
+        b.part_dk_ofs = b.part_dq_ofs + part(b.plan_q.max_chunks, p->num_q_heads);
+        b.part_dv_ofs = b.part_dk_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
+        b.end = b.part_dv_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
+        va::SmallPlan& more = b.plan_q.max_chunks >= b.plan_kv.max_chunks ? b.plan_q : b.plan_kv;
+        if (b.end <= room || more.max_chunks == 1) return b;
+        more = va::SmallPlan{more.max_chunks - 1, more.target, 0};
+    }
 }
 
 }  // namespace
@@ -341,7 +347,8 @@ int varlen_attn_fwd(const varlen_attn_params* p, const void* q, const void* k, c
     const int rc = check_params(p);
     if (rc != VA_OK) return rc;
     if (p->total_tokens == 0 || p->num_seqs == 0) return VA_OK;
-    return fwd_impl(p, q, k, v, cu_seqlens, o, lse, fwd_layout(p), workspace, workspace_bytes, hip_stream);
+    return fwd_impl(p, q, k, v, cu_seqlens, o, lse, fwd_layout(p, workspace_bytes), workspace, workspace_bytes,
+                    hip_stream);
 }
 
 namespace {
@@ -373,7 +380,7 @@ int varlen_attn_fwd_static_scratch(const varlen_attn_params* p, const void* q, c
     int rc = check_params(p);
     if (rc != VA_OK) return rc;
     if (p->total_tokens == 0 || p->num_seqs == 0) return VA_OK;
-    const FwdLayout fl = fwd_layout(p, true);
+    const FwdLayout fl = fwd_layout(p, (size_t)VA_STATIC_SCRATCH_BYTES);
     if (fl.end > (size_t)VA_STATIC_SCRATCH_BYTES) return VA_ERR_SCRATCH_LIMIT;
     rc = check_device();
     if (rc != VA_OK) return rc;
@@ -436,7 +443,7 @@ int varlen_attn_bwd(const varlen_attn_params* p, const void* dout, const void* q
         !aligned16(dq) || !aligned16(dk) || !aligned16(dv) || !aligned16(workspace) ||
         ((uintptr_t)lse & 3u) || ((uintptr_t)cu_seqlens & 3u))
         return VA_ERR_MISALIGNED;
-    BwdLayout lay = bwd_layout(p);
+    const BwdLayout lay = bwd_layout(p, workspace_bytes);
     if (workspace_bytes < lay.end) return VA_ERR_WORKSPACE_TOO_SMALL;
     rc = check_device();
     if (rc != VA_OK) return rc;

@@ -35,3 +35,45 @@ def test_rows_whose_scores_are_all_minus_infinity(D, causal):
         ro, rlse = binding.varlen_attn_fwd(clean, k, v, _cu(T), causal, D ** -0.5, kv_splits=splits)
         assert bool((o[rows] == 0).all()) and bool((lse[:, rows] == float("-inf")).all()), f"kv_splits {splits}"
         assert torch.equal(o[others], ro[others]) and torch.equal(lse[:, others], rlse[:, others])
+
+
+def _guarded(nbytes):
+    """A workspace of nbytes between two poisoned margins, and whether they are still whole."""
+    buf = torch.full((4096 + nbytes + 4096 + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+    return buf[4096:4096 + nbytes], lambda: bool((buf[:4096] == 0xA5).all()) and bool((buf[4096 + nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("lengths,Hq,Hkv,D,causal", [([2049], 4, 1, 128, True), ([1500], 2, 2, 80, False),
+                                                     ([1300, 0, 1, 1100], 2, 1, 64, True), ([1700], 2, 2, 96, False),
+                                                     ([1300] + [200] * 70, 1, 1, 64, False)])  # (by the work list)
+def test_smaller_workspaces_get_fewer_chunks(lengths, Hq, Hkv, D, causal):
+    """A workspace that does not hold all chunks (kept from a larger batch, sized without the hint) is worked with; one
+    that only holds what an uncut call needs gives that call's bits; one below that is refused; nothing is written past it."""
+    from paper_2605_08962_amd import binding
+    T, hint, sc = sum(lengths), max(lengths), D ** -0.5
+    q, k, v = _qkv(T, Hq, Hkv, D, 3 * D)
+    do, cu = torch.randn_like(q), _cu(*lengths)
+    size = lambda f, splits: f(binding.make_params(T, len(lengths), Hq, Hkv, D, causal, sc, splits, hint))
+    near = lambda a, b: float((a.float() - b.float()).norm()) <= 5e-3 * float(b.float().norm())
+    uncut = binding.varlen_attn_fwd(q, k, v, cu, causal, sc, kv_splits=1)
+    uncut_g = binding.varlen_attn_bwd(do, q, k, v, *uncut, cu, causal, sc)
+    for what, sizes in (("fwd", binding.fwd_workspace_bytes), ("bwd", binding.bwd_workspace_bytes)):
+        full, least = size(sizes, 0), size(sizes, 1)
+        part = {"fwd": Hq * T * (4 * D + 4), "bwd": Hq * T * D * 4}[what]
+        assert full >= least + 2 * part or (what == "bwd" and len(lengths) > 64 and full == least)
+        for n in sorted({n for n in (full, full - 1, least + 3 * part, least + 2 * part, least + part, least) if least <= n}):
+            print(f"case {what} {lengths} Hq={Hq} Hkv={Hkv} D={D} causal={causal} workspace {n} of {full}", flush=True)
+            ws, intact = _guarded(n)
+            if what == "fwd":
+                got, ref = binding.varlen_attn_fwd(q, k, v, cu, causal, sc, workspace=ws, max_seqlen=hint), uncut
+            else:
+                got, ref = binding.varlen_attn_bwd(do, q, k, v, *uncut, cu, causal, sc, workspace=ws, max_seqlen=hint), uncut_g
+            assert intact() and all(near(a, b) for a, b in zip(got, ref))
+            if n == least:
+                assert all(torch.equal(a, b) for a, b in zip(got, ref))
+        with pytest.raises(binding.VarlenAttnError):
+            ws = torch.empty(least - 1, dtype=torch.uint8, device="cuda")
+            if what == "fwd":
+                binding.varlen_attn_fwd(q, k, v, cu, causal, sc, workspace=ws, max_seqlen=hint)
+            else:
+                binding.varlen_attn_bwd(do, q, k, v, *uncut, cu, causal, sc, workspace=ws, max_seqlen=hint)
