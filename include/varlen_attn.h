@@ -123,16 +123,16 @@ int varlen_attn_fwd(const varlen_attn_params *p,
 /*
  * The forward for callers that can neither allocate device memory nor hand over a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and
- * results as varlen_attn_fwd, bit for bit, minus the workspace (with one exception: where max_seqlen is given and
- * the automatic chunks of a small launch would not fit the array, it makes fewer of them): the scratch the call needs (the
+ * results, bit for bit, as varlen_attn_fwd with a workspace of VA_STATIC_SCRATCH_BYTES (so also as with one of the size
+ * varlen_attn_fwd_workspace_bytes(p) gives, where that is no larger), minus the workspace: the scratch the call needs (the
  * scheduler's work list and, when the keys of a query tile are split, the fp32 partial results) lives in
  * an array of VA_STATIC_SCRATCH_BYTES that is part of the library's device code.  Every GPU the library
  * runs on holds its own copy of it from the first call there until the process ends.  The call allocates
  * nothing and calls no allocating routine; the first call on a device looks the array's address up
  * (hipGetSymbolAddress) and keeps it.
- * Limit: a call whose varlen_attn_fwd_workspace_bytes(p) exceeds VA_STATIC_SCRATCH_BYTES returns
- * VA_ERR_SCRATCH_LIMIT with nothing launched (kv_splits = 1 shrinks the need to the work list: 16 bytes per
- * 128 tokens and 20 per sample).
+ * Limit: a call that needs more than VA_STATIC_SCRATCH_BYTES returns VA_ERR_SCRATCH_LIMIT with nothing launched.  With
+ * kv_splits = 0 and 1 the need is the work list's (16 bytes per 128 tokens and 20 per sample; automatic chunks become
+ * fewer until their results fit beside it), with kv_splits = 2..8 what varlen_attn_fwd_workspace_bytes(p) says.
  * All calls on one GPU share that GPU's array, whatever their stream or thread: calls that overlap in time
  * on one GPU race on it and must be ordered by the caller (one stream, or events).  Nothing in it has to
  * start at zero: every call rewrites what it reads.

@@ -189,8 +189,7 @@ struct FwdLayout {
 };
 
 // `room`: bytes the work list and the parts may take.  Automatic chunks become fewer, down to none, until they fit; what
-// does not fit then, or is asked for by kv_splits, is the caller's error.  In a small launch without max_seqlen they never
-// take more than the static scratch array has, so that the entry point that uses it gives the same bits.
+// does not fit then, or is asked for by kv_splits, is the caller's error.
 FwdLayout fwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
     FwdLayout f;
     f.sched = va::sched_layout(p->total_tokens, p->num_seqs, va::FWD_TILE_Q);
@@ -200,7 +199,6 @@ FwdLayout fwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
         f.plan = small_plan(p, va::FWD_TILE_Q, va::fwd_tile_kv(p->head_dim), p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL,
                             p->num_q_heads, 1, fwd_cost(p->head_dim));
     f.splits = f.small ? f.plan.max_chunks : fwd_kv_splits(p);
-    if (f.small && p->max_seqlen == 0) room = std::min(room, (size_t)VA_STATIC_SCRATCH_BYTES);
     const size_t rows = (size_t)p->total_tokens * p->num_q_heads;
     f.part_o_ofs = f.sched.end_ofs;
     for (;; --f.splits) {

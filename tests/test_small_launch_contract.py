@@ -77,3 +77,23 @@ def test_smaller_workspaces_get_fewer_chunks(lengths, Hq, Hkv, D, causal):
                 binding.varlen_attn_fwd(q, k, v, cu, causal, sc, workspace=ws, max_seqlen=hint)
             else:
                 binding.varlen_attn_bwd(do, q, k, v, *uncut, cu, causal, sc, workspace=ws, max_seqlen=hint)
+
+
+@pytest.mark.parametrize("lengths,Hq,Hkv,D", [([8191], 4, 1, 128), ([2000], 2, 2, 64), ([6000, 5, 3000], 3, 3, 96)])
+@pytest.mark.parametrize("hinted", [False, True])
+def test_static_scratch_gives_the_bits_of_a_workspace_of_its_size(lengths, Hq, Hkv, D, hinted):
+    from paper_2605_08962_amd import binding
+    T, hint, sc = sum(lengths), max(lengths) if hinted else 0, D ** -0.5
+    q, k, v = _qkv(T, Hq, Hkv, D, T)
+    cu = _cu(*lengths)
+    need = binding.fwd_workspace_bytes(binding.make_params(T, len(lengths), Hq, Hkv, D, True, sc, 0, hint))
+    print(f"case {lengths} Hq={Hq} Hkv={Hkv} D={D} hint={hint} preferred workspace {need}", flush=True)
+    n = binding.STATIC_SCRATCH_BYTES
+    ref = binding.varlen_attn_fwd(q, k, v, cu, True, sc, workspace=torch.empty(n, dtype=torch.uint8, device="cuda"),
+                                  max_seqlen=hint)
+    got = [torch.full_like(t, float("nan")) for t in ref]
+    binding.varlen_attn_fwd_static_scratch(q, k, v, cu, True, sc, *got, max_seqlen=hint)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    own = binding.varlen_attn_fwd(q, k, v, cu, True, sc, max_seqlen=hint)
+    for a, b in zip(got, own):
+        assert torch.equal(a, b) if need <= n else float((a.float() - b.float()).norm()) <= 5e-3 * float(b.float().norm())
