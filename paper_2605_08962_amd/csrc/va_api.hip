@@ -118,13 +118,20 @@ struct SmallCost {
 
 // How the walks of a small launch are cut: for the samples the caller's sizes lead to expect, the number of workgroups
 // per CU, up to twice what it holds at a time, for which the chunks come out cheapest.
+// Several samples without max_seqlen are reckoned with as one that holds all tokens, and the device cuts by the lengths it
+// finds: 8192 tokens and ten or twenty samples of 16, 2 heads of 64, forward, 107 us where the average was reckoned with,
+// 55 us so.  Four even samples of 400 pay for a merge launch that finds nothing to do, 10.6 -> 13.2 us; where the average is
+// under 256 tokens a sample worth cutting is less likely and such a call shorter yet, so there nothing is cut.
+// Samples of up to 512 tokens are not: uncut here / in 2 to 4 chunks by the work list, one of 512 tokens, 2 heads, took
+// 10.8 / 15.4 us at head_dim 64, 11.6 / 15.8 at 80, 17.0 / 17.0 at 128 (causal 18.3 / 17.8); four of 400 10.6 / 16.0.
 va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner_rows, va::CostMode mode, int heads,
                          int per_pair, const SmallCost& cost) {
-    const int len = (int)expected_len(p), R = tile_rows / partner_rows;
+    const bool unknown = p->max_seqlen == 0 && p->num_seqs > 1;
+    const int len = unknown ? p->total_tokens : (int)expected_len(p), R = tile_rows / partner_rows;
     const int nu = (len + partner_rows - 1) / partner_rows, n = (len + tile_rows - 1) / tile_rows;
     const int samples = std::max(p->total_tokens / std::max(len, 1), 1);
     va::SmallPlan best{1, 0, 0};
-    if (nu * per_pair < 8 || len <= va::kShortBatchMaxSeqlen / 2) return best;
+    if (nu * per_pair < 8 || len <= va::VA_SMALL_UNCUT_LEN || (unknown && expected_len(p) < 256)) return best;
     const int longest = nu * per_pair, least = (longest + va::VA_SMALL_CHUNKS - 1) / va::VA_SMALL_CHUNKS;
     auto workgroups = [&](int chunk) {
         int64_t k = 0;

@@ -93,6 +93,7 @@ struct FwdArgs {
 };
 constexpr int VA_SMALL_CHUNKS = 8;     // most chunks a tile of a small launch is cut into
 constexpr int VA_SMALL_MAX_SEQS = 64;  // a small launch has one lane per sample
+constexpr int VA_SMALL_UNCUT_LEN = 512;  // no tile is cut in a small launch whose samples are all no longer (small_plan)
 constexpr int kShortBatchMaxSeqlen = 1024;  // max_seqlen hint up to which a batch counts as "short samples only"
 constexpr int FWD_TILE_Q = 128;
 constexpr int FWD_TILE_KV = 64;

@@ -93,8 +93,10 @@ __device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B
                 const int sum = p.mode == COST_CAUSAL_QUERY ? (n > 0 ? off + nu : 0) : n * nu - off;
                 const int total = __builtin_amdgcn_readlane(wave_incl_scan<false>(sum), 63) * p.heads * p.per_pair;
                 const int longest = __builtin_amdgcn_readlane(wave_incl_scan<true>(nu), 63) * p.per_pair;
-                chunk = __builtin_amdgcn_readfirstlane(
-                    chunk_steps(total, here * p.heads, longest, p.plan.target, p.plan.max_chunks));
+                chunk = max(longest, 1);
+                if (longest * p.partner_rows > VA_SMALL_UNCUT_LEN * p.per_pair)
+                    chunk = __builtin_amdgcn_readfirstlane(
+                        chunk_steps(total, here * p.heads, longest, p.plan.target, p.plan.max_chunks));
             }
         }
         if (idx < here) break;

@@ -97,3 +97,19 @@ def test_static_scratch_gives_the_bits_of_a_workspace_of_its_size(lengths, Hq, H
     own = binding.varlen_attn_fwd(q, k, v, cu, True, sc, max_seqlen=hint)
     for a, b in zip(got, own):
         assert torch.equal(a, b) if need <= n else float((a.float() - b.float()).norm()) <= 5e-3 * float(b.float().norm())
+
+
+@pytest.mark.parametrize("lengths,causal", [([16, 16, 1300, 1, 0], False), ([1100, 2, 63, 64], True), ([400] * 4, False)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_uneven_batches_without_the_hint(lengths, causal, D):
+    """Several samples of unknown lengths: the device cuts by the lengths it finds, and not at all where none is long."""
+    from paper_2605_08962_amd import binding
+    T, sc = sum(lengths), D ** -0.5
+    print(f"case {lengths} D={D} causal={causal}", flush=True)
+    q, k, v = _qkv(T, 2, 1, D, T + D)
+    assert binding.fwd_workspace_bytes(binding.make_params(T, len(lengths), 2, 1, D, causal, sc)) > 2 * T * 2 * D * 4
+    got = binding.varlen_attn_fwd(q, k, v, _cu(*lengths), causal, sc)
+    ref = binding.varlen_attn_fwd(q, k, v, _cu(*lengths), causal, sc, kv_splits=1)
+    for a, b in zip(got, ref):
+        assert float((a.float() - b.float()).norm()) <= 5e-3 * float(b.float().norm())
+        assert max(lengths) > 512 or torch.equal(a, b)
