@@ -3,9 +3,9 @@
 // (4-5 us of work and the gap behind it, a third of a call on a few hundred tokens), and a tile's walk over its
 // partner tiles is cut into chunks of equal length, so that the launch has as many workgroups as the chip has room for.
 //
-// The path is taken when a batch has at most 64 samples (one lane per sample) and fewer (tile, head) pairs than
-// workgroups fit on the chip.  Beyond that the order of the list matters (heaviest tiles first) and its launch is
-// lost in the noise.
+// The path is taken when a batch has at most 64 samples (one lane per sample) and no more (tile, head) pairs than
+// workgroups of the forward, or of dQ, fit on the chip.  Beyond that the order of the list matters (heaviest tiles first)
+// and its launch is lost in the noise.  dK/dV, of which fewer fit, goes along and looks after its order itself (small_tile).
 //
 // What bounds such a launch: the walk of the longest tile, while most of the chip idles; then, once cut, the memory
 // round trips and the fragments of each chunk's start (3-9 us), its fp32 results (64 or 128 KB written and read again
@@ -54,11 +54,23 @@ __host__ __device__ inline int tiles_with_chunk(int n, int nu, int r, int mode, 
     return k < 1 ? 1 : (k < n ? k : n);
 }
 
+// Place of sample s among n in decreasing order of length, equal ones in their own order; len_of(i): length of sample i.
+template <typename LenOf>
+__host__ __device__ inline int length_rank(int n, int s, int len, LenOf len_of) {
+    int rank = 0;
+    for (int i = 0; i < n; ++i) {
+        const int other = len_of(i);
+        rank += other > len || (other == len && i < s);
+    }
+    return rank;
+}
+
 struct SmallShape {  // of a launch
     int rows, partner_rows;  // R, U: rows per tile and per partner tile
     int mode;                // CostMode
     int heads, per_pair;     // `heads` workgroups walk each tile, `per_pair` times its partner tiles each
     SmallPlan plan;
+    int room;                // workgroups the chip holds at a time, where a launch may have more; else 0
 };
 struct SmallTile {
     int begin, len;  // first packed row and length of the sample
@@ -72,14 +84,29 @@ struct SmallTile {
 // First every tile's chunk 0, then the chunks 1 of the tiles that have one, and so on: no index in between is without
 // work.  (Workgroup ids go round-robin over the XCDs and their shader engines, wherever there is room; a launch
 // with holes in it leaves some of them with two workgroups per CU, one after the other, and others with none: measured
-// twice the time.)  Inside a sample the heaviest tiles come first.
+// twice the time.)  Inside a sample the heaviest tiles come first, and the longest sample's do in a launch that has more
+// workgroups than the chip holds at a time (dK/dV, one workgroup per CU at head_dim 96 and 128, can): a long sample's
+// tiles would start in the second round.  dK/dV, 4 heads of 128, 19 samples of 300 tokens and one of 2000 behind them,
+// 74 us in the batch's order, 61 so; 8 heads, 30 of 100 and one of 900, 48 -> 38 us; 12 of 400 unchanged.  Below that it
+// was none (dQ and dK/dV of 41 samples, 8 heads of 64: 26.1 / 26.8 us, longest first 26.9 / 30.7).
 // Must be reached by all 64 lanes; every result is wave-uniform.
 __device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B, int T, const SmallShape& p, int idx,
                                            SmallTile& out) {
     const int lane = threadIdx.x & 63;
     int begin = 0, end = 0;
     if (lane < B) sched_sample_rows(cu[lane], cu[lane + 1], T, begin, end);
-    const int len = end - begin, R = p.rows, r = p.rows / p.partner_rows;
+    int len = end - begin;
+    const int R = p.rows, r = p.rows / p.partner_rows;
+    if (p.room > 0 && B > 1 && (T / R + B) * p.heads > p.room) {
+        const int tiles = __builtin_amdgcn_readlane(wave_incl_scan<false>((len + R - 1) / R), 63);
+        const int next = __builtin_amdgcn_update_dpp(0, len, 0x130, 0xf, 0xf, false);  // wave_shl:1
+        if (tiles * p.heads > p.room && __builtin_amdgcn_ballot_w64(len < next)) {
+            const int place = length_rank(B, lane, len, [&](int i) { return __builtin_amdgcn_readlane(len, i); }) * 4;
+            begin = __builtin_amdgcn_ds_permute(place, begin);
+            len = __builtin_amdgcn_ds_permute(place, len);
+            if (lane >= B) begin = len = 0;
+        }
+    }
     const int n = (len + R - 1) / R, nu = (len + p.partner_rows - 1) / p.partner_rows;
     int chunk = 1 << 30, count = n, incl = 0, ch = 0;
     for (;; ++ch) {  // count: this lane's tiles that have a chunk ch

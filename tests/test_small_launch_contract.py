@@ -113,3 +113,32 @@ def test_uneven_batches_without_the_hint(lengths, causal, D):
     for a, b in zip(got, ref):
         assert float((a.float() - b.float()).norm()) <= 5e-3 * float(b.float().norm())
         assert max(lengths) > 512 or torch.equal(a, b)
+
+
+@pytest.mark.parametrize("lengths,Hq,Hkv", [([100] * 30 + [900], 8, 8), ([300] * 9 + [0, 1, 700, 129], 8, 4),
+                                            ([5, 64] * 31 + [0, 400], 4, 4)])
+@pytest.mark.parametrize("D,causal", [(64, True), (80, False), (96, True), (128, False)])
+def test_order_of_the_samples_does_not_show(lengths, Hq, Hkv, D, causal):
+    """dK/dV may have more workgroups than the chip holds and takes the longest samples first then (the first batch at
+    head_dim 96 and 128).  The batch turned round gives the same bits, and so does each sample by itself."""
+    from paper_2605_08962_amd import binding
+    T, sc = sum(lengths), D ** -0.5
+    assert len(lengths) <= 64 and 256 < (T // 128 + len(lengths)) * Hq
+    print(f"case B={len(lengths)} T={T} Hq={Hq} Hkv={Hkv} D={D} causal={causal}", flush=True)
+    x = _qkv(T, Hq, Hkv, D, T + D)
+    x.append(torch.randn_like(x[0]))
+
+    def call(q, k, v, do, lens):
+        o, lse = binding.varlen_attn_fwd(q, k, v, _cu(*lens), causal, sc, kv_splits=0, max_seqlen=max(max(lens), 1))
+        return (o, lse.t()) + binding.varlen_attn_bwd(do, q, k, v, o, lse, _cu(*lens), causal, sc)
+
+    got = [t.split(lengths) for t in call(*x, lengths)]
+    turned = [t.flip(0) if t.dim() == 1 else torch.cat(t.split(lengths)[::-1]) for t in x]
+    back = [t.split(lengths[::-1])[::-1] for t in call(*turned, lengths[::-1])]
+    for s in (lengths.index(max(lengths)), 0, len(lengths) - 1):
+        alone = call(*[t.split(lengths)[s].contiguous() for t in x], [lengths[s]]) if lengths[s] else None
+        for i in range(5):
+            # (the forward's keys may be cut by what else is in the launch: only the gradients and short samples' outputs)
+            assert torch.equal(got[i][s], back[i][s]), f"sample {s}, output {i}: order"
+            if alone and max(lengths) <= 512:
+                assert torch.equal(got[i][s], alone[i]), f"sample {s}, output {i}: alone"
