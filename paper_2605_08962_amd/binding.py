@@ -170,14 +170,17 @@ def varlen_attn_fwd_static_scratch(q, k, v, cu_seqlens, causal, softmax_scale, o
 
 
 def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, dq=None, dk=None,
-                    dv=None, workspace=None, stream=None, max_seqlen=0):
-    """dQ, dK, dV (bf16) from dO and the forward's saved O and LSE; asynchronous on the stream."""
+                    dv=None, workspace=None, stream=None, max_seqlen=0, kv_splits=0):
+    """dQ, dK, dV (bf16) from dO and the forward's saved O and LSE; asynchronous on the stream.
+    max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint; above 1024 a launch too small
+    to fill the GPU may cut its tiles into chunks, so that a sample's gradients depend, to rounding, on the launch).
+    kv_splits: 1 never does, 0 automatic."""
     lib = load()
     for t, n in ((dout, "dout"), (q, "q"), (k, "k"), (v, "v"), (out, "out")):
         _require(t, torch.bfloat16, n)
     _require(lse, torch.float32, "lse")
     _require(cu_seqlens, torch.int32, "cu_seqlens")
-    p = _params_of(q, k, cu_seqlens, causal, softmax_scale, 0, max_seqlen)
+    p = _params_of(q, k, cu_seqlens, causal, softmax_scale, kv_splits, max_seqlen)
     if dout.shape != q.shape or out.shape != q.shape or k.shape != v.shape:
         raise ValueError("dout and out must match q; k must match v")
     dq = torch.empty_like(q) if dq is None else dq

@@ -142,3 +142,32 @@ def test_order_of_the_samples_does_not_show(lengths, Hq, Hkv, D, causal):
             assert torch.equal(got[i][s], back[i][s]), f"sample {s}, output {i}: order"
             if alone and max(lengths) <= 512:
                 assert torch.equal(got[i][s], alone[i]), f"sample {s}, output {i}: alone"
+
+
+@pytest.mark.parametrize("lengths,Hq,Hkv,D,causal", [([2049], 4, 2, 128, True), ([1300, 3, 1700], 2, 2, 64, False),
+                                                     ([1100, 700], 2, 1, 80, True), ([1500], 3, 3, 96, False)])
+def test_hints_above_1024_right_or_wrong(lengths, Hq, Hkv, D, causal):
+    """With kv_splits = 1 the gradients are the same bits whatever the hint; cut by a hint that is exact, too large or too
+    small they agree with the oracle like the uncut ones, and the forward's outputs do."""
+    import oracle
+    from paper_2605_08962_amd import binding, workloads as W
+    from tests._util import LSE_ABS, assert_close, assert_gradients_close, to_f64, upload
+    w = W.make_custom(lengths, Hq, Hkv, D, causal, seed=5200 + D, with_dout=True)
+    d, T = upload(w), sum(lengths)
+    x = (d["q"], d["k"], d["v"])
+    plain = binding.varlen_attn_fwd(*x, d["cu"], causal, w.scale, kv_splits=1)
+    ref = binding.varlen_attn_bwd(d["dout"], *x, *plain, d["cu"], causal, w.scale)
+    ro, rlse = oracle.fwd(w.f32("q"), w.f32("k"), w.f32("v"), w.cu_seqlens, causal, w.scale)
+    for hint in (max(lengths), 1025, 1 << 20, T):
+        print(f"case {lengths} Hq={Hq} Hkv={Hkv} D={D} causal={causal} hint={hint}", flush=True)
+        got = binding.varlen_attn_bwd(d["dout"], *x, *plain, d["cu"], causal, w.scale, max_seqlen=hint, kv_splits=1)
+        assert all(torch.equal(a, b) for a, b in zip(got, ref))
+        p = binding.make_params(T, len(lengths), Hq, Hkv, D, causal, w.scale, 0, hint)
+        p1 = binding.make_params(T, len(lengths), Hq, Hkv, D, causal, w.scale, 1, hint)
+        assert binding.bwd_workspace_bytes(p) > binding.bwd_workspace_bytes(p1)        # the automatic choice cuts
+        o, lse = binding.varlen_attn_fwd(*x, d["cu"], causal, w.scale, max_seqlen=hint)
+        assert_close("O", to_f64(o), ro, allow_output_rounding=True)
+        assert float(abs(to_f64(lse) - rlse).max()) <= LSE_ABS
+        got = binding.varlen_attn_bwd(d["dout"], *x, *plain, d["cu"], causal, w.scale, max_seqlen=hint)
+        assert_gradients_close(f"hint {hint}", tuple(to_f64(t) for t in got), w.f32("q"), w.f32("k"), w.f32("v"),
+                               w.f32("dout"), w.cu_seqlens, causal, w.scale, to_f64(plain[0]), allow_output_rounding=True)
