@@ -256,12 +256,13 @@ int varlen_attn_balance_partition(const int32_t *lengths, int32_t num_seqs, int3
  * allocate, and read or re-enable now and then so the sample list does not grow without bound.
  */
 enum {
-    VA_KERNEL_SCHED = 0, /* tile scheduler (1 launch per forward, 1 per backward: both of its lists) */
+    VA_KERNEL_SCHED = 0, /* tile scheduler (1 launch per forward, 1 per backward: both of its lists; none in launches
+                            too small to fill the GPU) */
     VA_KERNEL_FWD = 1,   /* forward attention */
     VA_KERNEL_DKDV = 2,  /* backward: dK, dV */
     VA_KERNEL_DQ = 3,    /* backward: dQ (also forms Delta = rowsum(dO * O) and writes the per-row statistics
                             dK/dV reads; launched first) */
-    VA_KERNEL_MERGE = 4  /* merge of partial results (varlen_attn_merge, split forward) */
+    VA_KERNEL_MERGE = 4  /* merge of partial results (varlen_attn_merge, split forward) and sums of a cut backward */
 };
 int varlen_attn_profile_enable(int on);
 int varlen_attn_profile_read(int kernel, double *total_ms, int64_t *launches);

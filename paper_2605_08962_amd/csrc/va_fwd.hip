@@ -58,7 +58,7 @@ __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigne
     // SKIP: blocks of 32 keys that no row of this wave sees, past the sample's end or above the diagonal, leave out their
     // products, which would be of zeros, each behind a wave-uniform branch (with two blocks to a tile the first is always
     // computed: a branch around it cost the head_dim 64 kernel 7 spilled registers).  Measured: 64 ViT samples, 16 heads
-    // of 64, 2959 -> 2923 us; causal, 64..600 tokens, 16 heads of 64, lean form, 249 -> 232 us (four workgroups per CU
+    // of 64, 2878 -> 2844 us (four runs of each in turn, which differ by 4); causal, 64..600 tokens, 16 heads of 64, lean form, 249 -> 232 us (four workgroups per CU
     // now instead of three); no difference to the lean form at head_dim 64 without the causal mask, which goes without.
     bool dead[NB];
 #pragma unroll
@@ -490,11 +490,11 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     }
     for (; j < je; ++j) {  // the sample's ragged last tile and the causal diagonal
         VA_FWD_ITER_BEGIN()
-        // Every wave takes the masked variant here, also one whose rows see the whole tile or none of it
-        // (causal: rows above the key tile; such a wave adds exact zeros).  A second variant in this loop
-        // makes the compiler keep two sets of accumulator registers, and letting the idle wave skip the
-        // step costs 30 to 60 registers for the branch around it (one workgroup per CU less at head_dim
-        // 64): it has to wait at the barrier for the other waves anyway.
+        // Every wave takes the masked variant here, also one whose rows see the whole tile: a second variant in this
+        // loop makes the compiler keep two sets of accumulator registers.  Products of 32-key blocks that none of the
+        // wave's rows sees are left out inside the step (SKIP, where the branches fit the registers); a branch around
+        // the whole step cost 30 to 60 registers (one workgroup per CU less at head_dim 64), and such a wave has to
+        // wait at the barrier for the others anyway.
         tile_step<D, CAUSAL, true, 0, false, SKIP>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
         VA_FWD_ITER_END()
     }

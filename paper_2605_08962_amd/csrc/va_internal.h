@@ -117,7 +117,7 @@ struct BwdArgs {
     float scale;
     unsigned long long *clock_probe_dkdv, *clock_probe_dq;  // null, or 2 counters each (see ClockProbe)
     // Launches that do not fill the chip (va_small.h): every kernel finds its tiles from cu_seqlens, and the dQ launch
-    // builds the work lists on the side, which the workspace holds after every backward; a tile may be cut into chunks.
+    // builds the work lists on the side (see DqSmall); a tile may be cut into chunks.
     bool small;
     const int32_t* cu_seqlens;
     int num_seqs;

@@ -38,6 +38,11 @@ struct SchedJob {  // one work list
     int32_t *hdr, *tile_off;
     WorkItem* items;
 };
+inline SchedJob sched_job(int tile_rows, int partner_rows, CostMode mode, void* ws, const SchedLayout& lay) {
+    char* base = (char*)ws;
+    return SchedJob{tile_rows, partner_rows, (int)mode, (int)lay.max_items, (int32_t*)base,
+                    (int32_t*)(base + lay.tile_off_ofs), (WorkItem*)(base + lay.items_ofs)};
+}
 
 // LDS of a builder.  CACHE: samples whose clamped bounds and tile offsets are kept here (3 x 4 bytes each).  A batch
 // with up to three times as many keeps the tile offsets here, which is what the per-tile searches walk, and reads

@@ -39,15 +39,9 @@ sched_kernel(const int32_t* __restrict__ cu, int B, int T, SchedJob job0, SchedJ
     build_work_list(cu, B, T, blockIdx.x == 0 ? job0 : job1, lds);
 }
 
-static SchedJob make_job(int tile_rows, int partner_rows, CostMode mode, void* ws, const SchedLayout& lay) {
-    char* base = (char*)ws;
-    return SchedJob{tile_rows, partner_rows, (int)mode, (int)lay.max_items, (int32_t*)base,
-                    (int32_t*)(base + lay.tile_off_ofs), (WorkItem*)(base + lay.items_ofs)};
-}
-
 hipError_t launch_scheduler(const int32_t* cu_seqlens, int num_seqs, int total_tokens, int tile_rows,
                             int partner_rows, CostMode mode, void* ws, const SchedLayout& lay, hipStream_t stream) {
-    const SchedJob job = make_job(tile_rows, partner_rows, mode, ws, lay);
+    const SchedJob job = sched_job(tile_rows, partner_rows, mode, ws, lay);
     hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(SCHED_THREADS), 0, stream, cu_seqlens, num_seqs, total_tokens,
                        job, job);
     return hipGetLastError();
@@ -58,8 +52,8 @@ hipError_t launch_scheduler_pair(const int32_t* cu_seqlens, int num_seqs, int to
                                  int tile_rows_b, int partner_rows_b, CostMode mode_b, void* ws_b,
                                  const SchedLayout& lay_b, hipStream_t stream) {
     hipLaunchKernelGGL(sched_kernel, dim3(2), dim3(SCHED_THREADS), 0, stream, cu_seqlens, num_seqs, total_tokens,
-                       make_job(tile_rows_a, partner_rows_a, mode_a, ws_a, lay_a),
-                       make_job(tile_rows_b, partner_rows_b, mode_b, ws_b, lay_b));
+                       sched_job(tile_rows_a, partner_rows_a, mode_a, ws_a, lay_a),
+                       sched_job(tile_rows_b, partner_rows_b, mode_b, ws_b, lay_b));
     return hipGetLastError();
 }
 

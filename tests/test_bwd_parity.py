@@ -95,9 +95,8 @@ def test_packed_equals_alone():
 @pytest.mark.parametrize("D", [64, 80, 96, 128])
 @pytest.mark.parametrize("causal", [False, True])
 def test_max_seqlen_hint_changes_nothing(D, causal):
-    """max_seqlen is a hint that nothing is sized by: the gradients are bit-identical to those of the call
-    without it, whether the hint is right, generous, or wrong (a sample longer than promised); and they match
-    the oracle."""
+    """A hint of up to 1024 tokens changes nothing: the gradients are bit-identical to those of the call without
+    it, whether the hint is right, generous, or wrong (a sample longer than promised); and they match the oracle."""
     from paper_2605_08962_amd import binding
     lengths = [64, 1, 300, 0, 129, 128, 63, 65, 700, 2, 256, 1000, 127, 191, 192, 193]
     w = W.make_custom(lengths, 4, 2, D, causal, seed=650 + D + causal, with_dout=True)
