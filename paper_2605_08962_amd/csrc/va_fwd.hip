@@ -348,7 +348,9 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     const int n_lo = few_keys ? 64 / C::BKV : 0;
     const int nch = MODE == FWD_SMALL ? tl.nch : S;  // chunks of this tile
     const bool split = nch > 1;
-    const int jb = split ? ntiles * ch / nch : 0, je = split ? ntiles * (ch + 1) / nch : ntiles;  // this chunk's tiles
+    // this chunk's tiles (a small launch's are its tile's steps)
+    const int jb = MODE == FWD_SMALL ? tl.first_step() : split ? ntiles * ch / nch : 0,
+              je = MODE == FWD_SMALL ? tl.end_step() : split ? ntiles * (ch + 1) / nch : ntiles;
     if (MODE != FWD_SMALL && jb >= je) {  // fewer tiles than chunks: an empty part (its O is never read)
         if (qvalid && hh == 0) part_lse[((size_t)ch * Hq + h) * T + sb + qrow] = -INFINITY;
         return;

@@ -1,6 +1,9 @@
 """What launches that do not fill the chip are planned to take, as far as it shows in the workspace sizes, and in which order (CPU)."""
 import os
+import re
+import struct
 import subprocess
+import tempfile
 
 import pytest
 
@@ -34,3 +37,30 @@ def test_samples_are_taken_longest_first(tmp_path):
                    capture_output=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0 and "length order ok" in r.stdout, r.stdout
+
+
+def _kernel_scratch_bytes():
+    """{mangled kernel name: bytes of scratch memory per lane} from the metadata of the built library's device code."""
+    lib = open(os.path.join(ROOT, "paper_2605_08962_amd", "libvarlen_attn.so"), "rb").read()
+    magic, out, at = b"__CLANG_OFFLOAD_BUNDLE__", {}, 0
+    while (at := lib.find(magic, at)) >= 0:
+        n, pos = struct.unpack_from("<Q", lib, at + 24)[0], at + 32
+        for _ in range(n):
+            ofs, size, idlen = struct.unpack_from("<QQQ", lib, pos)
+            if b"gfx950" in lib[pos + 24:pos + 24 + idlen]:
+                with tempfile.NamedTemporaryFile(suffix=".elf") as f:
+                    f.write(lib[at + ofs:at + ofs + size])
+                    f.flush()
+                    notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], check=True,
+                                           capture_output=True, text=True).stdout
+                for name, rest in re.findall(r"\.name:\s+(_ZN2va\w+)\n((?:.*\n)*?.*\.private_segment_fixed_size:\s+\d+)", notes):
+                    out[name] = int(rest.rsplit(":", 1)[1])
+            pos += 24 + idlen
+        at += len(magic)
+    return out
+
+
+def test_dq_of_small_launches_keeps_everything_in_registers():
+    """Scratch loads in the loop wait for every tile load in flight.  The kernels' last template argument: small launches."""
+    scratch = {n: b for n, b in _kernel_scratch_bytes().items() if re.search(r"dq_kernel(_direct)?ILi\d+ELb[01]ELb1E", n)}
+    assert len(scratch) == 8 and not any(scratch.values()), scratch
