@@ -343,7 +343,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     if constexpr (SMALL) {
         const unsigned bid = blockIdx.x / SLICES;
         c = __builtin_amdgcn_readfirstlane((int)(bid % (unsigned)Hkv));
-        if (!small_tile(small.cu, small.num_seqs, T, dkdv_small_shape<CAUSAL>(Hq, Hkv, small.plan, 256 * kDkdvWgsPerCu<D>),
+        if (!small_tile(small.cu, small.num_seqs, T, dkdv_small_shape<CAUSAL>(Hq, Hkv, small.plan, CAUSAL ? 256 : 256 * kDkdvWgsPerCu<D>),
                         __builtin_amdgcn_readfirstlane((int)(bid / (unsigned)Hkv)), tl))
             return;
     } else {
@@ -792,7 +792,7 @@ template <int D>
 constexpr int kDqWgsPerCu = D == 64 ? 3 : 2;
 template <bool CAUSAL>
 __device__ __forceinline__ SmallShape dq_small_shape(int Hq, const SmallPlan& plan) {
-    return SmallShape{BWD_TILE_Q, BWD_STEP_KV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, Hq, 1, plan, 0};
+    return SmallShape{BWD_TILE_Q, BWD_STEP_KV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, Hq, 1, plan, CAUSAL ? 256 : 0};
 }
 // What a dQ workgroup works on: false if there is nothing left for it to do.
 struct DqWork {

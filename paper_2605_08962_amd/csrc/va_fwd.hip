@@ -268,7 +268,7 @@ struct FwdSmall {  // FWD_SMALL only
 };
 template <int D, bool CAUSAL>
 __device__ __forceinline__ SmallShape fwd_small_shape(const FwdSmall& sm, int heads) {
-    return SmallShape{FwdCfg<D>::BQ, FwdCfg<D>::BKV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, heads, 1, sm.plan, 0};
+    return SmallShape{FwdCfg<D>::BQ, FwdCfg<D>::BKV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, heads, 1, sm.plan, CAUSAL && D == 128 ? 256 : 0};
 }
 
 // One work item: the query tile `wid` names (see xcd_item_head), all its key tiles.  `lds` is the workgroup's

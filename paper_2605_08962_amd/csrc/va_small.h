@@ -65,12 +65,24 @@ __host__ __device__ inline int length_rank(int n, int s, int len, LenOf len_of) 
     return rank;
 }
 
+// Under the causal masks the v-th tile from a sample's light end costs the same in every sample.  from(v): tiles of the batch
+// that cost at least that (never more for a larger v, none above `most`).  The cost of the idx-th tile by falling cost.
+template <typename From>
+__host__ __device__ inline int cost_level(int idx, int most, From from) {
+    int v = 1, hi = most;
+    while (v < hi) {
+        const int mid = (v + hi + 1) >> 1;
+        if (from(mid) > idx) v = mid; else hi = mid - 1;
+    }
+    return v;
+}
+
 struct SmallShape {  // of a launch
     int rows, partner_rows;  // R, U: rows per tile and per partner tile
     int mode;                // CostMode
     int heads, per_pair;     // `heads` workgroups walk each tile, `per_pair` times its partner tiles each
     SmallPlan plan;
-    int room;                // workgroups the chip holds at a time, where a launch may have more; else 0
+    int room;                // workgroups beyond which the order of the samples counts (see small_tile), 0: it does not
 };
 struct SmallTile {
     int begin, len;  // first packed row and length of the sample
@@ -91,11 +103,15 @@ struct SmallTile {
 // First every tile's chunk 0, then the chunks 1 of the tiles that have one, and so on: no index in between is without
 // work.  (Workgroup ids go round-robin over the XCDs and their shader engines, wherever there is room; a launch
 // with holes in it leaves some of them with two workgroups per CU, one after the other, and others with none: measured
-// twice the time.)  Inside a sample the heaviest tiles come first, and the longest sample's do in a launch that has more
-// workgroups than the chip holds at a time (dK/dV, one workgroup per CU at head_dim 96 and 128, can): a long sample's
-// tiles would start in the second round.  dK/dV, 4 heads of 128, 19 samples of 300 tokens and one of 2000 behind them,
-// 74 us in the batch's order, 61 so; 8 heads, 30 of 100 and one of 900, 48 -> 38 us; 12 of 400 unchanged.  Below that it
-// was none (dQ and dK/dV of 41 samples, 8 heads of 64: 26.1 / 26.8 us, longest first 26.9 / 30.7).
+// twice the time.)  Inside a sample the heaviest tiles come first.  Across samples the order counts where `room`
+// workgroups are exceeded (SmallShape), since the last ones share a CU or wait for one:
+//   causal, from one workgroup per CU on: tiles by falling cost.  30 samples of 1318 tokens, one head of 128, dQ 49 -> 41 us,
+//     dK/dV 72 -> 52, forward 42 -> 39; 9 of 2229, 2 heads, dQ 75 -> 58, dK/dV 91 -> 72.  The forward at head_dim 64, 80 and
+//     96 goes without: the search cost it 2-6 % in the launches that have no use for it (at 128 nothing).
+//   without the mask, dK/dV beyond what the chip holds at a time (one workgroup per CU at head_dim 96 and 128): the longest
+//     sample first.  4 heads of 128, 19 samples of 300 tokens and one of 2000 behind them, 74 -> 61 us; 8 heads, 30 of 100
+//     and one of 900, 48 -> 38; 12 of 400 unchanged.  Below that it was no gain (dQ and dK/dV of 41 samples, 8 heads of 64:
+//     26.1 / 26.8 us, longest first 26.9 / 30.7).
 // Must be reached by all 64 lanes; every result is wave-uniform.
 __device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B, int T, const SmallShape& p, int idx,
                                            SmallTile& out) {
@@ -104,10 +120,12 @@ __device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B
     if (lane < B) sched_sample_rows(cu[lane], cu[lane + 1], T, begin, end);
     int len = end - begin;
     const int R = p.rows, r = p.rows / p.partner_rows;
+    bool by_cost = false;
     if (p.room > 0 && B > 1 && (T / R + B) * p.heads > p.room) {
         const int tiles = __builtin_amdgcn_readlane(wave_incl_scan<false>((len + R - 1) / R), 63);
+        by_cost = p.mode != COST_FULL && tiles * p.heads > p.room;
         const int next = __builtin_amdgcn_update_dpp(0, len, 0x130, 0xf, 0xf, false);  // wave_shl:1
-        if (tiles * p.heads > p.room && __builtin_amdgcn_ballot_w64(len < next)) {
+        if (!by_cost && tiles * p.heads > p.room && __builtin_amdgcn_ballot_w64(len < next)) {
             const int place = length_rank(B, lane, len, [&](int i) { return __builtin_amdgcn_readlane(len, i); }) * 4;
             begin = __builtin_amdgcn_ds_permute(place, begin);
             len = __builtin_amdgcn_ds_permute(place, len);
@@ -138,8 +156,20 @@ __device__ __forceinline__ bool small_tile(const int32_t* __restrict__ cu, int B
         idx -= here;
         count = tiles_with_chunk(n, nu, r, p.mode, (ch + 1) * chunk / p.per_pair);
     }
-    const int s = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= idx));  // samples before the one that holds idx
-    const int t = idx - (__builtin_amdgcn_readlane(incl, s) - __builtin_amdgcn_readlane(count, s));
+    int s, t;
+    if (by_cost && ch == 0) {
+        auto from = [&](int v) { return __builtin_amdgcn_readlane(wave_incl_scan<false>(max(n - v + 1, 0)), 63); };
+        const int v = cost_level(idx, __builtin_amdgcn_readlane(wave_incl_scan<true>(n), 63), from);
+        const int place = idx - from(v + 1);  // among the tiles of that cost (all lanes at work here: a lane operation)
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(n >= v);
+        const int before = __builtin_popcountll(has & ((1ull << lane) - 1));
+        const int hit = (n >= v ? 1 : 0) & (before == place ? 1 : 0);
+        s = __builtin_ctzll(__builtin_amdgcn_ballot_w64(hit != 0));
+        t = __builtin_amdgcn_readlane(n, s) - v;
+    } else {
+        s = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= idx));  // samples before the one that holds idx
+        t = idx - (__builtin_amdgcn_readlane(incl, s) - __builtin_amdgcn_readlane(count, s));
+    }
     const int ns = __builtin_amdgcn_readlane(n, s), us = __builtin_amdgcn_readlane(nu, s);
     out.begin = __builtin_amdgcn_readlane(begin, s);
     out.len = __builtin_amdgcn_readlane(len, s);
