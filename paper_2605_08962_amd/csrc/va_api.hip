@@ -113,11 +113,15 @@ struct SmallCost {
     float share;     // with w workgroups on a CU a step takes 1 + share * (w - 1)
     float fixed;     // prologue and epilogue
     float parts;     // fp32 results of 256 chunks, written and read again
+    float combine;   // the launch that combines them (the backward's two plans share one)
     int others;      // workgroups of the launch that do something else
 };
 
 // How the walks of a small launch are cut: for the samples the caller's sizes lead to expect, the number of workgroups
-// per CU, up to twice what it holds at a time, for which the chunks come out cheapest.
+// per CU, up to twice what it holds at a time, for which the chunks come out cheapest.  With several samples it is how
+// many workgroups that is beyond one per tile that goes to the device, which finds the chunk that gives as many: what is
+// expected leaves out the short samples beside the long ones (eight of up to 150 tokens and one of 1877, 8 heads of 80,
+// causal, with a hint: forward 36 us where the number was one for all workgroups, 27 so).
 // Several samples without max_seqlen are reckoned with as one that holds all tokens, and the device cuts by the lengths it
 // finds: 8192 tokens and ten or twenty samples of 16, 2 heads of 64, forward, 107 us where the average was reckoned with,
 // 55 us so.  Four even samples of 400 pay for a merge launch that finds nothing to do, 10.6 -> 13.2 us; where the average is
@@ -139,13 +143,16 @@ va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner
             k += va::tiles_with_chunk(n, nu, R, mode, ch * chunk / per_pair);
         return k * samples * heads;
     };
-    // w workgroups per CU: as many as it holds side by side, then one round after the other
-    auto time = [&](int w, int chunk) {
-        const int beside = std::min(w, cost.wgs_per_cu);
-        return (1.f + cost.share * (beside - 1)) * (chunk + cost.fixed) * w / beside;
+    // w workgroups per CU: as many as it holds side by side, then one round after the other.
+    auto time = [&](float w, int chunk) {
+        const float beside = std::min(w, (float)cost.wgs_per_cu);
+        return (1.f + cost.share * (beside - 1.f)) * (chunk + cost.fixed) * w / beside;
     };
-    float least_time = time((int)((workgroups(longest) + 255) / 256), longest);
-    for (int w = 1; w <= 2 * cost.wgs_per_cu; ++w) {
+    // Uncut: walks of one length take as long as the CUs with one more of them; under a causal mask the light tiles, which
+    // come last, fill up.
+    const float whole = workgroups(longest) / 256.f;
+    float least_time = time(std::max(mode == va::COST_FULL ? std::ceil(whole) : whole, 1.f), longest);
+    for (int w = 1; w <= (unknown ? 1 : 2) * cost.wgs_per_cu; ++w) {
         const int target = 256 * w - cost.others;
         int lo = least, hi = longest;  // smallest chunk that gives at most that many workgroups
         if (workgroups(hi) > target) continue;
@@ -154,10 +161,10 @@ va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner
             if (workgroups(mid) <= target) hi = mid; else lo = mid + 1;
         }
         if (lo == longest) continue;
-        const float t = time(w, lo) + cost.parts * w;
+        const float t = time((float)w, lo) + cost.parts * w + cost.combine;
         if (t < least_time) {
             least_time = t;
-            best.target = target;
+            best.extra = target - (int)workgroups(longest);
             best.chunk = p->num_seqs == 1 ? lo : 0;
             const int k = va::chunk_count(longest, lo, va::VA_SMALL_CHUNKS);
             best.max_chunks = p->num_seqs == 1 ? k : std::min(k + 1, (int)va::VA_SMALL_CHUNKS);
@@ -167,15 +174,20 @@ va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner
 }
 // Time stamps inside the kernels, samples of 4096 and 8192 tokens: a step of the forward at head_dim 128 (32 keys) takes
 // 0.8 / 1.1 / 1.4 us with one, two, three workgroups on the CU, of dQ 1.6 / 2.8 us, of dK/dV 1.5-2 us; prologue and
-// epilogue together 6-8 us each; parts at 5 TB/s.  Only the ratios matter, and not much: one sample of 2048 to 16000
-// tokens, 2 to 4 heads, forward and backward, at each head_dim, with all constants at about 0.6 of these was 4 % faster
-// to 10 % slower, at about 1.6 of them 4 % faster to 21 % slower.
+// epilogue together 6-8 us each; parts at 5 TB/s.  Fitted to the times of 460 random batches at every head_dim, uncut and
+// cut into 256 to 1536 workgroups, the steps take 0.65-0.9 us (forward), 0.75-1.2 (dQ) and 0.85-1.4 (dK/dV), share 0.3-0.6,
+// fixed 5-8 (forward at 128: 15); with these constants the choice is on average 3 % off the best one tried, and in 1 of 60
+// cases more than 5 % behind the uncut launch.
 SmallCost fwd_cost(int head_dim) {
-    return head_dim == 128 ? SmallCost{va::fwd_small_slots(128) / 256, 0.37f, 8.f, 8.f, 0}
-                           : SmallCost{va::fwd_small_slots(head_dim) / 256, 0.37f, 6.f, 4.f, 0};
+    return head_dim == 128 ? SmallCost{va::fwd_small_slots(128) / 256, 0.37f, 8.f, 8.f, 4.f, 0}
+                           : SmallCost{va::fwd_small_slots(head_dim) / 256, 0.37f, 6.f, 4.f, 4.f, 0};
 }
-SmallCost dq_cost(int head_dim) { return SmallCost{va::bwd_dq_slots(head_dim) / 256, 0.5f, 5.f, 4.f, 2}; }
-SmallCost dkdv_cost(int head_dim) { return SmallCost{va::bwd_dkdv_slots(head_dim) / 256, 0.5f, 5.f, 8.f, 0}; }
+SmallCost dq_cost(int head_dim) {
+    return SmallCost{va::bwd_dq_slots(head_dim) / 256, 0.5f, 5.f, 4.f * head_dim / 128, 3.f, 2};
+}
+SmallCost dkdv_cost(int head_dim) {
+    return SmallCost{va::bwd_dkdv_slots(head_dim) / 256, 0.5f, 5.f, 8.f * head_dim / 128, 3.f, 0};
+}
 
 // How many workgroups share the keys of one query tile in the forward when the launch goes by a work list.
 // Splitting only pays when the launch cannot fill the chip: fewer workgroups than the 256 CUs can hold at once (3 per
@@ -218,7 +230,7 @@ FwdLayout fwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
         }
         if (f.end <= room || p->kv_splits != 0 || f.splits == 1) break;
     }
-    if (f.splits < f.plan.max_chunks) f.plan = va::SmallPlan{f.splits, f.plan.target, 0};
+    if (f.splits < f.plan.max_chunks) f.plan = va::SmallPlan{f.splits, f.plan.extra, 0};
     return f;
 }
 
@@ -258,7 +270,7 @@ BwdLayout bwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
         b.end = b.part_dv_ofs + part(b.plan_kv.max_chunks, p->num_kv_heads);
         va::SmallPlan& more = b.plan_q.max_chunks >= b.plan_kv.max_chunks ? b.plan_q : b.plan_kv;
         if (b.end <= room || more.max_chunks == 1) return b;
-        more = va::SmallPlan{more.max_chunks - 1, more.target, 0};
+        more = va::SmallPlan{more.max_chunks - 1, more.extra, 0};
     }
 }
 

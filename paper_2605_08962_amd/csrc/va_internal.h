@@ -68,8 +68,8 @@ hipError_t launch_check_cu_seqlens(const int32_t* cu_seqlens, int num_seqs, int 
 // How the walks of a small launch (va_small.h) are cut.
 struct SmallPlan {
     int max_chunks;  // per tile; 1: not at all
-    int target;      // workgroups to come to
-    int chunk;       // partner tiles per chunk, 0: worked out on the device from `target` and the samples' lengths
+    int extra;       // workgroups to come to beyond one per tile
+    int chunk;       // partner tiles per chunk, 0: worked out on the device from `extra` and the samples' lengths
 };
 
 struct FwdArgs {

@@ -171,3 +171,17 @@ def test_hints_above_1024_right_or_wrong(lengths, Hq, Hkv, D, causal):
         got = binding.varlen_attn_bwd(d["dout"], *x, *plain, d["cu"], causal, w.scale, max_seqlen=hint)
         assert_gradients_close(f"hint {hint}", tuple(to_f64(t) for t in got), w.f32("q"), w.f32("k"), w.f32("v"),
                                w.f32("dout"), w.cu_seqlens, causal, w.scale, to_f64(plain[0]), allow_output_rounding=True)
+
+
+@pytest.mark.parametrize("D,causal,H", [(64, False, 5), (80, True, 5), (96, False, 4), (128, False, 5)])
+def test_even_batches_without_the_hint_are_not_cut_where_their_tiles_fill_the_chip(D, causal, H):
+    """No walk is longer than the work there is for a CU anyway: the bits of the uncut call."""
+    from paper_2605_08962_amd import binding
+    lengths = [640] * 12
+    T, sc = sum(lengths), D ** -0.5
+    print(f"case {lengths} D={D} causal={causal}", flush=True)
+    q, k, v = _qkv(T, H, H, D, D)
+    assert binding.fwd_workspace_bytes(binding.make_params(T, len(lengths), H, H, D, causal, sc)) > 2 * T * H * D * 4
+    got = binding.varlen_attn_fwd(q, k, v, _cu(*lengths), causal, sc)
+    ref = binding.varlen_attn_fwd(q, k, v, _cu(*lengths), causal, sc, kv_splits=1)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))

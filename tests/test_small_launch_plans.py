@@ -64,3 +64,12 @@ def test_dq_of_small_launches_keeps_everything_in_registers():
     """Scratch loads in the loop wait for every tile load in flight.  The kernels' last template argument: small launches."""
     scratch = {n: b for n, b in _kernel_scratch_bytes().items() if re.search(r"dq_kernel(_direct)?ILi\d+ELb[01]ELb1E", n)}
     assert len(scratch) == 8 and not any(scratch.values()), scratch
+
+
+@pytest.mark.parametrize("T,B,H,D,causal,hint,cut", [
+    (39540, 30, 1, 128, True, 1318, False), (20061, 9, 2, 128, True, 2229, False),   # the chip is full of them uncut
+    (9415, 9, 4, 96, False, 9199, True), (3126, 2, 4, 80, False, 1563, True), (1343, 1, 8, 64, False, 1343, True),
+    (4096, 1, 2, 128, True, 4096, True)])
+def test_backward_is_cut_where_that_pays(T, B, H, D, causal, hint, cut):
+    size = lambda splits: binding.bwd_workspace_bytes(binding.make_params(T, B, H, H, D, causal, 0.1, splits, hint))
+    assert (size(0) > size(1)) == cut
