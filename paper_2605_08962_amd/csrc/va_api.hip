@@ -201,6 +201,17 @@ int fwd_kv_splits(const varlen_attn_params* p) {
     return (int)std::max<int64_t>(s, 1);
 }
 
+// Causal batches of several long samples with many tiles to a CU: what they gain by the list's order (tiles by falling
+// cost) is more than its launch, unless the small kernel keeps that order itself, at head_dim 128 (see small_tile).  Small
+// kernel / list, with the hint, 2 heads of 64 and 80: 20 samples of 2047 tokens 54 / 42 and 66 / 48 us, 14 of 3000 62 / 55 and
+// 76 / 65; about even at 1300 tokens (20 samples, 27 / 27 and 32 / 31) and at 280 pairs (8 of 2047, 31 / 31 and 36 / 35); 35
+// samples of 700 18 / 21 and 21 / 25.  At head_dim 96, where two workgroups fit a CU and not three, 11 of 2047 52 / 44.
+bool fwd_wants_order(const varlen_attn_params* p) {
+    const int64_t pairs = ((int64_t)p->total_tokens / va::FWD_TILE_Q + p->num_seqs) * p->num_q_heads;
+    return p->causal && p->num_seqs > 1 && p->head_dim != 128 && pairs > (p->head_dim == 96 ? 320 : 384) &&
+           p->total_tokens / p->num_seqs >= 1000;
+}
+
 struct FwdLayout {
     va::SchedLayout sched;
     bool small;
@@ -214,7 +225,8 @@ struct FwdLayout {
 FwdLayout fwd_layout(const varlen_attn_params* p, size_t room = SIZE_MAX) {
     FwdLayout f;
     f.sched = va::sched_layout(p->total_tokens, p->num_seqs, va::FWD_TILE_Q);
-    f.small = p->kv_splits == 0 && small_launch(p, va::FWD_TILE_Q, p->num_q_heads, va::fwd_small_slots(p->head_dim));
+    f.small = p->kv_splits == 0 && small_launch(p, va::FWD_TILE_Q, p->num_q_heads, va::fwd_small_slots(p->head_dim)) &&
+              !fwd_wants_order(p);
     f.plan = va::SmallPlan{1, 0, 0};
     if (f.small)
         f.plan = small_plan(p, va::FWD_TILE_Q, va::fwd_tile_kv(p->head_dim), p->causal ? va::COST_CAUSAL_QUERY : va::COST_FULL,
