@@ -117,6 +117,18 @@ struct SmallCost {
     int others;      // workgroups of the launch that do something else
 };
 
+// How many workgroups share the keys of one query tile in the forward when the launch goes by a work list.
+// Splitting only pays when the launch cannot fill the chip: fewer workgroups than the 256 CUs can hold at once (3 per
+// CU at head_dim <= 80, else 2), and samples long enough that every chunk still gets two key tiles.
+int fwd_kv_splits(const varlen_attn_params* p) {
+    if (p->kv_splits >= 1) return p->kv_splits;
+    const int64_t wgs = ((int64_t)p->total_tokens / va::FWD_TILE_Q + p->num_seqs) * p->num_q_heads;
+    const int64_t slots = 256 * (p->head_dim <= 80 ? 3 : 2);
+    const int64_t tiles_per_sample = expected_len(p) / va::FWD_TILE_KV;
+    int64_t s = std::min<int64_t>(std::min<int64_t>(slots / std::max<int64_t>(wgs, 1), tiles_per_sample / 2), VA_MAX_KV_SPLITS);
+    return (int)std::max<int64_t>(s, 1);
+}
+
 // How the walks of a small launch are cut: for the samples the caller's sizes lead to expect, the number of workgroups
 // per CU, up to twice what it holds at a time, for which the chunks come out cheapest.  With several samples it is how
 // many workgroups that is beyond one per tile that goes to the device, which finds the chunk that gives as many: what is
@@ -124,8 +136,9 @@ struct SmallCost {
 // causal, with a hint: forward 36 us where the number was one for all workgroups, 27 so).
 // Several samples without max_seqlen are reckoned with as one that holds all tokens, and the device cuts by the lengths it
 // finds: 8192 tokens and ten or twenty samples of 16, 2 heads of 64, forward, 107 us where the average was reckoned with,
-// 55 us so.  Four even samples of 400 pay for a merge launch that finds nothing to do, 10.6 -> 13.2 us; where the average is
-// under 256 tokens a sample worth cutting is less likely and such a call shorter yet, so there nothing is cut.
+// 55 us so.  Four even samples of 400 pay for a merge launch that finds nothing to do, 10.6 -> 13.2 us; so that is done only
+// where the chip has room for twice the workgroups and the average is 256 tokens: below that a sample worth cutting is less
+// likely and such a call shorter yet.
 // Samples of up to 512 tokens are not: uncut here / in 2 to 4 chunks by the work list, one of 512 tokens, 2 heads, took
 // 10.8 / 15.4 us at head_dim 64, 11.6 / 15.8 at 80, 17.0 / 17.0 at 128 (causal 18.3 / 17.8); four of 400 10.6 / 16.0.
 va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner_rows, va::CostMode mode, int heads,
@@ -135,7 +148,7 @@ va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner
     const int nu = (len + partner_rows - 1) / partner_rows, n = (len + tile_rows - 1) / tile_rows;
     const int samples = std::max(p->total_tokens / std::max(len, 1), 1);
     va::SmallPlan best{1, 0, 0};
-    if (nu * per_pair < 8 || len <= va::VA_SMALL_UNCUT_LEN || (unknown && expected_len(p) < 256)) return best;
+    if (nu * per_pair < 8 || len <= va::VA_SMALL_UNCUT_LEN || (unknown && fwd_kv_splits(p) < 2)) return best;
     const int longest = nu * per_pair, least = (longest + va::VA_SMALL_CHUNKS - 1) / va::VA_SMALL_CHUNKS;
     auto workgroups = [&](int chunk) {
         int64_t k = 0;
@@ -187,18 +200,6 @@ SmallCost dq_cost(int head_dim) {
 }
 SmallCost dkdv_cost(int head_dim) {
     return SmallCost{va::bwd_dkdv_slots(head_dim) / 256, 0.5f, 5.f, 8.f * head_dim / 128, 3.f, 0};
-}
-
-// How many workgroups share the keys of one query tile in the forward when the launch goes by a work list.
-// Splitting only pays when the launch cannot fill the chip: fewer workgroups than the 256 CUs can hold at once (3 per
-// CU at head_dim <= 80, else 2), and samples long enough that every chunk still gets two key tiles.
-int fwd_kv_splits(const varlen_attn_params* p) {
-    if (p->kv_splits >= 1) return p->kv_splits;
-    const int64_t wgs = ((int64_t)p->total_tokens / va::FWD_TILE_Q + p->num_seqs) * p->num_q_heads;
-    const int64_t slots = 256 * (p->head_dim <= 80 ? 3 : 2);
-    const int64_t tiles_per_sample = expected_len(p) / va::FWD_TILE_KV;
-    int64_t s = std::min<int64_t>(std::min<int64_t>(slots / std::max<int64_t>(wgs, 1), tiles_per_sample / 2), VA_MAX_KV_SPLITS);
-    return (int)std::max<int64_t>(s, 1);
 }
 
 // Causal batches of several long samples with many tiles to a CU: what they gain by the list's order (tiles by falling

@@ -173,11 +173,12 @@ def test_hints_above_1024_right_or_wrong(lengths, Hq, Hkv, D, causal):
                                w.f32("dout"), w.cu_seqlens, causal, w.scale, to_f64(plain[0]), allow_output_rounding=True)
 
 
-@pytest.mark.parametrize("D,causal,H", [(64, False, 5), (80, True, 5), (96, False, 4), (128, False, 5)])
-def test_even_batches_without_the_hint_are_not_cut_where_their_tiles_fill_the_chip(D, causal, H):
+@pytest.mark.parametrize("L,B,H,D,causal", [(640, 12, 5, 64, False), (640, 12, 5, 80, True), (640, 12, 3, 96, False),
+                                               (600, 14, 3, 128, False)])
+def test_even_batches_without_the_hint_are_not_cut_where_their_tiles_fill_the_chip(L, B, H, D, causal):
     """No walk is longer than the work there is for a CU anyway: the bits of the uncut call."""
     from paper_2605_08962_amd import binding
-    lengths = [640] * 12
+    lengths = [L] * B
     T, sc = sum(lengths), D ** -0.5
     print(f"case {lengths} D={D} causal={causal}", flush=True)
     q, k, v = _qkv(T, H, H, D, D)

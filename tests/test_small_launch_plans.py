@@ -76,7 +76,7 @@ def test_backward_is_cut_where_that_pays(T, B, H, D, causal, hint, cut):
 
 
 @pytest.mark.parametrize("T,B,H,D,by_list", [(6141, 3, 8, 80, True), (30294, 9, 3, 64, True), (30000, 10, 2, 96, True),
-                                             (10770, 2, 2, 64, False), (7626, 17, 4, 96, False), (6141, 3, 8, 128, False)])
+                                             (10770, 2, 2, 64, False), (5083, 17, 2, 96, False), (6141, 3, 2, 128, False)])
 def test_causal_batches_of_long_samples_keep_the_order_of_the_list(T, B, H, D, by_list):
     """Causal forward with many tiles to a CU: as the work list has it, not cut; elsewhere the plan cuts."""
     size = lambda splits: binding.fwd_workspace_bytes(binding.make_params(T, B, H, H, D, True, 0.1, splits))
