@@ -102,11 +102,12 @@ size_t varlen_attn_bwd_workspace_bytes(const varlen_attn_params *p);
  * cu_seqlens into a list of 128-row query tiles ordered by decreasing cost; one workgroup per
  * (tile, head) streams the sample's K/V through LDS, S = QK^T and PV on bf16 MFMA, online softmax.
  * A launch too small to fill the GPU (at most 64 samples and fewer (tile, head) pairs than workgroups fit on the
- * chip: what a rank sees in the sequence-parallel state of Section 4.1.1, or a handful of short samples) goes without
+ * chip: what a rank sees in the sequence-parallel state of Section 4.1.1, or a handful of short samples; causal batches
+ * of long samples close to that limit are left out) goes without
  * the scheduler: every workgroup finds its tile from cu_seqlens.  With kv_splits = 0 the keys of its query tiles are
  * cut into up to 8 chunks of about equal length, one workgroup each, which write fp32 partial results into the
  * workspace, and a merge kernel combines them (same formula as varlen_attn_merge); how many is chosen from the sizes
- * (max_seqlen where given, else the average length), so that a sample's result then depends, to rounding, on what it
+ * (max_seqlen where given, else total_tokens and num_seqs), so that a sample's result then depends, to rounding, on what it
  * is launched with.  kv_splits = 1 cuts nothing, 2..8 forces that many chunks per tile.  The workspace size accounts
  * for it; a smaller workspace gets fewer of the automatic chunks.
  * A batch of short samples only (0 < max_seqlen <= 1024, keys not split) takes a leaner form of the same
