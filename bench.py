@@ -29,7 +29,7 @@ PEAK_BF16_TFLOPS = 2500.0  # dense bf16 MFMA, MI355X
 CSRC = os.path.join(ROOT, "paper_2605_08962_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_per_kernel.json")
 KERNEL_SYMBOL = {"fwd": "fwd_kernel", "dkdv": "dkdv_kernel", "dq": "dq_kernel"}
-KERNEL_SYMBOLS_ALL = ("fwd_kernel_lean", "fwd_kernel", "dkdv_kernel", "dq_kernel_direct", "dq_kernel")
+KERNEL_SYMBOLS_ALL = ("fwd_kernel_lean", "fwd_kernel", "dkdv_kernel", "dq_kernel")
 
 
 def kernel_source_hash():
@@ -44,10 +44,7 @@ def kernel_source_hash():
 
 
 def _instance(kernel, head_dim, causal):
-    sym = KERNEL_SYMBOL[kernel]
-    if kernel == "dq" and head_dim != 80:
-        sym = "dq_kernel_direct"        # head_dim 80 alone keeps the phased dQ kernel
-    return f"{sym}<{head_dim}, {'true' if causal else 'false'}>"
+    return f"{KERNEL_SYMBOL[kernel]}<{head_dim}, {'true' if causal else 'false'}>"
 
 
 def measured_traffic(kernel, head_dim, causal):
@@ -92,7 +89,7 @@ def record_traffic(paths):
     kernels = {}
     for (counter, name), (v, ids) in val.items():
         for sym in KERNEL_SYMBOLS_ALL:
-            # demangled "va::fwd_kernel<64, false>(...)" or "va::dq_kernel_direct<64, false, false>(...)" (the third:
+            # demangled "va::fwd_kernel<64, false>(...)" or "va::dq_kernel<64, false, false>(...)" (the third:
             # the form for launches that do not fill the chip, which is not counted here), or, where the profiler's
             # demangler gave up, the mangled "_ZN2va11dkdv_kernelILi64ELb0ELb0ELi2EEEv..."
             m = re.search(r"va::%s<(\d+), (true|false)(?:, false(?:, \d+)?)?>" % sym, name)

@@ -7,17 +7,25 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvarlen_attn.so")
-# (source, object name, extra flags).  va_bwd.hip is built in three parts: the head_dim 128 dK/dV and dQ
-# kernels get their own instruction-scheduling strategy (measured faster there: dK/dV 7 %, the two-workgroup dQ
-# kernel 1-7 %; slower for the other head sizes), and dK/dV at 128 is told to let MFMAs write S and dP into
-# ordinary vector registers: it runs one wave per SIMD on more than 256 registers, and the default puts every
-# MFMA result into the accumulation half of the register file, from where the vector ALU needs a copy per
-# register (64 per step; 5 % of its time).
+# (source, object name, extra flags).  va_bwd.hip is built in parts, each under the instruction-scheduling strategy that
+# measured best for its kernels among the default, iterative-ilp, iterative-minreg, iterative-maxocc, max-ilp and
+# max-memory-clause (64 ViT samples, 16 heads, unless said otherwise; the forward does best with the default):
+#   dQ iterative-ilp: LLM batch at head_dim 128 7 % faster than the default, 64 without the mask even, causal 1.3-3 %; head_dim
+#     96 1.6 %; 80 29.6 against 31.6 ms (65536 tokens and 256 short samples).
+#   dK/dV at 128, causal: iterative-ilp 7 % (iterative-maxocc: batches of 64..1024 tokens 1058 against 985 us); without the
+#     mask iterative-maxocc 10.58 -> 10.23 ms, 8 x 8192 tokens 7.61 -> 7.30 ms.
+#   dK/dV at 96: iterative-maxocc, 8.92 -> 8.41 ms.  At 80: iterative-minreg, 1 % (iterative-ilp: 8 % slower).
+# dK/dV at 96 and 128 are also told to let MFMAs write S and dP into ordinary vector registers: they run one wave per SIMD on
+# more than 256 registers, and the default puts every MFMA result into the accumulation half of the register file, from
+# where the vector ALU needs a copy per register (64 per step; 5 % of the time at 128, 9.52 -> 8.41 ms at 96).
+_SCHED = "-amdgpu-sched-strategy="
+_VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 SOURCES = [("va_api.hip", "va_api.o", []), ("va_sched.hip", "va_sched.o", []), ("va_fwd.hip", "va_fwd.o", []),
            ("va_bwd.hip", "va_bwd.o", ["-DVA_BWD_PART=0"]),
-           ("va_bwd.hip", "va_bwd_dkdv128.o", ["-DVA_BWD_PART=1", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp",
-                                               "-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
-           ("va_bwd.hip", "va_bwd_dq128.o", ["-DVA_BWD_PART=2", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]),
+           ("va_bwd.hip", "va_bwd_dkdv128c.o", ["-DVA_BWD_PART=1", "-mllvm", _SCHED + "iterative-ilp", *_VGPR_FORM]),
+           ("va_bwd.hip", "va_bwd_dq.o", ["-DVA_BWD_PART=2", "-mllvm", _SCHED + "iterative-ilp"]),
+           ("va_bwd.hip", "va_bwd_dkdv80.o", ["-DVA_BWD_PART=3", "-mllvm", _SCHED + "iterative-minreg"]),
+           ("va_bwd.hip", "va_bwd_dkdv128.o", ["-DVA_BWD_PART=4", "-mllvm", _SCHED + "iterative-maxocc", *_VGPR_FORM]),
            ("va_partition.hip", "va_partition.o", []), ("va_merge.hip", "va_merge.o", [])]
 # -packed-fp32-ops is switched off on purpose: hipcc must not form v_pk_*_f32 from float code.
 # -fno-honor-nans: the kernels never produce NaN from finite inputs (masked scores use a finite

@@ -11,19 +11,16 @@
 //            (contraction over query rows).
 //   dq     : one workgroup per (128-row query tile, query head); loops over 64-row key steps;
 //            S^T = K Q^T is kept with one QUERY per lane (as in the forward), so that dS^T is the
-//            B operand of dQ^T += K^T dS^T (contraction over key rows).  Two forms: dq_kernel (head_dim 80:
-//            phases, four LDS stages) and dq_kernel_direct (64, 96 and 128: operands read at use, two
-//            stages, more workgroups per CU).
+//            B operand of dQ^T += K^T dS^T (contraction over key rows).
 // Splitting the backward this way needs no atomics and no fp32 dQ buffer, and the result does not
 // depend on scheduling order; it recomputes S and dP once more than a fused kernel would.
 //
 // Staging is the forward's: 64-row tiles go straight from HBM/L2 into XOR-swizzled LDS tiles with
 // direct-to-LDS loads, three stages deep, one barrier per step, completion tracked with vmcnt.
 //
-// The file is compiled three times (VA_BWD_PART): part 0 holds everything but the head_dim 128 dK/dV
-// and dQ kernels, which parts 1 and 2 build under a different instruction-scheduling strategy of the
-// compiler (measured 7 % and up to 7 % faster there, slower for the other head sizes; part 1 also with
-// MFMA results in ordinary vector registers, see build.py).
+// The file is compiled in five parts (VA_BWD_PART), each under the instruction-scheduling strategy of the compiler that
+// measured best for its kernels (build.py): 1 dK/dV at head_dim 128, causal; 2 dQ; 3 dK/dV at 80; 4 dK/dV at 96, and at 128
+// without the mask; 0 the rest.
 #include "va_device.h"
 #include "va_internal.h"
 #include "va_sched.h"
@@ -34,8 +31,10 @@
 #endif
 
 namespace va {
-hipError_t launch_dkdv_128(const BwdArgs& a, hipStream_t stream);  // part 1
-hipError_t launch_dq_128(const BwdArgs& a, hipStream_t stream);    // part 2
+hipError_t launch_dkdv_128_causal(const BwdArgs& a, hipStream_t stream);  // part 1
+hipError_t launch_dkdv_80(const BwdArgs& a, hipStream_t stream);          // part 3
+hipError_t launch_dkdv_96(const BwdArgs& a, hipStream_t stream);          // part 4
+hipError_t launch_dkdv_128_full(const BwdArgs& a, hipStream_t stream);    // part 4
 
 template <int D>
 struct BwdCfg {
@@ -44,6 +43,7 @@ struct BwdCfg {
     static constexpr int DB = (D + 31) / 32;
     static constexpr int TILE = 64 * T::ROWB;        // one 64-row tile in LDS
     static constexpr int NI = TileDma<D, 64>::NI;    // load instructions per wave per tile
+    static constexpr int EXTRA = TileDma<D, 64>::EXTRA;  // and per pair of tiles
     static constexpr int STAT_BYTES = 4 * 128;       // per wave: 16 x lse2, 16 x delta
 };
 
@@ -280,8 +280,8 @@ __device__ __forceinline__ void dkdv_interleave() {
     }
 }
 
-// Load K of the 2*NI + 1 direct-to-LDS loads of one dK/dV step: K = 0 the stats, then NI loads of the Q
-// tile, then NI of the dO tile.  K beyond that is a no-op, so callers can name slots freely.
+// Load K of the 2*NI + EXTRA + 1 direct-to-LDS loads of one dK/dV step: K = 0 the stats, then NI loads of the Q
+// tile, NI of the dO tile, and what is left of the two.  K beyond that is a no-op, so callers can name slots freely.
 template <int D, int K>
 __device__ __forceinline__ void dkdv_issue_part(bool ragged, const TileDma<D, 64>& dma, const unsigned char* q,
                                                 const unsigned char* dO, const unsigned char* st,
@@ -290,9 +290,11 @@ __device__ __forceinline__ void dkdv_issue_part(bool ragged, const TileDma<D, 64
     if constexpr (K == 0) {
         dma4(st, stat_off, lds + 2 * BwdCfg<D>::TILE + (wave & 1) * 256);
     } else if constexpr (K <= NI) {
-        dma.template issue_one<K - 1>(q, ragged, lds, wave);
+        dma.issue_one(K - 1, q, ragged, lds, wave);
     } else if constexpr (K <= 2 * NI) {
-        dma.template issue_one<K - 1 - NI>(dO, ragged, lds + BwdCfg<D>::TILE, wave);
+        dma.issue_one(K - 1 - NI, dO, ragged, lds + BwdCfg<D>::TILE, wave);
+    } else if constexpr (K == 2 * NI + 1) {
+        dma.issue_extra(q, dO, ragged, ragged, lds, lds + BwdCfg<D>::TILE, wave);
     }
 }
 
@@ -328,7 +330,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     using C = BwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr int STAGE = 2 * C::TILE + C::STAT_BYTES;  // Q tile, dO tile, stats
-    constexpr int PER = 2 * C::NI + 1;                  // loads per wave per step
+    constexpr int PER = 2 * C::NI + C::EXTRA + 1;       // loads per wave per step
     // LDS stages: four where two workgroups per CU are out of reach anyway or still fit (head_dim 64),
     // three at head_dim 80, where the fourth would cost the second workgroup
     constexpr int NST = D == 80 ? 3 : 4;
@@ -441,8 +443,8 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     auto issue_all = [&]() {
         begin_issue();
         issue_stat();
-        dma.issue_tile(iss_q, iss_ragged, iss_lds, w);
-        dma.issue_tile(iss_do, iss_ragged, iss_lds + C::TILE, w);
+        dma.issue_tile(iss_q, iss_ragged, iss_lds, w, false);
+        dma.issue_tile(iss_do, iss_ragged, iss_lds + C::TILE, w, true);
     };
 
     int aaddr[C::KS], taddr[OB][2];
@@ -677,106 +679,24 @@ int bwd_dkdv_slots(int head_dim) { return 256 * (head_dim <= 80 ? kDkdvWgsPerCu<
 hipError_t launch_bwd_dkdv(const BwdArgs& a, hipStream_t stream) {
     switch (a.head_dim) {
         case 64: return launch_dkdv_d<64>(a, stream);
-        case 80: return launch_dkdv_d<80>(a, stream);
-        case 96: return launch_dkdv_d<96>(a, stream);
-        case 128: return launch_dkdv_128(a, stream);
+        case 80: return launch_dkdv_80(a, stream);
+        case 96: return launch_dkdv_96(a, stream);
+        case 128: return a.causal ? launch_dkdv_128_causal(a, stream) : launch_dkdv_128_full(a, stream);
         default: return hipErrorInvalidValue;
     }
 }
 #elif VA_BWD_PART == 1
-hipError_t launch_dkdv_128(const BwdArgs& a, hipStream_t stream) { return launch_dkdv_d<128>(a, stream); }
+hipError_t launch_dkdv_128_causal(const BwdArgs& a, hipStream_t stream) { return launch_dkdv_dc<128, true>(a, stream); }
+#elif VA_BWD_PART == 3
+hipError_t launch_dkdv_80(const BwdArgs& a, hipStream_t stream) { return launch_dkdv_d<80>(a, stream); }
+#elif VA_BWD_PART == 4
+hipError_t launch_dkdv_96(const BwdArgs& a, hipStream_t stream) { return launch_dkdv_d<96>(a, stream); }
+hipError_t launch_dkdv_128_full(const BwdArgs& a, hipStream_t stream) { return launch_dkdv_dc<128, false>(a, stream); }
 #endif
 
 // ------------------------------------------------------------------------------------------------
 // dQ
 // ------------------------------------------------------------------------------------------------
-// The step that holds the sample's end, for the kernel without the causal mask (under it the masked steps
-// run in phases, see dq_kernel): keys and rows beyond the sample are masked, dS goes through its MFMAs as
-// bf16 hi + lo.  Operands are read right before use.
-template <int D>
-__device__ __forceinline__ void dq_end_step(const unsigned char* kt, const unsigned char* vt,
-                                            const int (&aaddr)[BwdCfg<D>::KS], const int (&taddr)[BwdCfg<D>::DB][2],
-                                            const bf16x8 (&qf)[BwdCfg<D>::KS], const bf16x8 (&dof)[BwdCfg<D>::KS],
-                                            f32x16 (&dqacc)[BwdCfg<D>::DB], float c2, float lse2, float ndelta,
-                                            int kv0, int qrow, int L, int hh) {
-    using C = BwdCfg<D>;
-    constexpr int ROWB = C::T::ROWB;
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        if (b && kv0 + 32 >= L) break;  // the sample ends in the first half: the second adds zeros
-        f32x16 s, dp;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 ak = *(const bf16x8*)(kt + aaddr[ks] + b * 32 * ROWB);
-            s = mfma32(ak, qf[ks], s);
-            bf16x8 av = *(const bf16x8*)(vt + aaddr[ks] + b * 32 * ROWB);
-            dp = mfma32(av, dof[ks], dp);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float p = fast_exp2(__builtin_fmaf(s[r], c2, -lse2));
-            const int kv = kv0 + 32 * b + 8 * (r / 4) + 4 * hh + (r % 4);
-            p = (kv < L && qrow < L) ? p : 0.f;
-            dp[r] = p * (dp[r] + ndelta);
-        }
-#pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const bf16x8 dsb = pack_regs(dp, st);
-            const bf16x8 dsl = pack_regs_lo(dp, st, dsb);
-            const int rowoff = (32 * b + 16 * st) * ROWB;
-#pragma unroll
-            for (int db = 0; db < C::DB; ++db) {
-                bf16x8 ak = cat4(lds_read_tr(kt + rowoff + taddr[db][0]), lds_read_tr(kt + rowoff + taddr[db][1]));
-                dqacc[db] = mfma32(ak, dsb, dqacc[db]);
-                dqacc[db] = mfma32(ak, dsl, dqacc[db]);
-            }
-        }
-    }
-}
-
-// ---- the mask-free dQ step in phases (see the dK/dV kernel): S | dP with exp in its shadow | dQ
-// with dS in its shadow; the LDS operands of a phase are read one phase ahead ----
-template <int D>
-struct DqOpsA {  // operands of S^T = K Q^T or dP^T = V dO^T for the step's two 32-key blocks
-    bf16x8 a[2][BwdCfg<D>::KS];
-};
-template <int D>
-struct DqOpsT {  // K^T operands of dQ^T += K^T dS^T: key block b, 16-key step st, 32-channel block db
-    bf16x8 a[2][2][BwdCfg<D>::DB];
-};
-template <int D>
-__device__ __forceinline__ void dq_load_A(const unsigned char* tile, const int (&aaddr)[BwdCfg<D>::KS], DqOpsA<D>& f) {
-    constexpr int ROWB = BwdCfg<D>::T::ROWB;
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int ks = 0; ks < BwdCfg<D>::KS; ++ks) f.a[b][ks] = *(const bf16x8*)(tile + aaddr[ks] + b * 32 * ROWB);
-}
-template <int D>
-__device__ __forceinline__ void dq_load_T(const unsigned char* kt, const int (&taddr)[BwdCfg<D>::DB][2], DqOpsT<D>& f) {
-    constexpr int ROWB = BwdCfg<D>::T::ROWB;
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int db = 0; db < BwdCfg<D>::DB; ++db) {
-                const unsigned char* p0 = kt + (32 * b + 16 * st) * ROWB;
-                f.a[b][st][db] = cat4(lds_read_tr(p0 + taddr[db][0]), lds_read_tr(p0 + taddr[db][1]));
-            }
-}
-// acc[b] = init + sum_ks ops[b][ks] x frag[ks]
-template <int D>
-__device__ __forceinline__ void dq_run_A(const DqOpsA<D>& f, const bf16x8 (&frag)[BwdCfg<D>::KS], const f32x16& init,
-                                         f32x16 (&acc)[2]) {
-#pragma unroll
-    for (int ks = 0; ks < BwdCfg<D>::KS; ++ks)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = mfma32(f.a[b][ks], frag[ks], ks == 0 ? init : acc[b]);
-}
-
 // A small launch's dQ (va_small.h): every workgroup finds its tile, or chunk of a tile, from cu_seqlens.  The first two
 // build the work lists on the side, which no kernel of the call reads: the workspace holds them after every backward, for
 // comparison with the lists computed on the host.  Measured with and without, backward: four samples of 246 tokens in all
@@ -852,253 +772,16 @@ __device__ __forceinline__ void dq_store_part(const f32x16 (&dqacc)[BwdCfg<D>::D
         }
 }
 
-template <int D, bool CAUSAL, bool SMALL>
-__global__ void __launch_bounds__(256, (kDqWgsPerCu<D>))
-dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
-          const __bf16* __restrict__ dO, const __bf16* __restrict__ O, const float* __restrict__ LSE,
-          float2* __restrict__ stats, __bf16* __restrict__ dQ, const int32_t* __restrict__ hdr, const WorkItem* __restrict__ items,
-          int max_items, int T, int Hq, int Hkv, float scale, DqSmall small, unsigned long long* __restrict__ clock_probe) {
-    using C = BwdCfg<D>;
-    using LT = LdsTile<D>;
-    constexpr int STAGE = 2 * C::TILE;  // K tile, V tile
-    constexpr int NST = 4;              // LDS stages
-    constexpr int PER = 2 * C::NI;      // loads per wave per step
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
-
-    DqWork wk;
-    ClockProbe wg_clock;
-    wg_clock.begin(clock_probe);
-    if (!dq_find_work<D, CAUSAL, SMALL>(hdr, items, max_items, T, Hq, Hkv, small, lds, wk)) return;
-    const int sb = wk.sb, L = wk.L, q0 = wk.q0, h = wk.h, kvh = wk.kvh;
-
-    const int tid = threadIdx.x, w = uniform_wave_id(), l = tid & 63, ln = l & 31, hh = l >> 5;
-    const int qrow = q0 + 32 * w + ln;
-    const bool qvalid = qrow < L;
-
-    const int je = wk.je;  // key steps [wk.jb, je)
-    const int n_plain = min(je, (CAUSAL ? min(L, q0 + 1) : L) / BWD_STEP_KV);
-    const unsigned char* kbase = (const unsigned char*)(K + ((size_t)sb * Hkv + kvh) * D);
-    const unsigned char* vbase = (const unsigned char*)(V + ((size_t)sb * Hkv + kvh) * D);
-    const uint32_t row_bytes = (uint32_t)Hkv * D * 2;
-    TileDma<D, 64, D == 80> dma;
-    dma.init(row_bytes, L, w, l);
-    const uint32_t lds0 = lds_address(lds);
-    // Staging, as in the dK/dV kernel: pointers advanced by additions, loads issued unconditionally
-    // (after the last step the same step is fetched again into a stage nobody reads), so that every
-    // step has the same number of loads in flight and the loop needs no branches around them.
-    const int64_t step_bytes = (int64_t)BWD_STEP_KV * row_bytes;
-    const bool ragged_sample = (L % BWD_STEP_KV) != 0;
-    const int last_step = (L + BWD_STEP_KV - 1) / BWD_STEP_KV - 1;  // the one holding the sample's end
-    const unsigned char *nxt_k = kbase + wk.jb * step_bytes, *nxt_v = vbase + wk.jb * step_bytes;
-    int nxt_j = wk.jb, iss_stage = 0;
-    bool iss_ragged = false;
-    const unsigned char *iss_k = nullptr, *iss_v = nullptr;
-    uint32_t iss_lds = 0;
-    auto begin_issue = [&]() {
-        iss_k = nxt_k; iss_v = nxt_v;
-        iss_ragged = ragged_sample && nxt_j == last_step;
-        iss_lds = lds0 + iss_stage * STAGE;
-        iss_stage = iss_stage == NST - 1 ? 0 : iss_stage + 1;
-        const bool more = nxt_j + 1 < je;
-        const int64_t adv = more ? step_bytes : 0;
-        nxt_k += adv; nxt_v += adv;
-        nxt_j += more ? 1 : 0;
-    };
-    auto issue_all = [&]() {
-        begin_issue();
-        dma.issue_tile(iss_k, iss_ragged, iss_lds, w);
-        dma.issue_tile(iss_v, iss_ragged, iss_lds + C::TILE, w);
-    };
-
-    int aaddr[C::KS], taddr[C::DB][2];
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) aaddr[ks] = LT::off(ln, 2 * ks + hh);
-#pragma unroll
-    for (int db = 0; db < C::DB; ++db) {
-        taddr[db][0] = LT::tr_off(l, 0, db);
-        taddr[db][1] = LT::tr_off(l, 8, db);
-    }
-
-    issue_all();
-    issue_all();
-    issue_all();
-    bf16x8 qf[C::KS], dof[C::KS];
-    float lse2 = 0.f, ndelta = 0.f;  // ndelta = -Delta
-    {
-        const size_t off = ((size_t)(sb + (qvalid ? qrow : 0)) * Hq + h) * D + 8 * hh;
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 z = {};
-            qf[ks] = qvalid ? *(const bf16x8*)(Q + off + 16 * ks) : z;
-            dof[ks] = qvalid ? *(const bf16x8*)(dO + off + 16 * ks) : z;
-        }
-        // Row statistics of this lane's row: Delta = sum_d dO * O (each half of the wave sums its 8 of
-        // every 16 columns), and the saved LSE in base 2.  Written out for the dK/dV kernel.
-        float part = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 z = {};
-            const bf16x8 of = qvalid ? *(const bf16x8*)(O + off + 16 * ks) : z;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)dof[ks][e], (float)of[e], part);
-        }
-        ndelta = -xhalf_sum(part);
-        if (qvalid) {
-            lse2 = LSE[(size_t)h * T + sb + qrow] * kLog2e;
-            if (hh == 0 && wk.ch == 0) stats[(size_t)h * T + sb + qrow] = make_float2(lse2, ndelta);
-        }
-    }
-    wait_vmcnt<0>();
-    wg_barrier();
-    if constexpr (D > 80) {  // one wave per SIMD: see park_in_acc_registers
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) { park_in_acc_registers(qf[ks]); park_in_acc_registers(dof[ks]); }
-    }
-
-    f32x16 dqacc[C::DB];
-#pragma unroll
-    for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dqacc[db][r] = 0.f;
-    const float c2 = scale * kLog2e;
-    // causal: only a sample's first rows hold few terms, and only those need dS as bf16 hi + lo
-    const bool lo_steps = !CAUSAL || q0 == 0;
-
-    // Stage protocol as in the dK/dV kernel: step i lives in stage i % 4; the sync at the start of a step
-    // waits until step i + 1 has landed (step i + 2 may stay in flight) and passes the barrier, after
-    // which every wave is done with step i - 1, whose stage this step's loads refill.
-    int stage_i = 0;
-    int j = wk.jb;
-    if (q0 + 32 * w >= L) {  // no row of this wave exists: loads and barriers only (see the forward kernel)
-        for (; j < je; ++j) {
-            wait_vmcnt<PER>();
-            wg_barrier();
-            issue_all();
-        }
-        wait_vmcnt<0>();
-        return;
-    }
-    f32x16 nd16, zero16;  // -Delta of this lane's row as the starting value of dP; 0 for S
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { nd16[r] = ndelta; zero16[r] = 0.f; }
-    DqOpsA<D> fa;  // K rows for S, then V rows for dP
-    DqOpsA<D> fv;
-    DqOpsT<D> ft;
-    f32x16 s[2], dp[2];
-    dq_load_A<D>(lds + stage_i * STAGE, aaddr, fa);
-    // One key step in phases.  Masked steps (the causal diagonal, the sample's end) zero P outside the
-    // mask; fully masked waves run them all the same, they would only wait at the next barrier.
-    auto step = [&](auto masked_tag) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        wait_vmcnt<PER>();
-        wg_barrier();
-        const unsigned char* cur = lds + stage_i * STAGE;
-        const unsigned char* nxt = lds + (stage_i == NST - 1 ? 0 : stage_i + 1) * STAGE;
-        // S^T = K Q^T; meanwhile fetch the V rows and do the scalar bookkeeping of this step's loads
-        dq_load_A<D>(cur + C::TILE, aaddr, fv);
-        dq_run_A<D>(fa, qf, zero16, s);
-        begin_issue();
-        __builtin_amdgcn_sched_barrier(0);
-        dma.issue_tile(iss_k, iss_ragged, iss_lds, w);
-        // dP^T = V dO^T - Delta with P = exp2(c2 S - lse2) in its shadow; meanwhile fetch K^T
-        dq_load_T<D>(cur, taddr, ft);
-        dq_run_A<D>(fv, dof, nd16, dp);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                float p = fast_exp2(__builtin_fmaf(s[b][r], c2, -lse2));
-                if (MASKED) {
-                    const int kv = j * BWD_STEP_KV + 32 * b + 8 * (r / 4) + 4 * hh + (r % 4);
-                    const bool ok = kv < L && qrow < L && (!CAUSAL || kv <= qrow);
-                    p = ok ? p : 0.f;
-                }
-                s[b][r] = p;
-            }
-        dkdv_interleave<2 * C::KS, 4 * C::DB / C::KS, 8>();
-        __builtin_amdgcn_sched_barrier(0);
-        dma.issue_tile(iss_v, iss_ragged, iss_lds + C::TILE, w);
-        // dQ^T += K^T dS^T with dS = P (dP - Delta) in its shadow; meanwhile fetch the next step's K rows
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int st = 0; st < 2; ++st) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dp[b][8 * st + e] *= s[b][8 * st + e];
-                const bf16x8 dsb = pack_regs(dp[b], st);
-#pragma unroll
-                for (int db = 0; db < C::DB; ++db) dqacc[db] = mfma32(ft.a[b][st][db], dsb, dqacc[db]);
-            }
-        dq_load_A<D>(nxt, aaddr, fa);
-        dkdv_interleave<4 * C::DB, 2 * C::KS / (4 * C::DB) + 1, 6>();
-        __builtin_amdgcn_sched_barrier(0);
-        if (MASKED && lo_steps) {  // the lo parts of dS, on the K^T operands still in registers
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int st = 0; st < 2; ++st) {
-                    const bf16x8 dsl = pack_regs_lo(dp[b], st, pack_regs(dp[b], st));
-#pragma unroll
-                    for (int db = 0; db < C::DB; ++db) dqacc[db] = mfma32(ft.a[b][st][db], dsl, dqacc[db]);
-                }
-        }
-        stage_i = stage_i == NST - 1 ? 0 : stage_i + 1;
-    };
-    for (; j < n_plain; ++j) step(std::false_type{});
-    if constexpr (CAUSAL) {
-        for (; j < je; ++j) step(std::true_type{});
-    } else {
-        // Without the causal mask the only masked step is the one holding the sample's end: it takes the
-        // simple form (the phased one with hi + lo in every such step needs more registers than there are).
-        // Its sync sits at its end: the step's own stage was published by the sync before.
-        for (; j < je; ++j) {
-            dq_end_step<D>(lds + stage_i * STAGE, lds + stage_i * STAGE + C::TILE, aaddr, taddr, qf, dof,
-                           dqacc, c2, lse2, ndelta, j * BWD_STEP_KV, qrow, L, hh);
-            wait_vmcnt<PER>();
-            wg_barrier();
-            issue_all();
-            stage_i = stage_i == NST - 1 ? 0 : stage_i + 1;
-        }
-    }
-    wait_vmcnt<0>();  // the surplus loads issued near the end must land before this LDS is given away
-
-    if (SMALL && wk.nch > 1) {
-        if (qvalid) dq_store_part<D>(dqacc, small.part + (((size_t)wk.ch * T + sb + qrow) * Hq + h) * D, hh);
-    } else if (qvalid) {
-        __bf16* dqp = dQ + ((size_t)(sb + qrow) * Hq + h) * D;
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int d0 = 32 * db + 8 * r4 + 4 * hh;
-                if (d0 < D) {
-                    bf16x4 a;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) a[e] = (__bf16)(dqacc[db][4 * r4 + e] * scale);
-                    *(bf16x4*)(dqp + d0) = a;
-                }
-            }
-    }
-    wg_clock.end(clock_probe);
-}
-
 // ------------------------------------------------------------------------------------------------
-// dQ with the operands read right before their MFMAs: the dQ kernel of head_dim 64, 96 and 128.
-//
-// dq_kernel above keeps three sets of operands in flight (its phases) and four LDS stages.  At head_dim 96 and
-// 128 that takes 400 registers and 128 KB: one workgroup per CU, whose start (Q, dO, O, LSE, three stages of
-// K/V, all waited for) and end (stores) then run with nothing beside them; a query tile under the causal mask
-// has only (q0 + 128) / 64 key steps to spread that over: measured, the fixed cost of an item was about 8 of
-// its steps, and the matrix pipes were 41 % busy on the LLM batch against 60 % elsewhere.
-// This form keeps 32 keys of S and dP live at a time, double-buffers K/V in two LDS stages and fits 256
-// registers at head_dim 128 (150 at 64), so two (three at 64) workgroups share a CU and one's start and end
-// hide behind the others' steps.  Same arithmetic per element as dq_kernel (P, dP - Delta, dS rounded to
-// bf16, hi + lo where rows can have few keys).  Measured against dq_kernel:
-//   head_dim 128: the LLM batch's dQ 2.23 -> 1.79 ms, 16384-token causal samples 6.33 -> 5.33 ms, the same
-//     without the mask 5.73 -> 5.24 ms, 512-token causal samples 0.63 -> 0.44 ms; head_dim 96: 20-26 % faster;
-//   head_dim 64: the ViT batch's dQ 3.89 -> 3.81 ms, batches of 64..1024-token samples 9-15 % faster;
-//   head_dim 80: slower (32.6 against 30.6 ms on the long/short mix; its 20 KB tiles and three partly masked
-//     loads per tile leave it short of registers at three workgroups per CU), so head_dim 80 keeps dq_kernel.
+// The dQ kernel.  What bounds it is instruction issue, and at a workgroup's start (Q, dO, O, LSE and the first K/V tiles, all
+// waited for) and end memory latency, about 8 key steps' worth of it, which only another workgroup on the CU can cover.  So
+// K/V are double-buffered in two LDS stages, every operand is read right before its MFMAs, and two workgroups (three at
+// head_dim 64) fit a CU: 150 registers and 32 KB at head_dim 64, 246 and 64 KB at 128.
+// A form with four stages and the operands of a phase read one phase ahead (400 registers at 128, one workgroup per CU) took
+// 2.23 ms for the LLM batch's dQ against 1.79, 0.63 against 0.44 for 512-token causal samples, 3.89 against 3.81 for the ViT
+// batch.  At head_dim 80 it lost its lead with the loads without idle lanes and the compiler's strategy for this file's part 2
+// (iterative-ilp), and both blocks of a step scheduled together there: four stages -> two, 65536 tokens and 256 short samples,
+// 16 heads, 30.6 -> 30.1 ms; 256 samples of 64..1024 tokens 605 -> 549 us, causal 581 -> 500; LLM batch 1283 -> 1241.
 // (The operands that only the matrix cores touch are left to the compiler here: parked in the accumulation
 // half they pin 128 of the 256 registers there and the vector half spills.)
 // ------------------------------------------------------------------------------------------------
@@ -1113,7 +796,10 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         if (MASKED && b && kv0 + 32 >= L) break;   // the sample ends in the first block: the second adds zeros
-        if (b) __builtin_amdgcn_sched_barrier(0);  // keep the second block's operand reads behind the first block
+        // The second block's operand reads stay behind the first block: mixed, dQ took 8 % longer at head_dim 128, 3 % at 64
+        // (three workgroups per CU), about the same at 96.  Head_dim 80 has the registers (256 of 256): 0.6 % faster mixed on
+        // 65536 tokens, 1.5 % on 64..1024.
+        if (b && D != 80) __builtin_amdgcn_sched_barrier(0);
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -1145,7 +831,7 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
                 dqacc[db] = mfma32(ak, dsb, dqacc[db]);
             }
         }
-        if (MASKED && lo) {  // wave-uniform: the lo parts of dS, in a pass of their own (as in dq_kernel)
+        if (MASKED && lo) {  // wave-uniform: the lo parts of dS, in a pass of their own
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 const bf16x8 dsl = pack_regs_lo(dp, st, pack_regs(dp, st));
@@ -1162,7 +848,7 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
 
 template <int D, bool CAUSAL, bool SMALL>
 __global__ void __launch_bounds__(256, (kDqWgsPerCu<D>))
-dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
               const __bf16* __restrict__ dO, const __bf16* __restrict__ O, const float* __restrict__ LSE,
               float2* __restrict__ stats, __bf16* __restrict__ dQ, const int32_t* __restrict__ hdr,
               const WorkItem* __restrict__ items, int max_items, int T, int Hq, int Hkv, float scale, DqSmall small,
@@ -1203,11 +889,11 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
         if (j < nsteps) {
             const uint32_t st = lds0 + (j & 1) * STAGE;
             if (ragged_sample && j == last_step) {
-                dma.issue_tile(kbase + (size_t)j * step_bytes, true, st, w);
-                dma.issue_tile(vbase + (size_t)j * step_bytes, true, st + C::TILE, w);
+                dma.issue_tile(kbase + (size_t)j * step_bytes, true, st, w, false);
+                dma.issue_tile(vbase + (size_t)j * step_bytes, true, st + C::TILE, w, true);
             } else {
-                dma.issue_tile(kbase + (size_t)j * step_bytes, false, st, w);
-                dma.issue_tile(vbase + (size_t)j * step_bytes, false, st + C::TILE, w);
+                dma.issue_tile(kbase + (size_t)j * step_bytes, false, st, w, false);
+                dma.issue_tile(vbase + (size_t)j * step_bytes, false, st + C::TILE, w, true);
             }
         }
     };
@@ -1231,7 +917,8 @@ dq_kernel_direct(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
             qf[ks] = qvalid ? *(const bf16x8*)(Q + off + 16 * ks) : z;
             dof[ks] = qvalid ? *(const bf16x8*)(dO + off + 16 * ks) : z;
         }
-        // row statistics of this lane's row, as in dq_kernel (same order of operations)
+        // Row statistics of this lane's row: Delta = sum_d dO * O (each half of the wave sums its 8 of
+        // every 16 columns), and the saved LSE in base 2.  Written out for the dK/dV kernel.
         float part = 0.f;
 #pragma unroll
         for (int ks = 0; ks < C::KS; ++ks) {
@@ -1334,16 +1021,14 @@ static hipError_t launch_dq_dc(const BwdArgs& a, hipStream_t stream) {
                      sched_job(BWD_TILE_Q, BWD_STEP_KV, CAUSAL ? COST_CAUSAL_QUERY : COST_FULL, a.ws_q, a.lay_q)};
     }
     dim3 grid((unsigned)(a.max_items_q * a.num_q_heads * a.plan_q.max_chunks + (a.small ? 2 : 0))), block(256);
-#define VA_DQ_LAUNCH(KERNEL, SMALL)                                                                                      \
-    hipLaunchKernelGGL((KERNEL<D, CAUSAL, SMALL>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st, (__bf16*)a.dq,     \
-                       a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens, a.num_q_heads, a.num_kv_heads,      \
-                       a.scale, sm, a.clock_probe_dq)
-    if constexpr (D != 80) {  // (head_dim 80 keeps the phased dq_kernel: see dq_kernel_direct)
-        if (a.small) VA_DQ_LAUNCH(dq_kernel_direct, true); else VA_DQ_LAUNCH(dq_kernel_direct, false);
-    } else {
-        if (a.small) VA_DQ_LAUNCH(dq_kernel, true); else VA_DQ_LAUNCH(dq_kernel, false);
-    }
-#undef VA_DQ_LAUNCH
+    if (a.small)
+        hipLaunchKernelGGL((dq_kernel<D, CAUSAL, true>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st, (__bf16*)a.dq,
+                           a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens, a.num_q_heads, a.num_kv_heads,
+                           a.scale, sm, a.clock_probe_dq);
+    else
+        hipLaunchKernelGGL((dq_kernel<D, CAUSAL, false>), grid, block, 0, stream, q, k, v, dO, o, a.lse, st, (__bf16*)a.dq,
+                           a.sched_hdr_q, a.items_q, (int)a.max_items_q, a.total_tokens, a.num_q_heads, a.num_kv_heads,
+                           a.scale, sm, a.clock_probe_dq);
     return hipGetLastError();
 }
 template <int D>
@@ -1352,7 +1037,15 @@ static hipError_t launch_dq_d(const BwdArgs& a, hipStream_t stream) {
 }
 
 #if VA_BWD_PART == 2
-hipError_t launch_dq_128(const BwdArgs& a, hipStream_t stream) { return launch_dq_d<128>(a, stream); }
+hipError_t launch_bwd_dq(const BwdArgs& a, hipStream_t stream) {
+    switch (a.head_dim) {
+        case 64: return launch_dq_d<64>(a, stream);
+        case 80: return launch_dq_d<80>(a, stream);
+        case 96: return launch_dq_d<96>(a, stream);
+        case 128: return launch_dq_d<128>(a, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
 #elif VA_BWD_PART == 0
 int bwd_dq_slots(int head_dim) { return 256 * (head_dim == 64 ? kDqWgsPerCu<64> : kDqWgsPerCu<128>); }
 
@@ -1425,16 +1118,6 @@ hipError_t launch_bwd_sum_small(const BwdArgs& a, hipStream_t stream) {
         case 80: return launch_sum_d<80>(a, stream);
         case 96: return launch_sum_d<96>(a, stream);
         case 128: return launch_sum_d<128>(a, stream);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_bwd_dq(const BwdArgs& a, hipStream_t stream) {
-    switch (a.head_dim) {
-        case 64: return launch_dq_d<64>(a, stream);
-        case 80: return launch_dq_d<80>(a, stream);
-        case 96: return launch_dq_d<96>(a, stream);
-        case 128: return launch_dq_128(a, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -67,8 +67,8 @@ __device__ __forceinline__ int tr_lane_offset(int lane, int stride) {
 // of row r lives in slot c ^ swz(r).  swz is chosen so that (a) 16 consecutive rows read at one
 // logical chunk (MFMA A operand read along the row) and (b) 4 consecutive rows read over one
 // 64-byte span (transposing read down the columns) both cover all 64 banks exactly once.
-// Rows are 128 bytes for head_dim 64 and 256 bytes for 96 (4 slots unused) and 128; head_dim 80 has a
-// packed layout of its own (LdsTile<80>).
+// Rows are 128 bytes for head_dim 64 and 256 bytes for 128; head_dim 80 and 96 have a packed layout of
+// their own (PackedLdsTile).
 // ------------------------------------------------------------------------------------------------
 #define VA_GLOBAL __attribute__((address_space(1)))
 
@@ -76,7 +76,7 @@ template <int D>
 struct LdsTile {
     static constexpr int ROWB = D <= 64 ? 128 : 256;  // bytes per row
     static constexpr int SLOTS = ROWB / 16;
-    static constexpr int CHUNKS = D / 8;              // slots that hold data
+    static constexpr int CHUNKS = SLOTS;
     static constexpr int BLOCK_POS = 16 * SLOTS;      // 16-byte positions in a block of 16 rows
     __host__ __device__ __forceinline__ static constexpr int swz(int r) {
         if (ROWB == 256) return ((r & 3) << 2) | ((r >> 2) & 3);
@@ -91,36 +91,38 @@ struct LdsTile {
         const int c = 4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
         return off(r, c) + 8 * (lane & 1);
     }
-    // Which (row of the block, logical chunk) lives at 16-byte position p of a 16-row block; false
-    // for a position that holds no data.  The inverse of off(), used to aim the direct-to-LDS loads.
+    // Which (row of the block, logical chunk) lives at 16-byte position p of a 16-row block (true: every position
+    // holds data).  The inverse of off(), used to aim the direct-to-LDS loads.
     __host__ __device__ __forceinline__ static constexpr bool locate(int p, int& r, int& c) {
         r = p / SLOTS;
         c = (p % SLOTS) ^ swz(r);
-        return CHUNKS == SLOTS || c < CHUNKS;
+        return true;
     }
 };
 
-// head_dim 80: 160-byte rows, stored without padding (a 64-row tile takes 10 KB instead of 16 KB, which
-// is what lets three forward and two backward workgroups share a CU).  Ten chunks per row rule out an
-// XOR swizzle, so each block of 16 rows (2560 bytes = 10 segments of 256 bytes = 16 positions) is laid
-// out by hand.  With a = r / 4 and b = r % 4 inside the block, chunk c of row r sits in
-//     segment 2a + c/4  (c < 8)   or   segment c  (c = 8, 9),     position 4b + (c + a) % 4.
+// head_dim 80 and 96: rows of 160 and 192 bytes, stored without padding: a 64-row tile takes 10 or 12 KB instead of 16 KB
+// (more workgroups per CU), and every lane of the loads that fill it has data to fetch (10 or 12 loads instead of 16).
+// Such a row rules out an XOR swizzle, so each block of 16 rows (10 or 12 segments of 256 bytes = 16 positions) is laid out
+// by hand.  With a = r / 4 and b = r % 4 inside the block, chunk c of row r sits in
+//     segment FULL * a + c/4  (c < 4 * FULL)   or   segment c  (the two chunks 8 and 9 that head_dim 80 has beyond its two
+//     groups of four),     position 4b + (c + a) % 4.
 // (a) For one c the 16 rows occupy 16 different positions, so a row-wise 16-byte read of 16 rows covers
 // all 64 banks once.  (b) For one a (4 rows) and one group of 4 chunks the 16 (row, chunk) pairs do too,
-// which is the footprint of half a transposing read.  (c) Chunks 0-3 and 4-7 of a row are adjacent in
+// which is the footprint of half a transposing read.  (c) The four chunks of a group of a row are adjacent in
 // LDS (rotated), so four lanes of a load still fetch 64 contiguous bytes from memory.
-template <>
-struct LdsTile<80> {
-    static constexpr int ROWB = 160;  // nominal: a block of 16 rows is 16 * ROWB bytes
-    static constexpr int CHUNKS = 10;
-    static constexpr int BLOCK_POS = 160;
+template <int D>
+struct PackedLdsTile {
+    static constexpr int ROWB = 2 * D;  // nominal: a block of 16 rows is 16 * ROWB bytes
+    static constexpr int CHUNKS = D / 8;
+    static constexpr int FULL = CHUNKS / 4;  // groups of four chunks
+    static constexpr int BLOCK_POS = 16 * CHUNKS;
     __host__ __device__ __forceinline__ static constexpr int pos(int r, int c) {  // r in [0, 16)
         const int a = r >> 2, b = r & 3;
-        const int seg = c < 8 ? 2 * a + (c >> 2) : c;
+        const int seg = c < 4 * FULL ? FULL * a + (c >> 2) : c;
         return 16 * seg + 4 * b + ((c + a) & 3);
     }
     __host__ __device__ __forceinline__ static constexpr int off(int r, int c) { return (r >> 4) * (16 * ROWB) + 16 * pos(r & 15, c); }
-    // Columns 80..95 of the third 32-column block do not exist: the lanes that would address them
+    // Columns 80..95 of head_dim 80's third 32-column block do not exist: the lanes that would address them
     // re-read chunks 8 and 9 (same addresses as their partner lanes; the results are never used).
     __host__ __device__ __forceinline__ static int tr_off(int lane, int row0, int db) {
         const int r = row0 + 4 * (lane >> 5) + ((lane & 15) >> 2);
@@ -131,12 +133,14 @@ struct LdsTile<80> {
     __host__ __device__ __forceinline__ static constexpr bool locate(int p, int& r, int& c) {
         const int seg = p >> 4, b = (p >> 2) & 3, e = p & 3;
         int a = 0;
-        if (seg < 8) { a = seg >> 1; c = 4 * (seg & 1) + ((e - a) & 3); }
+        if (seg < 4 * FULL) { a = seg / FULL; c = 4 * (seg % FULL) + ((e - a) & 3); }
         else { c = seg; a = (e - c) & 3; }
         r = 4 * a + b;
         return true;
     }
 };
+template <> struct LdsTile<80> : PackedLdsTile<80> {};
+template <> struct LdsTile<96> : PackedLdsTile<96> {};
 
 // One direct-to-LDS load: every active lane fetches 16 bytes from base + its own byte offset; lane
 // i's data lands at lds_addr + 16 * i (lds_addr is a wave-uniform LDS byte address and goes through
@@ -157,19 +161,6 @@ __device__ __forceinline__ uint64_t uniform_u64(const void* p) {
 __device__ __forceinline__ void dma16(const void* base, uint32_t byte_off, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
                  : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(byte_off), "s"(uniform_u64(base)) : "memory", "m0");
-}
-// The same load for the lanes named in `lanes` only (a wave-uniform bit mask).  The execution mask is
-// narrowed inside the assembly statement and put back behind the load, so that the compiler sees no
-// branch: an `if (lane is active)` around the load costs a saved-exec branch per load and, worse, cuts
-// the loop body into basic blocks across which nothing is scheduled.  Must be reached by all 64 lanes.
-__device__ __forceinline__ void dma16_lanes(const void* base, uint32_t byte_off, uint32_t lds_addr, uint64_t lanes) {
-    uint64_t saved;
-    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %1\n\t"
-                 "global_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
-                 : "=&s"(saved)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(byte_off), "s"(uniform_u64(base)),
-                   "s"(lanes)
-                 : "memory", "m0");
 }
 // Same with 4 bytes per lane: lane i's dword lands at lds_addr + 4 * i.
 __device__ __forceinline__ void dma4(const void* base, uint32_t byte_off, uint32_t lds_addr) {
@@ -303,105 +294,63 @@ __host__ __device__ __forceinline__ int short_rotated_head(int hp, int item, int
 __device__ __forceinline__ int uniform_wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // Per-lane source offsets of the direct-to-LDS loads that fill one LdsTile of ROWS rows of a
-// [rows, heads, D] tensor, split over the 4 waves of the workgroup.  The offsets are relative to
+// [rows, heads, D] tensor, split over the NW waves of the workgroup.  The offsets are relative to
 // the tile's first row; they are computed once per kernel, so that issuing a tile costs no vector
 // ALU work.  `last` holds the offsets for the sample's ragged last tile, where rows past the sample
 // end re-read its last row (finite data that the caller masks).
-// MASK_BY_BRANCH: partly active loads sit behind an `if (lane active)` instead of narrowing the execution
-// mask in assembly.  The branch cuts the caller's loop body into blocks; one kernel (dQ at head_dim 80,
-// at its register limit) is faster that way because the compiler then hoists less across the loads.
-template <int D, int ROWS, bool MASK_BY_BRANCH = false>
+// A tile is PIECES loads of 64 x 16 contiguous LDS bytes, whatever rows those hold.  Every wave takes NI of them; two
+// may be left (10 pieces at head_dim 80 over 4 waves).  Tiles come in pairs (K and V, Q and dO) of one shape: the left
+// pieces of the first tensor go to waves 0 and 1, those of the second to waves 2 and 3, so that every wave issues
+// 2 NI + EXTRA loads for the pair.  (A load costs the SIMD about 26 cycles of issue however many of its lanes fetch
+// something.  One block of 16 rows per wave took six loads for the pair instead of five at head_dim 80, the third of each
+// half empty, and at 96, in rows padded to 256 bytes, eight instead of six.  64 ViT samples, 16 heads of 96: forward 4548 ->
+// 4238 us, dQ 6215 -> 5858, dK/dV 10129 -> 9725; at head_dim 80, 256 samples of 64..1024 tokens, dQ 632 -> 615, the others 0.6 %.)
+template <int D, int ROWS, int NW = 4>
 struct TileDma {
     using T = LdsTile<D>;
-    // 64-row tiles: one block of 16 rows per wave.  32-row tiles (head_dim 128 forward): 8 rows per wave, for the
-    // layouts whose rows hold data in every slot.
-    static_assert(ROWS == 64 || (ROWS == 32 && (D == 64 || D == 128)), "tile shape");
-    static constexpr int RPW = ROWS / 4;                                            // rows per wave
-    static constexpr int WAVE_POS = ROWS == 64 ? T::BLOCK_POS : RPW * (T::ROWB / 16);  // 16-byte positions per wave
-    static constexpr int NI = (WAVE_POS + 63) / 64;      // load instructions per wave per tile
-    static constexpr int WAVE_BYTES = RPW * T::ROWB;     // LDS bytes of one wave's rows
-    uint32_t full[NI], last[NI];
-    // lanes of load instruction i that hold data (a compile-time constant of the layout)
-    __device__ __forceinline__ static constexpr uint64_t lane_mask(int i) {
-        uint64_t m = 0;
-        for (int lane = 0; lane < 64; ++lane) {
-            const int p = 64 * i + lane;
-            int r = 0, c = 0;
-            if (ROWS == 32 ? p < WAVE_POS : (p < T::BLOCK_POS && T::locate(p, r, c))) m |= 1ull << lane;
-        }
-        return m;
-    }
-    struct LaneMasks { uint64_t m[NI]; };
-    __device__ __forceinline__ static constexpr LaneMasks lane_masks() {
-        LaneMasks k{};
-        for (int i = 0; i < NI; ++i) k.m[i] = lane_mask(i);
-        return k;
-    }
-    // load instruction i (known after unrolling) of a tile
-    __device__ __forceinline__ static void load(int i, const unsigned char* src, uint32_t off, uint32_t lds_addr) {
-        constexpr LaneMasks k = lane_masks();
-        const uint64_t m = k.m[i];
-        if (m == ~0ull) dma16(src, off, lds_addr);
-        else if (!MASK_BY_BRANCH) dma16_lanes(src, off, lds_addr, m);
-        else if ((m >> (threadIdx.x & 63)) & 1) dma16(src, off, lds_addr);
-    }
+    static constexpr int PIECES = ROWS / 16 * T::BLOCK_POS / 64;
+    static constexpr int NI = PIECES / NW;                     // loads per wave per tile, without
+    static constexpr int EXTRA = PIECES % NW ? 1 : 0;          // the one per pair of tiles
+    static_assert(ROWS % 16 == 0 && ROWS / 16 * T::BLOCK_POS % 64 == 0 && (PIECES % NW == 0 || PIECES % NW == 2) && NW >= 4,
+                  "pieces of a tile");
+    uint32_t full[NI + EXTRA], last[NI + EXTRA];
+    // Piece that load i of a wave fills (i == NI: the extra one).
+    __device__ __forceinline__ static int piece(int wave, int i) { return i < NI ? wave * NI + i : NW * NI + (wave & 1); }
     // row_bytes: bytes between consecutive rows of the tensor; L: rows in the sample
     __device__ __forceinline__ void init(uint32_t row_bytes, int L, int wave, int lane) {
         const int last_r0 = (L - 1) / ROWS * ROWS;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int p = 64 * i + lane;  // position inside this wave's block
+        for (int i = 0; i < NI + EXTRA; ++i) {
+            const int p = 64 * piece(wave, i) + lane;  // 16-byte position inside the tile
             int r = 0, c = 0;
-            if constexpr (ROWS == 64) {
-                T::locate(p < T::BLOCK_POS ? p : 0, r, c);  // (a lane without data gets some valid offset; it never loads)
-            } else {  // 8 rows per wave: the swizzle goes by the row inside the tile
-                constexpr int SLOTS = T::ROWB / 16;
-                r = (p < WAVE_POS ? p : 0) / SLOTS;
-                c = ((p < WAVE_POS ? p : 0) % SLOTS) ^ T::swz(RPW * wave + r);
-            }
-            const int row = RPW * wave + r;
+            T::locate(p % T::BLOCK_POS, r, c);
+            const int row = p / T::BLOCK_POS * 16 + r;
             full[i] = (uint32_t)row * row_bytes + c * 16;
             last[i] = (uint32_t)min(row, L - 1 - last_r0) * row_bytes + c * 16;
         }
     }
-    // LDS byte address of load instruction i of `wave` in the tile at `tile`
-    __device__ __forceinline__ static uint32_t dest(uint32_t tile, int wave, int i) {
-        return tile + wave * WAVE_BYTES + i * 1024;
-    }
-    // base: first byte of the sample's row 0 at this head; r0: first row of the tile; tile: LDS byte
-    // address of the tile; wave: uniform_wave_id()
-    __device__ __forceinline__ void issue(const unsigned char* base, uint32_t row_bytes, int r0, int L,
-                                          uint32_t tile, int wave) const {
-        const unsigned char* src = base + (size_t)r0 * row_bytes;
-        const bool ragged = r0 + ROWS > L;  // wave-uniform
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const uint32_t off = ragged ? last[i] : full[i];
-            load(i, src, off, dest(tile, wave, i));
-        }
-    }
-    // All loads of a tile whose first row's bytes at this head start at src.
-    __device__ __forceinline__ void issue_tile(const unsigned char* src, bool ragged, uint32_t tile, int wave) const {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const uint32_t off = ragged ? last[i] : full[i];
-            load(i, src, off, dest(tile, wave, i));
-        }
-    }
-    // Load instruction i of a tile, i known after unrolling (same as issue_one<i>).
-    __device__ __forceinline__ void issue_one_rt(int i, const unsigned char* src, bool ragged, uint32_t tile, int wave) const {
+    // Load i of a tile (known after unrolling): src = first byte of the tile's first row at this head, tile = LDS byte
+    // address of the tile, wave = uniform_wave_id().  Lets a caller spread a tile's loads over its compute phases: a wave
+    // that issues them back to back right after a barrier queues up behind every other wave doing the same and sits in the
+    // issue stage for hundreds of cycles.
+    __device__ __forceinline__ void issue_one(int i, const unsigned char* src, bool ragged, uint32_t tile, int wave) const {
         const uint32_t off = ragged ? last[i] : full[i];
-        load(i, src, off, dest(tile, wave, i));
+        dma16(src, off, tile + piece(wave, i) * 1024);
     }
-    // One of the NI load instructions of a tile: src = first byte of the tile's first row at this
-    // head.  Lets a caller spread a tile's loads over its compute phases: a wave that issues them
-    // back to back right after a barrier queues up behind every other wave doing the same and sits
-    // in the issue stage for hundreds of cycles.
-    template <int I>
-    __device__ __forceinline__ void issue_one(const unsigned char* src, bool ragged, uint32_t tile, int wave) const {
-        static_assert(I >= 0 && I < NI, "no such load");
-        const uint32_t off = ragged ? last[I] : full[I];
-        load(I, src, off, dest(tile, wave, I));
+    // Whether this wave's extra load belongs to the second tensor of a pair.
+    __device__ __forceinline__ static bool extra_is_second(int wave) { return wave >= 2; }
+    // All of this wave's loads of one tile of the first or second tensor.
+    __device__ __forceinline__ void issue_tile(const unsigned char* src, bool ragged, uint32_t tile, int wave, bool second) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) issue_one(i, src, ragged, tile, wave);
+        if (EXTRA && extra_is_second(wave) == second) issue_one(NI, src, ragged, tile, wave);
+    }
+    // The extra load of a pair of tiles, without a branch.
+    __device__ __forceinline__ void issue_extra(const unsigned char* first, const unsigned char* second, bool first_ragged,
+                                                bool second_ragged, uint32_t first_tile, uint32_t second_tile, int wave) const {
+        static_assert(NW == 4 || !EXTRA, "every wave has one");
+        const bool s = extra_is_second(wave);
+        if (EXTRA) issue_one(NI, s ? second : first, s ? second_ragged : first_ragged, s ? second_tile : first_tile, wave);
     }
 };
 
@@ -422,23 +371,6 @@ __device__ __forceinline__ void wg_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// Asks the instruction scheduler to lay out the current straight-line region as N_MFMA rounds of
-// {2 LDS reads, 1 MFMA, 5 vector-ALU instructions}.  Used where a region holds matrix work and
-// vector work that do not depend on each other (software-pipelined loops): left alone the
-// scheduler emits them as two blocks and the wave leaves one pipe idle at a time.
-template <int N_MFMA, int DS_AHEAD = 10, int DS_PER = 2, int VALU_PER = 5>
-__device__ __forceinline__ void interleave_mfma_valu() {
-    // LDS reads run DS_AHEAD instructions ahead of the MFMAs that consume them: an LDS read takes a
-    // few hundred cycles to return, an MFMA issues every 32
-    __builtin_amdgcn_sched_group_barrier(0x100, DS_AHEAD, 0);
-#pragma unroll
-    for (int i = 0; i < N_MFMA; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, DS_PER, 0);    // DS read
-        __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER, 0);  // VALU
-    }
-}
-
 // Moves a loop-invariant MFMA operand into the accumulation half of the register file.  A kernel that
 // runs one wave per SIMD has 512 registers, but the vector ALU only reaches the 256 "architectural"
 // ones; when those run short the compiler parks MFMA RESULTS in the other half and pays one copy
@@ -446,11 +378,6 @@ __device__ __forceinline__ void interleave_mfma_valu() {
 // matrix instructions read their A/B operands from either half, so operands that only they touch
 // are the right thing to keep there.
 __device__ __forceinline__ void park_in_acc_registers(bf16x8& x) { asm volatile("" : "+a"(x)); }
-
-// Forces x to be computed by this point of the program: without it the compiler sinks a value's
-// whole computation into the later block that first uses it, i.e. out of the pipeline slot that was
-// meant to overlap it with matrix work.
-__device__ __forceinline__ void pin_here(bf16x8& x) { asm volatile("" : "+v"(x)); }
 
 __device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3, float a4, float a5, float a6, float a7) {
     bf16x8 r;

@@ -28,6 +28,7 @@ struct FwdCfg {
     static constexpr int DB = (D + 31) / 32;           // 32-wide blocks of O^T rows
     static constexpr int TILE = BKV * T::ROWB;         // bytes of one K or V tile in LDS
     static constexpr int NI = TileDma<D, BKV>::NI;     // load instructions per wave per tile
+    static constexpr int EXTRA = TileDma<D, BKV>::EXTRA;  // and per pair of K and V tiles
 };
 
 // The running maximum m is only a reference point for the exponentials; it is moved (and O, l
@@ -373,7 +374,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     const int last_tile = (L + C::BKV - 1) / C::BKV - 1;  // the tile holding the sample's end
     auto tile_ptr = [&](const unsigned char* base, int j) { return base + (size_t)min(j, je - 1) * tile_bytes; };
     auto load_tile = [&](const unsigned char* base, int j, uint32_t lds_tile) {
-        dma.issue_tile(tile_ptr(base, j), ragged_sample && min(j, je - 1) == last_tile, lds_tile, w);
+        dma.issue_tile(tile_ptr(base, j), ragged_sample && min(j, je - 1) == last_tile, lds_tile, w, base == vbase);
     };
     // per-lane LDS offsets: K rows read along the row (A operand of S^T), V read down the columns
     int kaddr[C::KS], vaddr[C::DB][2];
@@ -424,9 +425,11 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         constexpr int NI = C::NI, HALF = (NI + 1) / 2;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            if (slot == (i < HALF ? 0 : 1) && (!LEAN || do_v)) dma.issue_one_rt(i, iss_v, iss_v_ragged, iss_v_lds, w);
-            if (slot == (i < HALF ? 2 : 3) && (!LEAN || do_k)) dma.issue_one_rt(i, iss_k, iss_k_ragged, iss_k_lds, w);
+            if (slot == (i < HALF ? 0 : 1) && (!LEAN || do_v)) dma.issue_one(i, iss_v, iss_v_ragged, iss_v_lds, w);
+            if (slot == (i < HALF ? 2 : 3) && (!LEAN || do_k)) dma.issue_one(i, iss_k, iss_k_ragged, iss_k_lds, w);
         }
+        if (C::EXTRA && slot == 1 && (!LEAN || (dma.extra_is_second(w) ? do_v : do_k)))
+            dma.issue_extra(iss_k, iss_v, iss_k_ragged, iss_v_ragged, iss_k_lds, iss_v_lds, w);
     };
 #define VA_FWD_ITER_BEGIN()                                                                \
         const int kv0 = j * C::BKV;                                                            \
@@ -440,8 +443,11 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         const unsigned char* kb = kbuf + kslot * C::TILE;                                      \
         const unsigned char* vb = vbuf + vslot * C::TILE;
     // K(j+1) and V(j+1) must have landed; K(j+2), issued last, may stay in flight (LEAN: if it was issued).
+    const bool extra_k = C::EXTRA && !dma.extra_is_second(w);
 #define VA_FWD_ITER_END()                                                                  \
-        if (!LEAN || do_k) wait_vmcnt<C::NI>(); else wait_vmcnt<0>();                          \
+        if (LEAN && !do_k) wait_vmcnt<0>();                                                    \
+        else if (extra_k) wait_vmcnt<C::NI + C::EXTRA>();                                      \
+        else wait_vmcnt<C::NI>();                                                              \
         wg_barrier();                                                                          \
         kslot = kslot == 2 ? 0 : kslot + 1;                                                    \
         vslot ^= 1;
