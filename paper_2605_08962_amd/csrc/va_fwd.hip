@@ -285,6 +285,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     using C = FwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr bool LEAN = MODE != FWD_GENERAL;
+    // whole rounds of the LDS slots in the mask-free loop (see there); elsewhere the registers for it are short
+    constexpr bool UNROLL = MODE == FWD_GENERAL || (MODE == FWD_SMALL && D > 80);
     constexpr bool SKIP = !(MODE == FWD_LEAN && D == 64 && !CAUSAL);  // see tile_step
 
     // S > 1: the key tiles of every query tile are split into S consecutive chunks (FWD_SMALL: into as many as its
@@ -397,9 +399,10 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     // prologue: K(0), V(0), K(1) and this lane's Q fragments.  Everything is waited for here, once:
     // the compiler cannot see the direct-to-LDS loads, and if the Q loads were still pending in its
     // bookkeeping at loop entry it would put a wait for ALL outstanding loads into every iteration.
-    load_tile(kbase, jb, lds0);
-    load_tile(vbase, jb, lds0 + 3 * C::TILE);
-    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0 + C::TILE);
+    // (slots: the first tile, which sets the reference maximum, ends on the pair of slots that the unrolled loop starts with)
+    load_tile(kbase, jb, lds0 + 2 * C::TILE);
+    load_tile(vbase, jb, lds0 + 4 * C::TILE);
+    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0);
     bf16x8 qf[C::KS];
     {
         const __bf16* qp = Q + ((size_t)(sb + (qvalid ? qrow : 0)) * Hq + h) * D + 8 * hh;
@@ -412,8 +415,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     wait_vmcnt<0>();
     wg_barrier();
 
-    int kslot = 0;  // (j - jb) % 3
-    int vslot = 0;  // (j - jb) % 2
+    int kslot = 2;  // (j - jb + 2) % 3
+    int vslot = 1;  // (j - jb + 1) % 2
     int j = jb;
     // Iteration j first fixes what it will load (V(j+1) into the other V slot, K(j+2) into the K slot
     // of tile j-1) and then lets the tile step issue those 2 NI loads in four portions, V first.
@@ -438,7 +441,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         iss_v_ragged = ragged_sample && min(j + 1, je - 1) == last_tile;                       \
         iss_k_ragged = ragged_sample && min(j + 2, je - 1) == last_tile;                       \
         iss_v_lds = lds0 + (3 + (vslot ^ 1)) * C::TILE;                                        \
-        iss_k_lds = lds0 + (kslot == 0 ? 2 : kslot - 1) * C::TILE; /* slot (j + 2 - jb) % 3 */ \
+        iss_k_lds = lds0 + (kslot == 0 ? 2 : kslot - 1) * C::TILE; /* slot of tile j - 1 */ \
         if (LEAN) { do_v = j + 1 < je; do_k = j + 2 < je; }                                    \
         const unsigned char* kb = kbuf + kslot * C::TILE;                                      \
         const unsigned char* vb = vbuf + vslot * C::TILE;
@@ -489,9 +492,69 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         VA_FWD_ITER_END()
         ++j;
     }
-    for (; j < min(n_plain, je); ++j) {  // no masks, every wave active, maximum taken on trust
+    // No masks, every wave active, maximum taken on trust (worth 2 % at head_dim 64 and 80, where the vector ALU is the busier
+    // pipe, 1.5 % at 128).  Issue slots bound this loop, so as little as possible stands in it besides the arithmetic: while
+    // the tiles that a step loads exist and are whole (`steady`), its loads need no bounds, no branch (LEAN) and no choice
+    // between the two sets of offsets; and where UNROLL, six steps, the common period of the three K and two V slots, are
+    // written out with their slots constants, so that LDS addresses are per-lane offsets plus immediates (eight or nine
+    // vector and up to thirty scalar instructions fewer per step of about 270).  Measured, before -> steady -> unrolled, us:
+    //   64 ViT samples, 16 heads of 64 2940 -> 2920 -> 2875, of 96 4238 -> 4123 -> 4025, of 128 5206 -> 5079 -> 4936; 65536 tokens
+    //   and 256 short samples, 16 heads of 80, 22896 -> 22476 -> 22123; LLM batch, 32/8 heads of 128, 1234 -> 1201 -> 1171;
+    //   small launches: 8192 tokens, 2 heads of 64 48.5 -> 46.2, of 128 79.4 -> 78.3 -> 74.5; 4096 causal, 2 heads of 128, 27.3 ->
+    //   25.3 -> 25.2.  Of 64 and 80 these keep the steady form: unrolled they need 141 and 168 registers, two of them spilled.
+    {
+        const int steady = min(n_plain, (ragged_sample ? min(je, last_tile) : je) - 2);
+        const unsigned char *nxt_v = vbase + (size_t)(j + 1) * tile_bytes, *nxt_k = kbase + (size_t)(j + 2) * tile_bytes;
+        auto issue_whole = [&](int slot, uint32_t v_lds, uint32_t k_lds) {
+            constexpr int NI = C::NI, HALF = (NI + 1) / 2;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                if (slot == (i < HALF ? 0 : 1)) dma.issue_one(i, nxt_v, false, v_lds, w);
+                if (slot == (i < HALF ? 2 : 3)) dma.issue_one(i, nxt_k, false, k_lds, w);
+            }
+            if (C::EXTRA && slot == 1) dma.issue_extra(nxt_k, nxt_v, false, false, k_lds, v_lds, w);
+        };
+        auto end_step = [&]() {
+            nxt_v += tile_bytes; nxt_k += tile_bytes;
+            if (extra_k) wait_vmcnt<C::NI + C::EXTRA>(); else wait_vmcnt<C::NI>();
+            wg_barrier();
+            ++j;
+        };
+        // Step I of a round; false if the reference maximum has to move first (its V loads are issued then, nothing else done).
+        auto round_step = [&](auto tag) {
+            constexpr int I = decltype(tag)::value;
+            auto issue_now = [&](int slot) { issue_whole(slot, lds0 + (3 + (I + 1) % 2) * C::TILE, lds0 + (I + 2) % 3 * C::TILE); };
+            if (!tile_step_trusting<D>(kbuf + I % 3 * C::TILE, vbuf + I % 2 * C::TILE, kaddr, vaddr, qf, oacc, m, lsum, c2, issue_now)) {
+                kslot = I % 3; vslot = I % 2;
+                return false;
+            }
+            end_step();
+            return true;
+        };
+        bool move_max = false;
+        while (j < steady) {
+            if (UNROLL && kslot == 0 && vslot == 0) {
+                while (j + 6 <= steady && !move_max)
+                    move_max = !(round_step(std::integral_constant<int, 0>{}) && round_step(std::integral_constant<int, 1>{}) &&
+                                 round_step(std::integral_constant<int, 2>{}) && round_step(std::integral_constant<int, 3>{}) &&
+                                 round_step(std::integral_constant<int, 4>{}) && round_step(std::integral_constant<int, 5>{}));
+                if (j >= steady) break;
+            }
+            auto issue_now = [&](int slot) {
+                issue_whole(slot, lds0 + (3 + (vslot ^ 1)) * C::TILE, lds0 + (kslot == 0 ? 2 : kslot - 1) * C::TILE);
+            };
+            const unsigned char* kb = kbuf + kslot * C::TILE;
+            const unsigned char* vb = vbuf + vslot * C::TILE;
+            if (move_max || !tile_step_trusting<D>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, issue_now))
+                tile_step<D, CAUSAL, false, 2>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, j * C::BKV, L, qrow, hh, issue_now);
+            move_max = false;
+            end_step();
+            kslot = kslot == 2 ? 0 : kslot + 1;
+            vslot ^= 1;
+        }
+    }
+    for (; j < min(n_plain, je); ++j) {
         VA_FWD_ITER_BEGIN()
-        // (measured: worth 2 % at head_dim 64 and 80, where the vector ALU is the busier pipe, 1.5 % at 128)
         if (!tile_step_trusting<D>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, issue))
             tile_step<D, CAUSAL, false, 2>(kb, vb, kaddr, vaddr, qf, oacc, m, lsum, c2, kv0, L, qrow, hh, issue);
         VA_FWD_ITER_END()
