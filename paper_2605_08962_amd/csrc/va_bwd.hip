@@ -334,6 +334,13 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     // LDS stages: four where two workgroups per CU are out of reach anyway or still fit (head_dim 64),
     // three at head_dim 80, where the fourth would cost the second workgroup
     constexpr int NST = D == 80 ? 3 : 4;
+    // Mask-free steps whose loads stay inside the head take pointers by addition and no choice of offsets (15 scalar and 6
+    // vector instructions fewer per step; head_dim 80 spills 11 registers in the loop's second copy and goes without); at
+    // head_dim 64 whole rounds of the stages are written out besides, their LDS addresses constants (elsewhere the copies cost
+    // registers the kernel does not have; slices take a handful of steps, for which less code is better).  Measured: 64 ViT samples, 16 heads of 64 5195 -> 5144 us, of 96 8453 -> 8385; LLM
+    // batch at 96 1926 -> 1895; at 128 even.
+    constexpr bool UNROLLED = D == 64 && OB == C::DB;
+    constexpr bool STEADY = D != 80 && OB == C::DB;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
 
     constexpr unsigned SLICES = C::DB / OB;
@@ -437,9 +444,8 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     };
     // slot S of 6 per step carries loads S and S + 6
 #define VA_DKDV_ISSUE_SLOT(S)                                                                             \
-    dkdv_issue_part<D, (S)>(iss_ragged, dma, iss_q, iss_do, iss_st, iss_ragged ? stat_last : stat_full,   \
-                            iss_lds, w);                                                                  \
-    dkdv_issue_part<D, (S) + 6>(iss_ragged, dma, iss_q, iss_do, iss_st, 0, iss_lds, w);
+    dkdv_issue_part<D, (S)>(ragged, dma, iss_q, iss_do, iss_st, ragged ? stat_last : stat_full, iss_lds, w); \
+    dkdv_issue_part<D, (S) + 6>(ragged, dma, iss_q, iss_do, iss_st, 0, iss_lds, w);
     auto issue_all = [&]() {
         begin_issue();
         issue_stat();
@@ -522,8 +528,10 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     bf16x8 pb[2], dsb[2];
     // STAGE_TAG: the step's stage where the caller knows it (-1 otherwise); with it the LDS addresses of the
     // operand reads are per-lane offsets plus immediates instead of vector additions per step
-    auto phased = [&](auto stage_tag) {
+    // steady_tag: the step it loads is neither the last of its head nor of the chunk
+    auto phased = [&](auto stage_tag, auto steady_tag) {
         constexpr int KNOWN = decltype(stage_tag)::value;
+        constexpr bool STEADY = decltype(steady_tag)::value;
         VA_DKDV_SYNC()
         const int si = KNOWN >= 0 ? KNOWN : stage_i;
         const unsigned char* cur = lds + si * STAGE;
@@ -531,7 +539,14 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         // half 0 (the scalar bookkeeping of this step's loads runs behind its MFMAs)
         dkdv_load_lse<D, 0>(cur, lv, hh);
         dkdv_run_S<D>(fa, kf, s);
-        begin_issue();
+        if constexpr (STEADY) {
+            iss_q = nxt_q; iss_do = nxt_do; iss_st = nxt_st;
+            iss_lds = lds0 + (KNOWN >= 0 ? (KNOWN + NST - 1) % NST : stage_i == 0 ? NST - 1 : stage_i - 1) * STAGE;
+            nxt_q += step_q; nxt_do += step_q; nxt_st += step_st;
+        } else {
+            begin_issue();
+        }
+        const bool ragged = !STEADY && iss_ragged;
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(0)
         VA_DKDV_ISSUE_SLOT(1)
@@ -559,7 +574,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         dkdv_interleave<4 * OB, 2, 2>();                // dV, dK; next half's S/dP operand reads; dS
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(5)
-        VA_DKDV_ADVANCE()
+        if (KNOWN < 0) VA_DKDV_ADVANCE()
     };
 
     // A wave whose keys all lie beyond the sample keeps up the loads and the barriers only (see the forward kernel).
@@ -583,16 +598,23 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         if (st < plain_end) {
             dkdv_load_A<D, 0>(lds + stage_i * STAGE, aaddr, fa, dpa, hh);
             using Unknown = std::integral_constant<int, -1>;
-            if constexpr (D == 64) {  // (elsewhere the four copies of the step cost registers the kernel does not have)
-                for (; st < plain_end && stage_i != 0; ++st) phased(Unknown{});
-                for (; st + NST <= plain_end; st += NST) {  // whole rounds of the stages, each stage a constant
-                    phased(std::integral_constant<int, 0>{});
-                    phased(std::integral_constant<int, 1>{});
-                    phased(std::integral_constant<int, 2>{});
-                    phased(std::integral_constant<int, 3>{});
+            const int steady_end = STEADY ? min(plain_end, end - NST) : st, st0 = st;
+            auto rounds = [&](int until, auto steady) {  // whole rounds of the stages, each stage a constant
+                for (; st < until && stage_i != 0; ++st) phased(Unknown{}, steady);
+                for (; st + NST <= until; st += NST) {
+                    phased(std::integral_constant<int, 0>{}, steady);
+                    phased(std::integral_constant<int, 1>{}, steady);
+                    phased(std::integral_constant<int, 2>{}, steady);
+                    if constexpr (NST == 4) phased(std::integral_constant<int, 3>{}, steady);
                 }
-            }
-            for (; st < plain_end; ++st) phased(Unknown{});
+            };
+            if constexpr (UNROLLED) rounds(steady_end, std::true_type{});
+            for (; st < steady_end; ++st) phased(Unknown{}, std::true_type{});
+            nxt_s += st - st0; nxt_n += st - st0;
+            iss_stage = stage_i == 0 ? NST - 1 : stage_i - 1;
+            // (a walk too short for steady steps: short samples)
+            if constexpr (UNROLLED) if (st == st0) rounds(plain_end, std::false_type{});
+            for (; st < plain_end; ++st) phased(Unknown{}, std::false_type{});
         }
         for (; st < end; ++st) VA_DKDV_CAREFUL(st)
     }

@@ -321,10 +321,16 @@ struct TileDma {
         const int last_r0 = (L - 1) / ROWS * ROWS;
 #pragma unroll
         for (int i = 0; i < NI + EXTRA; ++i) {
-            const int p = 64 * piece(wave, i) + lane;  // 16-byte position inside the tile
-            int r = 0, c = 0;
-            T::locate(p % T::BLOCK_POS, r, c);
-            const int row = p / T::BLOCK_POS * 16 + r;
+            int r = 0, c = 0, row = 0;
+            if constexpr (EXTRA == 0 && 64 * NI % T::BLOCK_POS == 0) {  // whole blocks of 16 rows per wave
+                const int p = 64 * i + lane;
+                T::locate(p % T::BLOCK_POS, r, c);
+                row = 16 * (wave * (64 * NI / T::BLOCK_POS) + p / T::BLOCK_POS) + r;
+            } else {
+                const int p = 64 * piece(wave, i) + lane;  // 16-byte position inside the tile
+                T::locate(p % T::BLOCK_POS, r, c);
+                row = 16 * (p / T::BLOCK_POS) + r;
+            }
             full[i] = (uint32_t)row * row_bytes + c * 16;
             last[i] = (uint32_t)min(row, L - 1 - last_r0) * row_bytes + c * 16;
         }

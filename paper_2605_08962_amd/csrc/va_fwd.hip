@@ -285,7 +285,9 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     using C = FwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr bool LEAN = MODE != FWD_GENERAL;
-    // whole rounds of the LDS slots in the mask-free loop (see there); elsewhere the registers for it are short
+    // the mask-free loop's forms (see there): short samples at head_dim 64 do better with less code, and whole rounds of the
+    // LDS slots take registers that not every form has
+    constexpr bool STEADY = !(MODE == FWD_LEAN && D == 64);
     constexpr bool UNROLL = MODE == FWD_GENERAL || (MODE == FWD_SMALL && D > 80);
     constexpr bool SKIP = !(MODE == FWD_LEAN && D == 64 && !CAUSAL);  // see tile_step
 
@@ -503,7 +505,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     //   small launches: 8192 tokens, 2 heads of 64 48.5 -> 46.2, of 128 79.4 -> 78.3 -> 74.5; 4096 causal, 2 heads of 128, 27.3 ->
     //   25.3 -> 25.2.  Of 64 and 80 these keep the steady form: unrolled they need 141 and 168 registers, two of them spilled.
     {
-        const int steady = min(n_plain, (ragged_sample ? min(je, last_tile) : je) - 2);
+        const int steady = STEADY ? min(n_plain, (ragged_sample ? min(je, last_tile) : je) - 2) : 0;
         const unsigned char *nxt_v = vbase + (size_t)(j + 1) * tile_bytes, *nxt_k = kbase + (size_t)(j + 2) * tile_bytes;
         auto issue_whole = [&](int slot, uint32_t v_lds, uint32_t k_lds) {
             constexpr int NI = C::NI, HALF = (NI + 1) / 2;
