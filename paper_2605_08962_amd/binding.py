@@ -1,17 +1,22 @@
 """Python binding of libvarlen_attn.so: argument marshalling only.
 
+Forward and backward are marshalled in native code (csrc/va_host.cpp) where nothing is unusual about the call, else here.
 Every step of the attention path runs in the library's HIP kernels.  PyTorch is used for device
 memory (outputs, workspace) and for the current stream handle, nothing else.  There is no CPU or
 eager fallback: if the library is missing or a call fails, this raises.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libvarlen_attn.so")
+HOST_PATH = os.path.join(_HERE, "_varlen_attn_host.so")
 _lib = None
+_host = None
 
 VA_OK = 0
 VA_ERR_BAD_CU_SEQLENS = 8
@@ -75,6 +80,23 @@ def load():
     return lib
 
 
+def _load_host():
+    """The native half of this module, told where the library's entry points are."""
+    global _host
+    if _host is None:
+        lib = load()
+        if not os.path.exists(HOST_PATH):
+            from . import build as _build
+            _build.build_host()
+        loader = importlib.machinery.ExtensionFileLoader("_varlen_attn_host", HOST_PATH)
+        host = importlib.util.module_from_spec(importlib.util.spec_from_loader("_varlen_attn_host", loader))
+        loader.exec_module(host)
+        host.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.varlen_attn_fwd_workspace_bytes, lib.varlen_attn_bwd_workspace_bytes, lib.varlen_attn_fwd, lib.varlen_attn_bwd)))
+        _host = host
+    return _host
+
+
 def status_string(status):
     return load().varlen_attn_status_string(int(status)).decode()
 
@@ -125,6 +147,12 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=No
     """O bf16 [T,Hq,D] and LSE fp32 [Hq,T] of packed attention; asynchronous on the stream.
     kv_splits: 0 automatic, 1 never, 2..8 workgroups sharing the keys of each query tile.
     max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint)."""
+    done = (_host or _load_host()).fwd(q, k, v, cu_seqlens, bool(causal), float(softmax_scale), out, lse, workspace,
+                                       None if stream is None else stream.cuda_stream, int(kv_splits), int(max_seqlen))
+    if type(done) is tuple:
+        return done
+    if done is not NotImplemented:
+        _check(done)
     lib = load()
     for t, n in ((q, "q"), (k, "k"), (v, "v")):
         _require(t, torch.bfloat16, n)
@@ -136,9 +164,8 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=No
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device)
-    need = fwd_workspace_bytes(p)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(fwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
     _check(lib.varlen_attn_fwd(ctypes.byref(p), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                cu_seqlens.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                workspace.data_ptr(), workspace.numel(), _stream_handle(stream)))
@@ -175,6 +202,13 @@ def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, 
     max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint; above 1024 a launch too small
     to fill the GPU may cut its tiles into chunks, so that a sample's gradients depend, to rounding, on the launch).
     kv_splits: 1 never does, 0 automatic."""
+    done = (_host or _load_host()).bwd(dout, q, k, v, out, lse, cu_seqlens, bool(causal), float(softmax_scale), dq, dk, dv,
+                                       workspace, None if stream is None else stream.cuda_stream, int(kv_splits),
+                                       int(max_seqlen))
+    if type(done) is tuple:
+        return done
+    if done is not NotImplemented:
+        _check(done)
     lib = load()
     for t, n in ((dout, "dout"), (q, "q"), (k, "k"), (v, "v"), (out, "out")):
         _require(t, torch.bfloat16, n)
@@ -186,9 +220,8 @@ def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, 
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
-    need = bwd_workspace_bytes(p)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(bwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
     _check(lib.varlen_attn_bwd(ctypes.byref(p), dout.data_ptr(), q.data_ptr(), k.data_ptr(),
                                v.data_ptr(), out.data_ptr(), lse.data_ptr(), cu_seqlens.data_ptr(),
                                dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), workspace.data_ptr(),

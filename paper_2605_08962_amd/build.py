@@ -1,12 +1,15 @@
-"""Builds libvarlen_attn.so from csrc/ with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Builds libvarlen_attn.so from csrc/ with hipcc for gfx950 (cross-compiles without a GPU), and the native half of the Python
+binding with g++ against torch."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvarlen_attn.so")
+HOST = os.path.join(HERE, "_varlen_attn_host.so")
 # (source, object name, extra flags).  va_bwd.hip is built in parts, each under the instruction-scheduling strategy that
 # measured best for its kernels among the default, iterative-ilp, iterative-minreg, iterative-maxocc, max-ilp and
 # max-memory-clause (64 ViT samples, 16 heads, unless said otherwise; the forward does best with the default):
@@ -50,10 +53,28 @@ def _compile(item):
     return obj
 
 
+def build_host():
+    """_varlen_attn_host.so; returns its path."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+           sysconfig.get_paths()["include"]]
+    # (under its own name only when whole: another process may be loading the old one)
+    tmp = f"{HOST}.{os.getpid()}"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in inc),
+                    os.path.join(CSRC, "va_host.cpp"), "-o", tmp, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip",
+                    "-ltorch_cpu", "-ltorch_python"], check=True)
+    os.replace(tmp, HOST)
+    return HOST
+
+
 def build():
     os.makedirs(os.path.join(CSRC, "_build"), exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        host = ex.submit(build_host)
         objs = list(ex.map(_compile, SOURCES))
+        host.result()
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     return LIB
 
