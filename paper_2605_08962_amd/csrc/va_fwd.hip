@@ -398,13 +398,14 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     float m = kMaskedScore, lsum = 0.f;
     const float c2 = scale * kLog2e;
 
-    // prologue: K(0), V(0), K(1) and this lane's Q fragments.  Everything is waited for here, once:
+    // Prologue: K(0), V(0) and this lane's Q fragments.  Everything is waited for here, once:
     // the compiler cannot see the direct-to-LDS loads, and if the Q loads were still pending in its
-    // bookkeeping at loop entry it would put a wait for ALL outstanding loads into every iteration.
+    // bookkeeping at loop entry it would put a wait for ALL outstanding loads into every iteration.  K(1) follows: waited for
+    // along with the rest it made the start of every workgroup longer (64..1024-token samples, 16 heads of 96, 441 -> 433 us, of
+    // 80 384 -> 381).
     // (slots: the first tile, which sets the reference maximum, ends on the pair of slots that the unrolled loop starts with)
     load_tile(kbase, jb, lds0 + 2 * C::TILE);
     load_tile(vbase, jb, lds0 + 4 * C::TILE);
-    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0);
     bf16x8 qf[C::KS];
     {
         const __bf16* qp = Q + ((size_t)(sb + (qvalid ? qrow : 0)) * Hq + h) * D + 8 * hh;
@@ -416,6 +417,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     }
     wait_vmcnt<0>();
     wg_barrier();
+    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0);
 
     int kslot = 2;  // (j - jb + 2) % 3
     int vslot = 1;  // (j - jb + 1) % 2
