@@ -77,6 +77,9 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
     // without the causal mask every masked step carries lo parts, next to the hi parts' MFMAs; under it few
     // steps do (`lo`), in a pass of their own behind one wave-uniform branch
     constexpr bool LO_INLINE = MASKED && !CAUSAL;
+    // rows that exist and see this lane's key, counted from the lane's first: comparisons with constants (what a key beyond
+    // the sample makes of them stays in its lane and is not stored)
+    const int end_row = L - q0 - 4 * hh, first_row = kv - q0 - 4 * hh;
     // The two 32-query halves of the step are handled one after the other, so that only one half's
     // scores and dP (2 x 16 registers) are live at a time.
 #pragma unroll
@@ -114,9 +117,8 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
         for (int r = 0; r < 16; ++r) {
             float p = fast_exp2(__builtin_fmaf(s[r], c2, -lv[r]));
             if (MASKED) {
-                const int q = q0 + 32 * qb + 8 * (r / 4) + 4 * hh + (r % 4);
-                const bool ok = q < L && kv < L && (!CAUSAL || kv <= q);
-                p = ok ? p : 0.f;
+                const int c = 32 * qb + 8 * (r / 4) + (r % 4);
+                p = c < end_row && (!CAUSAL || c >= first_row) ? p : 0.f;
             }
             s[r] = p;
             dp[r] = p * dp[r];
@@ -818,6 +820,8 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
                                               const f32x16& ndelta16, int kv0, int qrow, int L, int hh, bool lo) {
     using C = BwdCfg<D>;
     constexpr int ROWB = C::T::ROWB;
+    // the last key this lane's row sees, counted from the lane's first (a row beyond the sample is not stored)
+    const int last_key = (CAUSAL ? min(L - 1, qrow) : L - 1) - kv0 - 4 * hh;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         if (MASKED && b && kv0 + 32 >= L) break;   // the sample ends in the first block: the second adds zeros
@@ -839,11 +843,7 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             float p = fast_exp2(__builtin_fmaf(s[r], c2, -lse2));
-            if (MASKED) {
-                const int kv = kv0 + 32 * b + 8 * (r / 4) + 4 * hh + (r % 4);
-                const bool ok = kv < L && qrow < L && (!CAUSAL || kv <= qrow);
-                p = ok ? p : 0.f;
-            }
+            if (MASKED) p = 32 * b + 8 * (r / 4) + (r % 4) <= last_key ? p : 0.f;
             dp[r] *= p;
         }
 #pragma unroll

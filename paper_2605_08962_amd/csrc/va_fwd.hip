@@ -80,13 +80,14 @@ __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigne
         if (FIRST_SLOT <= b) issue(b);
     }
     if (NB == 1 && FIRST_SLOT <= 1) issue(1);
+    // the last key this lane's row sees, counted from the lane's first: one comparison with a constant per score
+    const int last_key = (CAUSAL ? min(L - 1, qrow) : L - 1) - kv0 - 4 * hh;
     bool ok[NB][16];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            int kv = kv0 + 32 * b + 8 * (r / 4) + 4 * hh + (r % 4);
-            ok[b][r] = !BOUNDARY || (kv < L && (!CAUSAL || kv <= qrow));
+            ok[b][r] = !BOUNDARY || 32 * b + 8 * (r / 4) + (r % 4) <= last_key;
             if (!ok[b][r]) s[b][r] = kMaskedScore;
         }
     float mx = s[0][0];
