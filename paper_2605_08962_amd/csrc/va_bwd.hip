@@ -54,7 +54,7 @@ __device__ __forceinline__ bf16x8 pack_regs(const f32x16& x, int st) {
 __device__ __forceinline__ bf16x8 pack_regs_lo(const f32x16& x, int st, bf16x8 hi) {
     bf16x8 r;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = (__bf16)(x[8 * st + e] - (float)hi[e]);
+    for (int e = 0; e < 8; ++e) r[e] = (__bf16)(x[8 * st + e] - bf16_as_float(hi, e));
     return r;
 }
 
@@ -123,10 +123,11 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
             s[r] = p;
             dp[r] = p * dp[r];
         }
+        bf16x8 pk[2], dsk[2];
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            const bf16x8 pb = pack_regs(s, st);
-            const bf16x8 dsb = pack_regs(dp, st);
+            const bf16x8 pb = pk[st] = pack_regs(s, st);
+            const bf16x8 dsb = dsk[st] = pack_regs(dp, st);
             bf16x8 pl, dsl;
             if (LO_INLINE) { pl = pack_regs_lo(s, st, pb); dsl = pack_regs_lo(dp, st, dsb); }
             const int rowoff = (32 * qb + 16 * st) * ROWB;
@@ -143,8 +144,8 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
         if (MASKED && CAUSAL && lo) {
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
-                const bf16x8 pl = pack_regs_lo(s, st, pack_regs(s, st));
-                const bf16x8 dsl = pack_regs_lo(dp, st, pack_regs(dp, st));
+                const bf16x8 pl = pack_regs_lo(s, st, pk[st]);
+                const bf16x8 dsl = pack_regs_lo(dp, st, dsk[st]);
                 const int rowoff = (32 * qb + 16 * st) * ROWB;
 #pragma unroll
                 for (int db = 0; db < OB; ++db) {
