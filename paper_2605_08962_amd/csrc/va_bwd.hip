@@ -71,7 +71,7 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
                                           const int (&taddr)[OB][2],
                                           const bf16x8 (&kf)[BwdCfg<D>::KS], const bf16x8 (&vf)[BwdCfg<D>::KS],
                                           f32x16 (&dkacc)[OB], f32x16 (&dvacc)[OB],
-                                          float c2, int q0, int kv, int L, int hh, bool lo = MASKED) {
+                                          float c2, int q0, int kv, int L, int hh, bool lo, int wk_lo) {
     using C = BwdCfg<D>;
     constexpr int ROWB = C::T::ROWB;
     // without the causal mask every masked step carries lo parts, next to the hi parts' MFMAs; under it few
@@ -88,6 +88,9 @@ __device__ __forceinline__ void dkdv_step(const unsigned char* qt, const unsigne
         // 256 samples of 64..1024 tokens, 16 heads of 80, dK/dV 758 -> 736 us, dQ 628 -> 618; the ViT batch 5040 -> 5008
         // and 3710 -> 3691; the LLM batch's dK/dV 2421 -> 2381 (four runs of each in turn, apart by 3, 5 and 25 us).
         if (MASKED && qb && q0 + 32 >= L) break;
+        // Under the causal mask: no row of the first half sees a key of this wave (16 heads of 64, 64..1024 tokens, 417 -> 409 us,
+        // LLM batch 2397 -> 2374; slices, alone on their SIMDs, wait for the other waves anyway).
+        if (MASKED && CAUSAL && OB == C::DB && qb == 0 && q0 + 31 < wk_lo) continue;
         // keep the instruction scheduler from hoisting the second half's LDS reads over the first
         // half: it would hold both halves' operands in registers and spill
         // (a slice has the registers, and nothing else on its SIMD to hide one half's latencies behind)
@@ -517,7 +520,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
            step here takes the masked variant (a superset of the plain one) to keep code small */ \
         if (!CAUSAL || q0 + BWD_STEP_Q - 1 >= wk_lo)                                     \
             dkdv_step<D, CAUSAL, true, OB>(b, b + C::TILE, b + 2 * C::TILE, aaddr, taddr, kf, vf, dkacc, dvacc, \
-                                       c2, q0, kv, L, hh, lo_steps);                     \
+                                       c2, q0, kv, L, hh, lo_steps, wk_lo);              \
         VA_DKDV_SYNC()                                                                   \
         issue_all();                                                                     \
         VA_DKDV_ADVANCE()                                                                \
@@ -826,6 +829,9 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         if (MASKED && b && kv0 + 32 >= L) break;   // the sample ends in the first block: the second adds zeros
+        // Above the diagonal no row of this wave sees a key of the block, nor of the next (LLM batch 1693 -> 1662 us, 16 heads of
+        // 64, 64..1024 tokens, 313 -> 310; six causal samples of 30..200 tokens 13.8 -> 12.6).
+        if (MASKED && CAUSAL && kv0 + 32 * b > __builtin_amdgcn_readfirstlane(qrow) + 31) break;
         // The second block's operand reads stay behind the first block: mixed, dQ took 8 % longer at head_dim 128, 3 % at 64
         // (three workgroups per CU), about the same at 96.  Head_dim 80 has the registers (256 of 256): 0.6 % faster mixed on
         // 65536 tokens, 1.5 % on 64..1024.
