@@ -1,6 +1,6 @@
 """Python binding of libvarlen_attn.so: argument marshalling only.
 
-Forward and backward are marshalled in native code (csrc/va_host.cpp) where nothing is unusual about the call, else here.
+Forward, backward and merge are marshalled in native code (csrc/va_host.cpp) where nothing is unusual about the call, else here.
 Every step of the attention path runs in the library's HIP kernels.  PyTorch is used for device
 memory (outputs, workspace) and for the current stream handle, nothing else.  There is no CPU or
 eager fallback: if the library is missing or a call fails, this raises.
@@ -92,7 +92,8 @@ def _load_host():
         host = importlib.util.module_from_spec(importlib.util.spec_from_loader("_varlen_attn_host", loader))
         loader.exec_module(host)
         host.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-            lib.varlen_attn_fwd_workspace_bytes, lib.varlen_attn_bwd_workspace_bytes, lib.varlen_attn_fwd, lib.varlen_attn_bwd)))
+            lib.varlen_attn_fwd_workspace_bytes, lib.varlen_attn_bwd_workspace_bytes, lib.varlen_attn_fwd, lib.varlen_attn_bwd,
+            lib.varlen_attn_merge)))
         _host = host
     return _host
 
@@ -256,6 +257,11 @@ def profile_clock_probe(counters):
 
 def varlen_attn_merge(o_parts, lse_parts, out=None, lse=None, stream=None):
     """Merge partial results over key shards: o_parts bf16 [P,T,Hq,D], lse_parts fp32 [P,Hq,T]."""
+    done = (_host or _load_host()).merge(o_parts, lse_parts, out, lse, None if stream is None else stream.cuda_stream)
+    if type(done) is tuple:
+        return done
+    if done is not NotImplemented:
+        _check(done)
     _require(o_parts, torch.bfloat16, "o_parts")
     _require(lse_parts, torch.float32, "lse_parts")
     P, T, Hq, D = o_parts.shape

@@ -1,5 +1,5 @@
-// The Python binding's usual call in native code: what binding.py's varlen_attn_fwd and varlen_attn_bwd do between being
-// called and calling the library, for plain tensors that pass every check.  Anything else (a check that fails, a tensor
+// The Python binding's usual call in native code: what binding.py's varlen_attn_fwd, varlen_attn_bwd and varlen_attn_merge do
+// between being called and calling the library, for plain tensors that pass every check.  Anything else (a check that fails, a tensor
 // subclass, a torch function mode) gets NotImplemented, and binding.py goes through its own checks, which name the fault.
 //
 // Why: the attention call on four samples of 246 tokens runs 7 us on the GPU; checks, parameter block, allocations and
@@ -19,6 +19,7 @@ decltype(&varlen_attn_fwd_workspace_bytes) fwd_workspace_bytes = nullptr;
 decltype(&varlen_attn_bwd_workspace_bytes) bwd_workspace_bytes = nullptr;
 decltype(&varlen_attn_fwd) attn_fwd = nullptr;
 decltype(&varlen_attn_bwd) attn_bwd = nullptr;
+decltype(&varlen_attn_merge) attn_merge = nullptr;
 
 bool plain(PyObject* o) { return THPVariable_CheckExact(o); }
 bool plain_or_none(PyObject* o) { return o == Py_None || plain(o); }
@@ -60,6 +61,14 @@ bool stream_of(PyObject* o, void*& stream) {  // None: the current stream; else 
     return !PyErr_Occurred();
 }
 PyObject* not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
+PyObject* object_of(PyObject* given, const at::Tensor& t) { return given == Py_None ? THPVariable_Wrap(t) : (Py_INCREF(given), given); }
+PyObject* pair(PyObject* given_a, const at::Tensor& a, PyObject* given_b, const at::Tensor& b) {
+    PyObject *x = object_of(given_a, a), *y = x ? object_of(given_b, b) : nullptr;
+    PyObject* r = y ? PyTuple_Pack(2, x, y) : nullptr;
+    Py_XDECREF(x);
+    Py_XDECREF(y);
+    return r;
+}
 
 // A C++ exception becomes a RuntimeError with its message, as torch's own functions make of it.
 template <typename F>
@@ -76,11 +85,11 @@ PyObject* guarded(F f) {
     return nullptr;
 }
 
-// bind(addresses of the four library functions)
+// bind(addresses of the five library functions)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (n != 4) { PyErr_SetString(PyExc_TypeError, "bind takes 4 addresses"); return nullptr; }
-    void* f[4];
-    for (int i = 0; i < 4; ++i) {
+    if (n != 5) { PyErr_SetString(PyExc_TypeError, "bind takes 5 addresses"); return nullptr; }
+    void* f[5];
+    for (int i = 0; i < 5; ++i) {
         f[i] = PyLong_AsVoidPtr(a[i]);
         if (PyErr_Occurred()) return nullptr;
     }
@@ -88,6 +97,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     bwd_workspace_bytes = (decltype(bwd_workspace_bytes))f[1];
     attn_fwd = (decltype(attn_fwd))f[2];
     attn_bwd = (decltype(attn_bwd))f[3];
+    attn_merge = (decltype(attn_merge))f[4];
     Py_RETURN_NONE;
 }
 
@@ -124,13 +134,7 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         Py_BEGIN_ALLOW_THREADS
         status = attn_fwd(&p, qp, kp, vp, cup, op, lp, wp, ws_bytes, stream);
         Py_END_ALLOW_THREADS
-        if (status != VA_OK) return PyLong_FromLong(status);
-        PyObject* o = a[6] == Py_None ? THPVariable_Wrap(out) : (Py_INCREF(a[6]), a[6]);
-        PyObject* l = a[7] == Py_None ? THPVariable_Wrap(lse) : (Py_INCREF(a[7]), a[7]);
-        PyObject* r = o && l ? PyTuple_Pack(2, o, l) : nullptr;
-        Py_XDECREF(o);
-        Py_XDECREF(l);
-        return r;
+        return status != VA_OK ? PyLong_FromLong(status) : pair(a[6], out, a[7], lse);
     });
 }
 
@@ -172,7 +176,7 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor* grads[3] = {&dq, &dk, &dv};
         PyObject* r = PyTuple_New(3);
         for (int i = 0; r && i < 3; ++i) {
-            PyObject* g = a[9 + i] == Py_None ? THPVariable_Wrap(*grads[i]) : (Py_INCREF(a[9 + i]), a[9 + i]);
+            PyObject* g = object_of(a[9 + i], *grads[i]);
             if (!g) { Py_DECREF(r); return nullptr; }
             PyTuple_SET_ITEM(r, i, g);
         }
@@ -180,9 +184,44 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// merge(o_parts, lse_parts, out, lse, stream) -> (out, lse), a status or NotImplemented
+PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 5 || !attn_merge) { PyErr_SetString(PyExc_TypeError, "merge takes 5 arguments, after bind"); return nullptr; }
+    if (!plain(a[0]) || !plain(a[1]) || !plain_or_none(a[2]) || !plain_or_none(a[3]) || at::impl::torch_function_mode_enabled())
+        return not_implemented();
+    return guarded([&]() -> PyObject* {
+        const at::Tensor &o = THPVariable_Unpack(a[0]), &l = THPVariable_Unpack(a[1]);
+        if (!usable(o, at::kBFloat16) || !usable(l, at::kFloat) || o.dim() != 4 || l.dim() != 3 || l.size(0) != o.size(0) ||
+            l.size(1) != o.size(2) || l.size(2) != o.size(1))
+            return not_implemented();
+        for (int i = 0; i < 4; ++i) if (!fits(o.size(i))) return not_implemented();
+        varlen_attn_params p{};
+        p.total_tokens = (int32_t)o.size(1);
+        p.num_seqs = 1;
+        p.num_q_heads = p.num_kv_heads = (int32_t)o.size(2);
+        p.head_dim = (int32_t)o.size(3);
+        p.softmax_scale = 1.f;
+        const at::Tensor out = a[2] == Py_None ? at::empty({o.size(1), o.size(2), o.size(3)}, o.options()) : THPVariable_Unpack(a[2]);
+        const at::Tensor lse = a[3] == Py_None ? at::empty({o.size(2), o.size(1)}, l.options()) : THPVariable_Unpack(a[3]);
+        void* stream;
+        if (!stream_of(a[4], stream)) return nullptr;
+        const int32_t parts = (int32_t)o.size(0);
+        const void* op = o.data_ptr();
+        const float* lp = (const float*)l.data_ptr();
+        void* outp = out.data_ptr();
+        float* lsep = (float*)lse.data_ptr();
+        int status;
+        Py_BEGIN_ALLOW_THREADS
+        status = attn_merge(&p, parts, op, lp, outp, lsep, stream);
+        Py_END_ALLOW_THREADS
+        return status != VA_OK ? PyLong_FromLong(status) : pair(a[2], out, a[3], lse);
+    });
+}
+
 PyMethodDef methods[] = {{"bind", (PyCFunction)(void (*)())bind, METH_FASTCALL, nullptr},
                          {"fwd", (PyCFunction)(void (*)())fwd, METH_FASTCALL, nullptr},
                          {"bwd", (PyCFunction)(void (*)())bwd, METH_FASTCALL, nullptr},
+                         {"merge", (PyCFunction)(void (*)())merge, METH_FASTCALL, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_varlen_attn_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
