@@ -653,21 +653,16 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         __bf16* dkp = dK + ((size_t)(sb + kv) * Hkv + c) * D;
         __bf16* dvp = dV + ((size_t)(sb + kv) * Hkv + c) * D;
 #pragma unroll
-        for (int db = 0; db < OB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int d0 = 32 * (db0 + db) + 8 * r4 + 4 * hh;
-                if (d0 < D) {
-                    bf16x4 a, b;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        a[e] = (__bf16)(dkacc[db][4 * r4 + e] * scale);
-                        b[e] = (__bf16)(dvacc[db][4 * r4 + e]);
-                    }
-                    *(bf16x4*)(dkp + d0) = a;
-                    *(bf16x4*)(dvp + d0) = b;
-                }
+        for (int db = 0; db < OB; ++db) {
+            const int d0 = 32 * (db0 + db);
+            if (D % 32 == 0 || d0 + 32 <= D) {
+                store_channels<32>(dkp + d0, dkacc[db], scale, hh);
+                store_channels<32>(dvp + d0, dvacc[db], 1.f, hh);
+            } else {
+                store_channels<16>(dkp + d0, dkacc[db], scale, hh);
+                store_channels<16>(dvp + d0, dvacc[db], 1.f, hh);
             }
+        }
     }
     wg_clock.end(clock_probe);
 }
@@ -1025,17 +1020,8 @@ dq_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf
     } else if (qvalid) {
         __bf16* dqp = dQ + ((size_t)(sb + qrow) * Hq + h) * D;
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int d0 = 32 * db + 8 * r4 + 4 * hh;
-                if (d0 < D) {
-                    bf16x4 a;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) a[e] = (__bf16)(dqacc[db][4 * r4 + e] * scale);
-                    *(bf16x4*)(dqp + d0) = a;
-                }
-            }
+        for (int db = 0; db < D / 32; ++db) store_channels<32>(dqp + 32 * db, dqacc[db], scale, hh);
+        if constexpr (D % 32 != 0) store_channels<16>(dqp + D - 16, dqacc[C::DB - 1], scale, hh);
     }
     wg_clock.end(clock_probe);
 }

@@ -399,6 +399,28 @@ __device__ __forceinline__ float bf16_as_float(bf16x8 x, int e) {
     return __uint_as_float(e & 1 ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
 }
 
+// Rounds a 32-channel block of a result to bf16 and stores it: x is an MFMA result with channels down and rows across, lane l
+// holds channels 8 i + 4 (l / 32) .. + 3 (i = 0..3) of row l % 32.  The halves of the wave trade, so that a lane stores 16 bytes
+// where it has 8: half as many stores, each of which reaches 32 rows.  What a workgroup of a few steps spends at its end is these
+// stores.  Measured, 8 bytes -> 16, forward / dK/dV / dQ, us: 64..384 tokens, 16 heads of 64, 191.6/385.8/288.9 ->
+// 180.9/356.2/278.4; 64..1024 tokens, of 80 384/717/567 -> 369/684/552, of 96 436/922/594 -> 418/878/577, of 128 causal 483/908/676 ->
+// 474/840/666; ViT batch 2853/5089/3767 -> 2832/5042/3743; long walks even.  CHANNELS: 32, or 16 where the row ends there; dst: the
+// row's first channel of the block.  Must be reached by lanes l and l ^ 32 together (they share the row).
+template <int CHANNELS>
+__device__ __forceinline__ void store_channels(__bf16* dst, const f32x16& x, float f, int half) {
+#pragma unroll
+    for (int i = 0; i < CHANNELS / 16; ++i) {
+        bf16x8 v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (__bf16)(x[8 * i + e] * f);
+        const u32x4 w = __builtin_bit_cast(u32x4, v);
+        const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+        const u32x4 out = {a[0], b[0], a[1], b[1]};
+        *(u32x4*)(dst + 16 * i + 8 * half) = out;
+    }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 constexpr float kLog2e = 1.4426950408889634f;

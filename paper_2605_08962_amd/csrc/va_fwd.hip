@@ -603,17 +603,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
         }
         __bf16* op = O + ((size_t)(sb + qrow) * Hq + h) * D;
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                int d0 = 32 * db + 8 * r4 + 4 * hh;
-                if (d0 < D) {
-                    bf16x4 o4;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][4 * r4 + e] * inv);
-                    *(bf16x4*)(op + d0) = o4;
-                }
-            }
+        for (int db = 0; db < D / 32; ++db) store_channels<32>(op + 32 * db, oacc[db], inv, hh);
+        if constexpr (D % 32 != 0) store_channels<16>(op + D - 16, oacc[C::DB - 1], inv, hh);
         if (hh == 0) LSE[(size_t)h * T + sb + qrow] = row_lse;
     }
     wg_clock.end(clock_probe);
