@@ -53,20 +53,25 @@ def _compile(item):
     return obj
 
 
-def build_host():
-    """_varlen_attn_host.so; returns its path."""
+def compile_host(source, target):
+    """A CPython module from `source` against the installed torch."""
     import torch
     t = os.path.dirname(torch.__file__)
     inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
            sysconfig.get_paths()["include"]]
     # (under its own name only when whole: another process may be loading the old one)
-    tmp = f"{HOST}.{os.getpid()}"
+    tmp = f"{target}.{os.getpid()}"
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                     f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in inc),
-                    os.path.join(CSRC, "va_host.cpp"), "-o", tmp, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip",
-                    "-ltorch_cpu", "-ltorch_python"], check=True)
-    os.replace(tmp, HOST)
-    return HOST
+                    source, "-o", tmp, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"],
+                   check=True)
+    os.replace(tmp, target)
+    return target
+
+
+def build_host():
+    """_varlen_attn_host.so; returns its path."""
+    return compile_host(os.path.join(CSRC, "va_host.cpp"), HOST)
 
 
 def build():

@@ -9,6 +9,7 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/varlen_attn.h"
@@ -70,19 +71,13 @@ PyObject* pair(PyObject* given_a, const at::Tensor& a, PyObject* given_b, const 
     return r;
 }
 
-// A C++ exception becomes a RuntimeError with its message, as torch's own functions make of it.
+// Errors come out as torch's own Python functions raise them: torch.OutOfMemoryError of an allocation, and what a dispatch mode
+// raised inside one.
 template <typename F>
 PyObject* guarded(F f) {
-    try {
-        return f();
-    } catch (const c10::Error& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-    } catch (...) {
-        PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
-    }
-    return nullptr;
+    HANDLE_TH_ERRORS
+    return f();
+    END_HANDLE_TH_ERRORS
 }
 
 // bind(addresses of the five library functions)
