@@ -71,6 +71,14 @@ PyObject* pair(PyObject* given_a, const at::Tensor& a, PyObject* given_b, const 
     return r;
 }
 
+// The interpreter's lock is given up from the first allocation, which may have to go to the driver, to the launch's end.
+struct WithoutLock {
+    PyThreadState* state = PyEval_SaveThread();
+    WithoutLock() = default;
+    WithoutLock(const WithoutLock&) = delete;
+    ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
 // Errors come out as torch's own Python functions raise them: torch.OutOfMemoryError of an allocation, and what a dispatch mode
 // raised inside one.
 template <typename F>
@@ -114,21 +122,18 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             !fill(p, q, k, cu, a[4] == Py_True, scale, splits, longest) || k.sizes() != v.sizes() || k.size(0) != q.size(0) ||
             k.size(2) != q.size(2))
             return not_implemented();
-        const at::Tensor out = given_or_like(a[6], q);
-        const at::Tensor lse = a[7] == Py_None ? at::empty({q.size(1), q.size(0)}, q.options().dtype(at::kFloat))
-                                               : THPVariable_Unpack(a[7]);
-        const at::Tensor ws = workspace_of(a[8], a[8] == Py_None ? fwd_workspace_bytes(&p) : 0, q);
         void* stream;
         if (!stream_of(a[9], stream)) return nullptr;
-        const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
-        const int32_t* cup = (const int32_t*)cu.data_ptr();
-        void *op = out.data_ptr(), *wp = ws.data_ptr();
-        float* lp = (float*)lse.data_ptr();
-        const size_t ws_bytes = (size_t)ws.numel();
+        at::Tensor out, lse;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = attn_fwd(&p, qp, kp, vp, cup, op, lp, wp, ws_bytes, stream);
-        Py_END_ALLOW_THREADS
+        {
+            WithoutLock free;
+            out = given_or_like(a[6], q);
+            lse = a[7] == Py_None ? at::empty({q.size(1), q.size(0)}, q.options().dtype(at::kFloat)) : THPVariable_Unpack(a[7]);
+            const at::Tensor ws = workspace_of(a[8], a[8] == Py_None ? fwd_workspace_bytes(&p) : 0, q);
+            status = attn_fwd(&p, q.data_ptr(), k.data_ptr(), v.data_ptr(), (const int32_t*)cu.data_ptr(), out.data_ptr(),
+                              (float*)lse.data_ptr(), ws.data_ptr(), (size_t)ws.numel(), stream);
+        }
         return status != VA_OK ? PyLong_FromLong(status) : pair(a[6], out, a[7], lse);
     });
 }
@@ -154,19 +159,20 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             !fill(p, q, k, cu, a[7] == Py_True, scale, splits, longest) || dout.sizes() != q.sizes() ||
             out.sizes() != q.sizes() || k.sizes() != v.sizes())
             return not_implemented();
-        const at::Tensor dq = given_or_like(a[9], q), dk = given_or_like(a[10], k), dv = given_or_like(a[11], v);
-        const at::Tensor ws = workspace_of(a[12], a[12] == Py_None ? bwd_workspace_bytes(&p) : 0, q);
         void* stream;
         if (!stream_of(a[13], stream)) return nullptr;
-        const void *gp = dout.data_ptr(), *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr(), *op = out.data_ptr();
-        const float* lp = (const float*)lse.data_ptr();
-        const int32_t* cup = (const int32_t*)cu.data_ptr();
-        void *dqp = dq.data_ptr(), *dkp = dk.data_ptr(), *dvp = dv.data_ptr(), *wp = ws.data_ptr();
-        const size_t ws_bytes = (size_t)ws.numel();
+        at::Tensor dq, dk, dv;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = attn_bwd(&p, gp, qp, kp, vp, op, lp, cup, dqp, dkp, dvp, wp, ws_bytes, stream);
-        Py_END_ALLOW_THREADS
+        {
+            WithoutLock free;
+            dq = given_or_like(a[9], q);
+            dk = given_or_like(a[10], k);
+            dv = given_or_like(a[11], v);
+            const at::Tensor ws = workspace_of(a[12], a[12] == Py_None ? bwd_workspace_bytes(&p) : 0, q);
+            status = attn_bwd(&p, dout.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                              (const float*)lse.data_ptr(), (const int32_t*)cu.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                              dv.data_ptr(), ws.data_ptr(), (size_t)ws.numel(), stream);
+        }
         if (status != VA_OK) return PyLong_FromLong(status);
         const at::Tensor* grads[3] = {&dq, &dk, &dv};
         PyObject* r = PyTuple_New(3);
@@ -196,19 +202,17 @@ PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
         p.num_q_heads = p.num_kv_heads = (int32_t)o.size(2);
         p.head_dim = (int32_t)o.size(3);
         p.softmax_scale = 1.f;
-        const at::Tensor out = a[2] == Py_None ? at::empty({o.size(1), o.size(2), o.size(3)}, o.options()) : THPVariable_Unpack(a[2]);
-        const at::Tensor lse = a[3] == Py_None ? at::empty({o.size(2), o.size(1)}, l.options()) : THPVariable_Unpack(a[3]);
         void* stream;
         if (!stream_of(a[4], stream)) return nullptr;
-        const int32_t parts = (int32_t)o.size(0);
-        const void* op = o.data_ptr();
-        const float* lp = (const float*)l.data_ptr();
-        void* outp = out.data_ptr();
-        float* lsep = (float*)lse.data_ptr();
+        at::Tensor out, lse;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = attn_merge(&p, parts, op, lp, outp, lsep, stream);
-        Py_END_ALLOW_THREADS
+        {
+            WithoutLock free;
+            out = a[2] == Py_None ? at::empty({o.size(1), o.size(2), o.size(3)}, o.options()) : THPVariable_Unpack(a[2]);
+            lse = a[3] == Py_None ? at::empty({o.size(2), o.size(1)}, l.options()) : THPVariable_Unpack(a[3]);
+            status = attn_merge(&p, (int32_t)o.size(0), o.data_ptr(), (const float*)l.data_ptr(), out.data_ptr(),
+                                (float*)lse.data_ptr(), stream);
+        }
         return status != VA_OK ? PyLong_FromLong(status) : pair(a[2], out, a[3], lse);
     });
 }

@@ -104,3 +104,13 @@ def test_a_python_error_inside_an_allocation_stays_what_it_is(host, make):
     call = make(host)
     with Refuses(), pytest.raises(KeyError, match="no allocations here"):
         call()
+
+
+@CALLS
+def test_allocations_leave_the_interpreter_to_other_threads(host, make):
+    """As torch.empty does: one that has to go to the driver may take milliseconds."""
+    call = make(host)
+    host.watch(False)
+    call()
+    with_lock, without_lock = host.watch(False)
+    assert with_lock == 0 and without_lock >= 2
