@@ -126,6 +126,17 @@ def _require(t, dtype, name):
         raise ValueError(f"{name} must be a contiguous {dtype} tensor on the GPU")
 
 
+def _require_room(t, dtype, name, elements=0):
+    """A caller's own buffer (or None): what the kernels write or read by its address alone.  It may be larger than needed or
+    shaped otherwise, and in pinned host memory; dtype None: any (a workspace, of which one byte an element is counted on)."""
+    if t is None:
+        return
+    if not ((t.is_cuda or t.is_pinned()) and (dtype is None or t.dtype == dtype) and t.is_contiguous()):
+        raise ValueError(f"{name} must be a contiguous {'' if dtype is None else f'{dtype} '}tensor on the GPU")
+    if t.numel() < elements:
+        raise ValueError(f"{name} must hold at least {elements} elements")
+
+
 def fwd_workspace_bytes(params):
     return int(load().varlen_attn_fwd_workspace_bytes(ctypes.byref(params)))
 
@@ -147,7 +158,8 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=No
                     stream=None, kv_splits=0, max_seqlen=0):
     """O bf16 [T,Hq,D] and LSE fp32 [Hq,T] of packed attention; asynchronous on the stream.
     kv_splits: 0 automatic, 1 never, 2..8 workgroups sharing the keys of each query tile.
-    max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint)."""
+    max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint).
+    out, lse, workspace: the caller's own buffers, contiguous, large enough, of any shape."""
     done = (_host or _load_host()).fwd(q, k, v, cu_seqlens, bool(causal), float(softmax_scale), out, lse, workspace,
                                        None if stream is None else stream.cuda_stream, int(kv_splits), int(max_seqlen))
     if type(done) is tuple:
@@ -161,6 +173,9 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=No
     p = _params_of(q, k, cu_seqlens, causal, softmax_scale, kv_splits, max_seqlen)
     if k.shape != v.shape or k.shape[0] != q.shape[0] or k.shape[2] != q.shape[2]:
         raise ValueError("k and v must be [T, Hkv, D] matching q's T and D")
+    _require_room(out, torch.bfloat16, "out", q.numel())
+    _require_room(lse, torch.float32, "lse", q.shape[0] * q.shape[1])
+    _require_room(workspace, None, "workspace")
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
@@ -202,7 +217,8 @@ def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, 
     """dQ, dK, dV (bf16) from dO and the forward's saved O and LSE; asynchronous on the stream.
     max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint; above 1024 a launch too small
     to fill the GPU may cut its tiles into chunks, so that a sample's gradients depend, to rounding, on the launch).
-    kv_splits: 1 never does, 0 automatic."""
+    kv_splits: 1 never does, 0 automatic.
+    dq, dk, dv, workspace: the caller's own buffers, contiguous, large enough, of any shape."""
     done = (_host or _load_host()).bwd(dout, q, k, v, out, lse, cu_seqlens, bool(causal), float(softmax_scale), dq, dk, dv,
                                        workspace, None if stream is None else stream.cuda_stream, int(kv_splits),
                                        int(max_seqlen))
@@ -218,6 +234,12 @@ def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, 
     p = _params_of(q, k, cu_seqlens, causal, softmax_scale, kv_splits, max_seqlen)
     if dout.shape != q.shape or out.shape != q.shape or k.shape != v.shape:
         raise ValueError("dout and out must match q; k must match v")
+    if k.dim() != 3 or k.shape[0] != q.shape[0] or k.shape[2] != q.shape[2]:
+        raise ValueError("k and v must be [T, Hkv, D] matching q's T and D")
+    _require_room(lse, torch.float32, "lse", q.shape[0] * q.shape[1])
+    for t, like, n in ((dq, q, "dq"), (dk, k, "dk"), (dv, v, "dv")):
+        _require_room(t, torch.bfloat16, n, like.numel())
+    _require_room(workspace, None, "workspace")
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
@@ -267,6 +289,8 @@ def varlen_attn_merge(o_parts, lse_parts, out=None, lse=None, stream=None):
     P, T, Hq, D = o_parts.shape
     if tuple(lse_parts.shape) != (P, Hq, T):
         raise ValueError("lse_parts must be [P, Hq, T]")
+    _require_room(out, torch.bfloat16, "out", T * Hq * D)
+    _require_room(lse, torch.float32, "lse", T * Hq)
     p = make_params(T, 1, Hq, Hq, D, False, 1.0)
     if out is None:
         out = torch.empty((T, Hq, D), dtype=torch.bfloat16, device=o_parts.device)

@@ -25,6 +25,14 @@ decltype(&varlen_attn_merge) attn_merge = nullptr;
 bool plain(PyObject* o) { return THPVariable_CheckExact(o); }
 bool plain_or_none(PyObject* o) { return o == Py_None || plain(o); }
 bool usable(const at::Tensor& t, at::ScalarType type) { return t.is_cuda() && t.scalar_type() == type && t.is_contiguous(); }
+// A buffer of the caller's own (or none): the kernels go by its address, so it has to hold what they read or write there.
+bool has_room(const at::Tensor& t, at::ScalarType type, int64_t elements) { return usable(t, type) && t.numel() >= elements; }
+bool none_or_room(PyObject* o, at::ScalarType type, int64_t elements) {
+    return o == Py_None || has_room(THPVariable_Unpack(o), type, elements);
+}
+bool none_or_scratch(PyObject* o) {  // (of any type: one byte an element is counted on)
+    return o == Py_None || (THPVariable_Unpack(o).is_cuda() && THPVariable_Unpack(o).is_contiguous());
+}
 bool fits(int64_t x) { return x >= 0 && x <= INT32_MAX; }
 
 // total_tokens, head counts and head_dim from q and k, the rest as given; false if something does not fit the block.
@@ -120,7 +128,8 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         varlen_attn_params p;
         if (!usable(q, at::kBFloat16) || !usable(k, at::kBFloat16) || !usable(v, at::kBFloat16) || !usable(cu, at::kInt) ||
             !fill(p, q, k, cu, a[4] == Py_True, scale, splits, longest) || k.sizes() != v.sizes() || k.size(0) != q.size(0) ||
-            k.size(2) != q.size(2))
+            k.size(2) != q.size(2) || !none_or_room(a[6], at::kBFloat16, q.numel()) ||
+            !none_or_room(a[7], at::kFloat, q.size(0) * q.size(1)) || !none_or_scratch(a[8]))
             return not_implemented();
         void* stream;
         if (!stream_of(a[9], stream)) return nullptr;
@@ -155,9 +164,11 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         varlen_attn_params p;
         for (const at::Tensor* t : {&dout, &q, &k, &v, &out})
             if (!usable(*t, at::kBFloat16)) return not_implemented();
-        if (!usable(lse, at::kFloat) || !usable(cu, at::kInt) ||
-            !fill(p, q, k, cu, a[7] == Py_True, scale, splits, longest) || dout.sizes() != q.sizes() ||
-            out.sizes() != q.sizes() || k.sizes() != v.sizes())
+        if (!usable(cu, at::kInt) || !fill(p, q, k, cu, a[7] == Py_True, scale, splits, longest) || dout.sizes() != q.sizes() ||
+            out.sizes() != q.sizes() || k.sizes() != v.sizes() || k.size(0) != q.size(0) || k.size(2) != q.size(2) ||
+            !has_room(lse, at::kFloat, q.size(0) * q.size(1)) || !none_or_room(a[9], at::kBFloat16, q.numel()) ||
+            !none_or_room(a[10], at::kBFloat16, k.numel()) || !none_or_room(a[11], at::kBFloat16, k.numel()) ||
+            !none_or_scratch(a[12]))
             return not_implemented();
         void* stream;
         if (!stream_of(a[13], stream)) return nullptr;
@@ -193,7 +204,9 @@ PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         const at::Tensor &o = THPVariable_Unpack(a[0]), &l = THPVariable_Unpack(a[1]);
         if (!usable(o, at::kBFloat16) || !usable(l, at::kFloat) || o.dim() != 4 || l.dim() != 3 || l.size(0) != o.size(0) ||
-            l.size(1) != o.size(2) || l.size(2) != o.size(1))
+            l.size(1) != o.size(2) || l.size(2) != o.size(1) ||
+            !none_or_room(a[2], at::kBFloat16, o.size(1) * o.size(2) * o.size(3)) ||
+            !none_or_room(a[3], at::kFloat, o.size(1) * o.size(2)))
             return not_implemented();
         for (int i = 0; i < 4; ++i) if (!fits(o.size(i))) return not_implemented();
         varlen_attn_params p{};

@@ -1,5 +1,6 @@
 """The native half of the binding (csrc/va_host.cpp), built for CPU tensors (marshalling_check.cpp) and bound to functions that
-only note what they are called with: what it allocates and how, what it refuses, and which errors come out of it."""
+only note what they are called with: what it allocates and how, what it refuses, and which errors come out of it.  The same
+refusals of the Python half, by name, with a library that notes its calls."""
 import ctypes
 import importlib.machinery
 import importlib.util
@@ -10,7 +11,7 @@ import pytest
 import torch
 from torch.utils._python_dispatch import TorchDispatchMode
 
-from paper_2605_08962_amd import build
+from paper_2605_08962_amd import binding, build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 T, HQ, HKV, D, WORKSPACE = 70, 2, 1, 64, 4096
@@ -114,3 +115,83 @@ def test_allocations_leave_the_interpreter_to_other_threads(host, make):
     call()
     with_lock, without_lock = host.watch(False)
     assert with_lock == 0 and without_lock >= 2
+
+
+def _bf(*shape):
+    return torch.zeros(shape, dtype=torch.bfloat16)
+
+
+# What a call may not be given: (call, replaced arguments, the name that the Python half refuses it by).
+BAD = [
+    # k and v of another length or head_dim than q: read past their ends
+    (_bwd, dict(k=_bf(T - 1, HKV, D), v=_bf(T - 1, HKV, D)), "k and v"),
+    (_bwd, dict(k=_bf(T, HKV, 32), v=_bf(T, HKV, 32)), "k and v"),
+    (_bwd, dict(k=_bf(T, HKV), v=_bf(T, HKV)), "k and v"),
+    (_bwd, dict(lse=torch.zeros(HQ, T - 1)), "lse"),
+    (_bwd, dict(lse=torch.zeros(T)), "lse"),
+    # results: too small, of another type, with gaps
+    (_fwd, dict(out=_bf(T - 1, HQ, D)), "out"),
+    (_fwd, dict(out=torch.zeros(T, HQ, D)), "out"),
+    (_fwd, dict(out=_bf(T, HQ, 2 * D)[:, :, :D]), "out"),
+    (_fwd, dict(out_lse=torch.zeros(HQ, T - 1)), "lse"),
+    (_fwd, dict(out_lse=torch.zeros(HQ, T, dtype=torch.float64)), "lse"),
+    (_bwd, dict(dq=_bf(T, HQ, D - 8)), "dq"),
+    (_bwd, dict(dk=_bf(T, HQ, D).float()), "dk"),
+    (_bwd, dict(dv=_bf(HKV, T, D)[:, ::2]), "dv"),
+    (_merge, dict(out=_bf(T, 1, D)), "out"),
+    (_merge, dict(out_lse=torch.zeros(1, T)), "lse"),
+    # a workspace whose elements do not lie side by side
+    (_fwd, dict(workspace=torch.zeros(1, dtype=torch.uint8).expand(1 << 20)), "workspace"),
+    (_bwd, dict(workspace=torch.zeros(2 * WORKSPACE, dtype=torch.uint8)[::2]), "workspace"),
+]
+# And what it may: a buffer that is larger than the result, or shaped otherwise.
+GOOD = [
+    (_fwd, dict(out=_bf(T + 9, HQ, D), out_lse=torch.zeros(HQ * T + 3))),
+    (_fwd, dict(out=_bf(T, HQ * D), workspace=torch.zeros(WORKSPACE))),
+    (_bwd, dict(dq=_bf(T * HQ * D), dk=_bf(T + 1, HKV, D), lse=torch.zeros(HQ * T))),
+    (_merge, dict(out=_bf(T + 9, HQ, D), out_lse=torch.zeros(HQ * T + 3))),
+]
+
+
+@pytest.mark.parametrize("make,other,name", BAD)
+def test_the_native_half_refuses_what_would_leave_its_buffers(host, make, other, name):
+    assert make(host, **other)() is NotImplemented
+    assert not host.calls
+
+
+@pytest.mark.parametrize("make,other", GOOD)
+def test_the_native_half_takes_larger_buffers(host, make, other):
+    assert type(make(host, **other)()) is tuple and len(host.calls) == 1
+
+
+@pytest.fixture
+def python_half(host, monkeypatch):
+    """Something with the native half's call signatures that goes through the Python half."""
+    never = lambda *a: NotImplemented  # noqa: E731
+    monkeypatch.setattr(binding, "_host", types.SimpleNamespace(fwd=never, bwd=never, merge=never))
+    calls = []
+    noted = lambda name: lambda *a: calls.append(name) or 0  # noqa: E731
+    size = lambda p: WORKSPACE  # noqa: E731
+    lib = types.SimpleNamespace(varlen_attn_fwd=noted("fwd"), varlen_attn_bwd=noted("bwd"), varlen_attn_merge=noted("merge"),
+                                varlen_attn_fwd_workspace_bytes=size, varlen_attn_bwd_workspace_bytes=size)
+    monkeypatch.setattr(binding, "load", lambda: lib)
+    monkeypatch.setattr(binding, "_stream_handle", lambda stream: None)
+    monkeypatch.setattr(torch.Tensor, "is_cuda", property(lambda t: True))
+    kw = lambda *names: lambda a: dict(zip(names, a))  # noqa: E731
+    fwd, bwd = kw("out", "lse", "workspace", "stream"), kw("dq", "dk", "dv", "workspace", "stream")
+    return types.SimpleNamespace(
+        fwd=lambda *a: binding.varlen_attn_fwd(*a[:6], **fwd(a[6:10])),
+        bwd=lambda *a: binding.varlen_attn_bwd(*a[:9], **bwd(a[9:14])),
+        merge=binding.varlen_attn_merge, calls=calls)
+
+
+@pytest.mark.parametrize("make,other,name", BAD)
+def test_the_python_half_refuses_the_same_by_name(python_half, make, other, name):
+    with pytest.raises(ValueError, match=f"^{name} must"):
+        make(python_half, **other)()
+    assert not python_half.calls
+
+
+@pytest.mark.parametrize("make,other", GOOD)
+def test_the_python_half_takes_the_same(python_half, make, other):
+    assert type(make(python_half, **other)()) is tuple and len(python_half.calls) == 1

@@ -71,3 +71,30 @@ def test_native_calls_refuse_what_the_python_way_refuses():
         assert want is not None and _refusal(binding.varlen_attn_fwd, q, *args, **kw) == want
     assert _refusal(binding.varlen_attn_fwd, q[:, :, ::2], k, v, cu, True, 0.1)[0] is ValueError
     assert _refusal(binding.varlen_attn_merge, q[None], torch.zeros((1, 2, 69), device="cuda"))[1] == "lse_parts must be [P, Hq, T]"
+
+
+@pytest.mark.gpu
+def test_a_backward_whose_k_and_v_do_not_match_q_is_refused():
+    q, k, v, cu = _inputs("cuda")
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, True, 0.1)
+    for k2, v2, l2, why in [(k[:-1], v[:-1], lse, "k and v must be"), (k[..., :32].contiguous(), v[..., :32].contiguous(), lse, "k and v must be"),
+                            (k, v, lse[:, :-1].contiguous(), "lse must hold at least 140 elements")]:
+        for first in (q, q.as_subclass(Subclass)):
+            with pytest.raises(ValueError, match=why):
+                binding.varlen_attn_bwd(first, q, k2, v2, o, l2, cu, True, 0.1)
+
+
+@pytest.mark.gpu
+def test_results_go_where_the_caller_says():
+    """Buffers larger than the result or shaped otherwise, and pinned host memory (which only the Python half takes)."""
+    q, k, v, cu = _inputs("cuda")
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, True, 0.1)
+    for out, l2 in [(torch.zeros((75, 2, 64), dtype=torch.bfloat16, device="cuda"), torch.zeros(150, device="cuda")),
+                    (torch.zeros(70 * 128, dtype=torch.bfloat16).pin_memory(), torch.zeros(140).pin_memory())]:
+        got = binding.varlen_attn_fwd(q, k, v, cu, True, 0.1, out=out, lse=l2)
+        torch.cuda.synchronize()
+        assert got[0] is out and got[1] is l2
+        assert torch.equal(out.flatten()[:o.numel()].cuda(), o.flatten()) and torch.equal(l2[:140].cuda(), lse.flatten())
+        assert not out.flatten()[o.numel():].any() and not l2[140:].any()
+    with pytest.raises(ValueError, match="^out must be"):
+        binding.varlen_attn_fwd(q, k, v, cu, True, 0.1, out=torch.empty((70, 2, 64), dtype=torch.bfloat16))
