@@ -154,9 +154,40 @@ def _stream_handle(stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+class _Allocating:
+    """Allocations for kernels on `stream`, made while this is entered.  They come from that stream's pool: a workspace goes
+    back to it as soon as the call returns, with the kernels still to run, and what the current stream's pool hands out may be
+    in use by work that is still queued there.  result(t): t is the caller's, who uses it on the current stream and may drop it
+    with such work queued."""
+
+    def __init__(self, stream, device):
+        self._user = None
+        if stream is not None:
+            current = torch.cuda.current_stream(device)
+            if stream.cuda_stream != current.cuda_stream:
+                self._user = current
+                self._pool = torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else
+                                               torch.cuda.ExternalStream(stream.cuda_stream, device=device))
+
+    def __enter__(self):
+        if self._user is not None:
+            self._pool.__enter__()
+        return self
+
+    def __exit__(self, *error):
+        if self._user is not None:
+            self._pool.__exit__(*error)
+
+    def result(self, t):
+        if self._user is not None:
+            t.record_stream(self._user)
+        return t
+
+
 def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=None, workspace=None,
                     stream=None, kv_splits=0, max_seqlen=0):
-    """O bf16 [T,Hq,D] and LSE fp32 [Hq,T] of packed attention; asynchronous on the stream.
+    """O bf16 [T,Hq,D] and LSE fp32 [Hq,T] of packed attention; asynchronous on the stream (default: the current one; the
+    inputs must be ready there, and what is not given is allocated from its pool).
     kv_splits: 0 automatic, 1 never, 2..8 workgroups sharing the keys of each query tile.
     max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint).
     out, lse, workspace: the caller's own buffers, contiguous, large enough, of any shape."""
@@ -176,12 +207,13 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, causal, softmax_scale, out=None, lse=No
     _require_room(out, torch.bfloat16, "out", q.numel())
     _require_room(lse, torch.float32, "lse", q.shape[0] * q.shape[1])
     _require_room(workspace, None, "workspace")
-    if out is None:
-        out = torch.empty_like(q)
-    if lse is None:
-        lse = torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device)
-    if workspace is None:
-        workspace = torch.empty(max(fwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
+    with _Allocating(stream, q.device) as a:
+        if out is None:
+            out = a.result(torch.empty_like(q))
+        if lse is None:
+            lse = a.result(torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device))
+        if workspace is None:
+            workspace = torch.empty(max(fwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
     _check(lib.varlen_attn_fwd(ctypes.byref(p), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                cu_seqlens.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                workspace.data_ptr(), workspace.numel(), _stream_handle(stream)))
@@ -214,7 +246,7 @@ def varlen_attn_fwd_static_scratch(q, k, v, cu_seqlens, causal, softmax_scale, o
 
 def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, dq=None, dk=None,
                     dv=None, workspace=None, stream=None, max_seqlen=0, kv_splits=0):
-    """dQ, dK, dV (bf16) from dO and the forward's saved O and LSE; asynchronous on the stream.
+    """dQ, dK, dV (bf16) from dO and the forward's saved O and LSE; asynchronous on the stream (as varlen_attn_fwd).
     max_seqlen: 0 unknown, else the caller's promise that no sample is longer (a hint; above 1024 a launch too small
     to fill the GPU may cut its tiles into chunks, so that a sample's gradients depend, to rounding, on the launch).
     kv_splits: 1 never does, 0 automatic.
@@ -240,11 +272,12 @@ def varlen_attn_bwd(dout, q, k, v, out, lse, cu_seqlens, causal, softmax_scale, 
     for t, like, n in ((dq, q, "dq"), (dk, k, "dk"), (dv, v, "dv")):
         _require_room(t, torch.bfloat16, n, like.numel())
     _require_room(workspace, None, "workspace")
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
-    if workspace is None:
-        workspace = torch.empty(max(bwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
+    with _Allocating(stream, q.device) as a:
+        dq = a.result(torch.empty_like(q)) if dq is None else dq
+        dk = a.result(torch.empty_like(k)) if dk is None else dk
+        dv = a.result(torch.empty_like(v)) if dv is None else dv
+        if workspace is None:
+            workspace = torch.empty(max(bwd_workspace_bytes(p), 16), dtype=torch.uint8, device=q.device)
     _check(lib.varlen_attn_bwd(ctypes.byref(p), dout.data_ptr(), q.data_ptr(), k.data_ptr(),
                                v.data_ptr(), out.data_ptr(), lse.data_ptr(), cu_seqlens.data_ptr(),
                                dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), workspace.data_ptr(),
@@ -292,10 +325,11 @@ def varlen_attn_merge(o_parts, lse_parts, out=None, lse=None, stream=None):
     _require_room(out, torch.bfloat16, "out", T * Hq * D)
     _require_room(lse, torch.float32, "lse", T * Hq)
     p = make_params(T, 1, Hq, Hq, D, False, 1.0)
-    if out is None:
-        out = torch.empty((T, Hq, D), dtype=torch.bfloat16, device=o_parts.device)
-    if lse is None:
-        lse = torch.empty((Hq, T), dtype=torch.float32, device=o_parts.device)
+    with _Allocating(stream, o_parts.device) as a:
+        if out is None:
+            out = a.result(torch.empty((T, Hq, D), dtype=torch.bfloat16, device=o_parts.device))
+        if lse is None:
+            lse = a.result(torch.empty((Hq, T), dtype=torch.float32, device=o_parts.device))
     _check(load().varlen_attn_merge(ctypes.byref(p), P, o_parts.data_ptr(), lse_parts.data_ptr(), out.data_ptr(),
                                     lse.data_ptr(), _stream_handle(stream)))
     return out, lse
@@ -305,7 +339,8 @@ def check_cu_seqlens(cu_seqlens, total_tokens, stream=None):
     """True if the device array obeys cu[0] = 0, non-decreasing, cu[-1] = total_tokens.  Synchronises the stream."""
     _require(cu_seqlens, torch.int32, "cu_seqlens")
     p = make_params(total_tokens, cu_seqlens.numel() - 1, 1, 1, 64, False, 1.0)
-    ws = torch.empty(16, dtype=torch.uint8, device=cu_seqlens.device)
+    with _Allocating(stream, cu_seqlens.device):
+        ws = torch.empty(16, dtype=torch.uint8, device=cu_seqlens.device)
     rc = load().varlen_attn_check_cu_seqlens(ctypes.byref(p), cu_seqlens.data_ptr(), ws.data_ptr(), ws.numel(),
                                              _stream_handle(stream))
     if rc == VA_ERR_BAD_CU_SEQLENS:

@@ -1,6 +1,6 @@
 // The Python binding's usual call in native code: what binding.py's varlen_attn_fwd, varlen_attn_bwd and varlen_attn_merge do
 // between being called and calling the library, for plain tensors that pass every check.  Anything else (a check that fails, a tensor
-// subclass, a torch function mode) gets NotImplemented, and binding.py goes through its own checks, which name the fault.
+// subclass, a torch function mode, allocations for another stream) gets NotImplemented, and binding.py goes through its own checks, which name the fault.
 //
 // Why: the attention call on four samples of 246 tokens runs 7 us on the GPU; checks, parameter block, allocations and
 // argument conversion in Python took 13 us per call, so that a program that makes such calls waited for its host.
@@ -69,6 +69,11 @@ bool stream_of(PyObject* o, void*& stream) {  // None: the current stream; else 
     stream = PyLong_AsVoidPtr(o);
     return !PyErr_Occurred();
 }
+// Whether a call that allocates has to leave it to binding.py: its kernels run on another stream than the one whose pool
+// at::empty takes memory from (see _Allocating there).
+bool elsewhere(PyObject* given, const void* stream, const at::Tensor& q) {
+    return given != Py_None && stream != (void*)c10::hip::getCurrentHIPStream(q.device().index()).stream();
+}
 PyObject* not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
 PyObject* object_of(PyObject* given, const at::Tensor& t) { return given == Py_None ? THPVariable_Wrap(t) : (Py_INCREF(given), given); }
 PyObject* pair(PyObject* given_a, const at::Tensor& a, PyObject* given_b, const at::Tensor& b) {
@@ -133,6 +138,7 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             return not_implemented();
         void* stream;
         if (!stream_of(a[9], stream)) return nullptr;
+        if ((a[6] == Py_None || a[7] == Py_None || a[8] == Py_None) && elsewhere(a[9], stream, q)) return not_implemented();
         at::Tensor out, lse;
         int status;
         {
@@ -172,6 +178,8 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             return not_implemented();
         void* stream;
         if (!stream_of(a[13], stream)) return nullptr;
+        for (int i = 9; i < 13; ++i)
+            if (a[i] == Py_None && elsewhere(a[13], stream, q)) return not_implemented();
         at::Tensor dq, dk, dv;
         int status;
         {
@@ -217,6 +225,7 @@ PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
         p.softmax_scale = 1.f;
         void* stream;
         if (!stream_of(a[4], stream)) return nullptr;
+        if ((a[2] == Py_None || a[3] == Py_None) && elsewhere(a[4], stream, o)) return not_implemented();
         at::Tensor out, lse;
         int status;
         {

@@ -1,6 +1,7 @@
 """The native half of the binding (csrc/va_host.cpp), built for CPU tensors (marshalling_check.cpp) and bound to functions that
 only note what they are called with: what it allocates and how, what it refuses, and which errors come out of it.  The same
 refusals of the Python half, by name, with a library that notes its calls."""
+import contextlib
 import ctypes
 import importlib.machinery
 import importlib.util
@@ -175,14 +176,36 @@ def python_half(host, monkeypatch):
     lib = types.SimpleNamespace(varlen_attn_fwd=noted("fwd"), varlen_attn_bwd=noted("bwd"), varlen_attn_merge=noted("merge"),
                                 varlen_attn_fwd_workspace_bytes=size, varlen_attn_bwd_workspace_bytes=size)
     monkeypatch.setattr(binding, "load", lambda: lib)
-    monkeypatch.setattr(binding, "_stream_handle", lambda stream: None)
+    at, made = [0], []  # the current stream's handle; (who, stream then current) of every allocation and record
+
+    class Stream:
+        def __init__(self, handle, device=None):
+            self.cuda_stream = handle
+
+    @contextlib.contextmanager
+    def on(stream):
+        was, at[0] = at[0], stream.cuda_stream
+        yield
+        at[0] = was
+
+    class Allocations(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            if "empty" in str(func):
+                made.append(("empty", at[0]))
+            return func(*args, **(kwargs or {}))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream(at[0]))
+    monkeypatch.setattr(torch.cuda, "stream", on)
+    monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", Stream)
+    monkeypatch.setattr(torch.Tensor, "record_stream", lambda t, s: made.append(("record", s.cuda_stream)))
     monkeypatch.setattr(torch.Tensor, "is_cuda", property(lambda t: True))
     kw = lambda *names: lambda a: dict(zip(names, a))  # noqa: E731
     fwd, bwd = kw("out", "lse", "workspace", "stream"), kw("dq", "dk", "dv", "workspace", "stream")
     return types.SimpleNamespace(
         fwd=lambda *a: binding.varlen_attn_fwd(*a[:6], **fwd(a[6:10])),
         bwd=lambda *a: binding.varlen_attn_bwd(*a[:9], **bwd(a[9:14])),
-        merge=binding.varlen_attn_merge, calls=calls)
+        merge=lambda *a: binding.varlen_attn_merge(*a[:4], stream=a[4]), calls=calls, made=made, at=at, Stream=Stream,
+        allocations=Allocations)
 
 
 @pytest.mark.parametrize("make,other,name", BAD)
@@ -195,3 +218,35 @@ def test_the_python_half_refuses_the_same_by_name(python_half, make, other, name
 @pytest.mark.parametrize("make,other", GOOD)
 def test_the_python_half_takes_the_same(python_half, make, other):
     assert type(make(python_half, **other)()) is tuple and len(python_half.calls) == 1
+
+
+# Scratch that a call allocates for itself is given back when the call returns, while its kernels may still run: it has to come
+# from the pool of the stream they run on, where what is given back is reused behind them and what is taken is free.
+GIVEN = {_fwd: lambda: dict(out=_bf(T, HQ, D), out_lse=torch.zeros(HQ, T), workspace=torch.zeros(WORKSPACE)),
+         _bwd: lambda: dict(dq=_bf(T, HQ, D), dk=_bf(T, HKV, D), dv=_bf(T, HKV, D), workspace=torch.zeros(WORKSPACE)),
+         _merge: lambda: dict(out=_bf(T, HQ, D), out_lse=torch.zeros(HQ, T))}
+
+
+@CALLS
+def test_the_native_half_allocates_on_the_current_stream_only(host, make):
+    host.set_current_stream(48)
+    for stream, given, taken in [(None, False, True), (48, False, True), (None, True, True), (64, True, True), (64, False, False)]:
+        host.calls.clear()
+        done = make(host, stream=stream, **(GIVEN[make]() if given else {}))()
+        assert (type(done) is tuple) == taken and (done is NotImplemented) == (not taken)
+        assert [args[-1] for _, args in host.calls] == ([stream or 48] if taken else [])
+
+
+@CALLS
+def test_the_python_half_allocates_on_the_stream_of_the_call(python_half, make):
+    python_half.at[0] = 48
+    results = {_fwd: 2, _bwd: 3, _merge: 2}[make]
+    for handle, given, pool in [(None, False, 48), (48, False, 48), (64, True, None), (64, False, 64)]:
+        python_half.made.clear()
+        call = make(python_half, stream=None if handle is None else python_half.Stream(handle), **(GIVEN[make]() if given else {}))
+        with python_half.allocations():
+            call()
+        empties = [s for what, s in python_half.made if what == "empty"]
+        assert set(empties) == (set() if given else {pool}) and (given or len(empties) >= results)
+        # the results are used on the stream that was current, and may be dropped with such uses under way
+        assert [s for what, s in python_half.made if what == "record"] == ([48] * results if pool == 64 else [])

@@ -98,3 +98,39 @@ def test_results_go_where_the_caller_says():
         assert not out.flatten()[o.numel():].any() and not l2[140:].any()
     with pytest.raises(ValueError, match="^out must be"):
         binding.varlen_attn_fwd(q, k, v, cu, True, 0.1, out=torch.empty((70, 2, 64), dtype=torch.bfloat16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("as_handle", [False, True])
+def test_what_a_call_on_another_stream_allocates_is_that_streams(as_handle):
+    """Results and workspace lie in the pool of the stream the kernels run on (long enough a sample for chunks, whose fp32 parts
+    make the workspace the largest piece), and the results are right."""
+    T, hq = 3000, 2
+    q, k, v, _ = _inputs("cuda", T=T)
+    cu = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, True, 0.1, max_seqlen=T)
+    grads = binding.varlen_attn_bwd(q, q, k, v, o, lse, cu, True, 0.1, max_seqlen=T)
+    merged = binding.varlen_attn_merge(o[None], lse[None])
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+
+    class Handle:
+        cuda_stream = side.cuda_stream
+    stream = Handle() if as_handle else side
+
+    def pool():
+        return [(s["address"], s["address"] + s["total_size"]) for s in torch.cuda.memory_snapshot() if s["stream"] == side.cuda_stream]
+    p = binding.make_params(T, 1, hq, 1, 64, True, 0.1, max_seqlen=T)
+    for call, want, scratch in [
+            (lambda s: binding.varlen_attn_fwd(q, k, v, cu, True, 0.1, stream=s, max_seqlen=T), (o, lse), binding.fwd_workspace_bytes(p)),
+            (lambda s: binding.varlen_attn_bwd(q, q, k, v, o, lse, cu, True, 0.1, stream=s, max_seqlen=T), grads,
+             binding.bwd_workspace_bytes(p)),
+            (lambda s: binding.varlen_attn_merge(o[None], lse[None], stream=s), merged, 0)]:
+        torch.cuda.empty_cache()
+        got = call(stream)
+        segments = pool()
+        assert sum(b - a for a, b in segments) >= scratch + sum(t.nbytes for t in got)
+        assert all(any(a <= t.data_ptr() < b for a, b in segments) for t in got)
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
+        del got
