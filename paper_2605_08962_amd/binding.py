@@ -1,6 +1,7 @@
 """Python binding of libvarlen_attn.so: argument marshalling only.
 
-Forward, backward and merge are marshalled in native code (csrc/va_host.cpp) where nothing is unusual about the call, else here.
+Forward, backward and merge are marshalled in native code (csrc/va_host.cpp) where that is built and nothing is unusual about the
+call, else here.
 Every step of the attention path runs in the library's HIP kernels.  PyTorch is used for device
 memory (outputs, workspace) and for the current stream handle, nothing else.  There is no CPU or
 eager fallback: if the library is missing or a call fails, this raises.
@@ -9,14 +10,17 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import subprocess
+import threading
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libvarlen_attn.so")
-HOST_PATH = os.path.join(_HERE, "_varlen_attn_host.so")
 _lib = None
 _host = None
+_host_lock = threading.Lock()
 
 VA_OK = 0
 VA_ERR_BAD_CU_SEQLENS = 8
@@ -80,20 +84,40 @@ def load():
     return lib
 
 
+class _PythonHalf:
+    """Stands where the native half should: leaves every call to the code below."""
+
+    @staticmethod
+    def fwd(*args):
+        return NotImplemented
+
+    bwd = merge = fwd
+
+
 def _load_host():
-    """The native half of this module, told where the library's entry points are."""
+    """The native half of this module, told where the library's entry points are (building it first only when it is not there).
+    Without a compiler, torch's headers or a module that loads, the Python half does all of it, 4-6 us of host time a call slower."""
     global _host
-    if _host is None:
+    with _host_lock:
+        if _host is not None:
+            return _host
         lib = load()
-        if not os.path.exists(HOST_PATH):
-            from . import build as _build
-            _build.build_host()
-        loader = importlib.machinery.ExtensionFileLoader("_varlen_attn_host", HOST_PATH)
-        host = importlib.util.module_from_spec(importlib.util.spec_from_loader("_varlen_attn_host", loader))
-        loader.exec_module(host)
-        host.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-            lib.varlen_attn_fwd_workspace_bytes, lib.varlen_attn_bwd_workspace_bytes, lib.varlen_attn_fwd, lib.varlen_attn_bwd,
-            lib.varlen_attn_merge)))
+        from . import build as _build
+        try:
+            path = _build.host_path()
+            if not os.path.exists(path):
+                _build.build_host()
+            loader = importlib.machinery.ExtensionFileLoader("_varlen_attn_host", path)
+            host = importlib.util.module_from_spec(importlib.util.spec_from_loader("_varlen_attn_host", loader))
+            loader.exec_module(host)
+        except (OSError, ImportError, subprocess.SubprocessError) as e:
+            warnings.warn(f"the native half of the binding is not available ({e}); calls are marshalled in Python", RuntimeWarning,
+                          stacklevel=3)
+            host = _PythonHalf
+        else:
+            host.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+                lib.varlen_attn_fwd_workspace_bytes, lib.varlen_attn_bwd_workspace_bytes, lib.varlen_attn_fwd, lib.varlen_attn_bwd,
+                lib.varlen_attn_merge)))
         _host = host
     return _host
 

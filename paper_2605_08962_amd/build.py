@@ -1,5 +1,7 @@
 """Builds libvarlen_attn.so from csrc/ with hipcc for gfx950 (cross-compiles without a GPU), and the native half of the Python
 binding with g++ against torch."""
+import glob
+import hashlib
 import os
 import subprocess
 import sys
@@ -9,7 +11,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvarlen_attn.so")
-HOST = os.path.join(HERE, "_varlen_attn_host.so")
+HOST_SOURCES = [os.path.join(CSRC, "va_host.cpp"), os.path.join(HERE, "..", "include", "varlen_attn.h")]
 # (source, object name, extra flags).  va_bwd.hip is built in parts, each under the instruction-scheduling strategy that
 # measured best for its kernels among the default, iterative-ilp, iterative-minreg, iterative-maxocc, max-ilp and
 # max-memory-clause (64 ViT samples, 16 heads, unless said otherwise; the forward does best with the default):
@@ -58,20 +60,36 @@ def compile_host(source, target):
     import torch
     t = os.path.dirname(torch.__file__)
     inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
-           sysconfig.get_paths()["include"]]
+           sysconfig.get_paths()["include"]]  # (system headers: warnings are of our own source)
     # (under its own name only when whole: another process may be loading the old one)
     tmp = f"{target}.{os.getpid()}"
-    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in inc),
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-isystem{d}" for d in inc),
                     source, "-o", tmp, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"],
                    check=True)
     os.replace(tmp, target)
     return target
 
 
+def host_path():
+    """Where the native half of the binding belongs.  It reaches into torch's and CPython's objects, so its name says what it was
+    built from and for: one that does not match what runs is never loaded."""
+    import torch
+    h = hashlib.sha256()
+    for path in HOST_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return os.path.join(HERE, f"_varlen_attn_host.{sysconfig.get_config_var('SOABI')}.torch-{torch.__version__}."
+                              f"{h.hexdigest()[:12]}.so")
+
+
 def build_host():
-    """_varlen_attn_host.so; returns its path."""
-    return compile_host(os.path.join(CSRC, "va_host.cpp"), HOST)
+    """The native half of the binding, in place of an older one for the same torch and interpreter; returns its path."""
+    path = compile_host(HOST_SOURCES[0], host_path())
+    for old in glob.glob(glob.escape(path[:-len("123456789012.so")]) + "?" * 12 + ".so"):
+        if old != path:
+            os.remove(old)
+    return path
 
 
 def build():

@@ -7,6 +7,7 @@ import importlib.machinery
 import importlib.util
 import os
 import types
+import warnings
 
 import pytest
 import torch
@@ -250,3 +251,44 @@ def test_the_python_half_allocates_on_the_stream_of_the_call(python_half, make):
         assert set(empties) == (set() if given else {pool}) and (given or len(empties) >= results)
         # the results are used on the stream that was current, and may be dropped with such uses under way
         assert [s for what, s in python_half.made if what == "record"] == ([48] * results if pool == 64 else [])
+
+
+def test_the_native_half_is_named_after_what_it_was_built_for(monkeypatch, tmp_path):
+    """One built for another torch or interpreter, or from other sources, is another file: it is not loaded."""
+    here = build.host_path()
+    assert os.path.dirname(here) == build.HERE and here == build.host_path()
+    names = {here}
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "2.11.0")
+        names.add(build.host_path())
+    with monkeypatch.context() as m:
+        m.setattr(build.sysconfig, "get_config_var", lambda name: "cpython-399")
+        names.add(build.host_path())
+    for name in ("va_host.cpp", "varlen_attn.h"):
+        for i, path in enumerate(build.HOST_SOURCES):
+            if os.path.basename(path) == name:
+                changed = tmp_path / name
+                changed.write_bytes(open(path, "rb").read() + b"\n")
+                with monkeypatch.context() as m:
+                    m.setattr(build, "HOST_SOURCES", [str(changed) if j == i else x for j, x in enumerate(build.HOST_SOURCES)])
+                    names.add(build.host_path())
+    assert len(names) == 5
+
+
+@pytest.mark.parametrize("how", ["cannot be built", "cannot be loaded"])
+def test_without_the_native_half_calls_go_through_the_python_half(monkeypatch, tmp_path, how):
+    path = tmp_path / "host.so"
+
+    def no_compiler():
+        raise FileNotFoundError("g++")
+    if how == "cannot be loaded":
+        path.write_bytes(b"")
+    monkeypatch.setattr(binding, "_host", None)
+    monkeypatch.setattr(build, "host_path", lambda: str(path))
+    monkeypatch.setattr(build, "build_host", no_compiler)
+    q = _bf(T, HQ, D)
+    with pytest.warns(RuntimeWarning, match="native half"), pytest.raises(ValueError, match="^q must"):
+        binding.varlen_attn_fwd(q, q, q, torch.tensor([0, T]).int(), True, 0.1)
+    with warnings.catch_warnings(), pytest.raises(ValueError, match="^o_parts must"):
+        warnings.simplefilter("error")  # (said once)
+        binding.varlen_attn_merge(q[None], q)
