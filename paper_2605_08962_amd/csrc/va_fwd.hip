@@ -650,17 +650,14 @@ fwd_kernel_small(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, con
                                         part_o, part_lse, small, clock_probe);
 }
 
-// Rows per workgroup of the merge: at 32 every thread merged two pieces one after the other, a memory round trip each (4096
-// tokens, 2 heads of 128, causal, 5.9 -> 5.1 us, 2048 tokens 6.0 -> 4.2; 8191 tokens, 4 heads, 10.4 -> 10.2).
-constexpr int kMergeRows = 16;
-// Merge of the chunks fwd_kernel_small left: one workgroup per (query tile, kMergeRows of its rows, head); tiles that were
+// Merge of the chunks fwd_kernel_small left: one workgroup per (query tile, ROWS of its rows, head); tiles that were
 // not split are already done.  Eight output channels per thread.
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int ROWS>
 __global__ void __launch_bounds__(256)
 fwd_merge_small(const float* __restrict__ part_o, const float* __restrict__ part_lse, __bf16* __restrict__ O,
                 float* __restrict__ LSE, FwdSmall small, int T, int Hq) {
     using C = FwdCfg<D>;
-    constexpr int CPR = D / 8, ROWS = kMergeRows, SHARES = C::BQ / ROWS;
+    constexpr int CPR = D / 8, SHARES = C::BQ / ROWS;
     const int h = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)Hq));
     const int q = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)Hq));
     SmallTile tl;
@@ -732,17 +729,27 @@ static hipError_t launch_d(const FwdArgs& a, hipStream_t stream) {
     return a.causal ? launch_dc<D, true>(a, stream) : launch_dc<D, false>(a, stream);
 }
 
-template <int D>
-static hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream) {
+template <int D, int ROWS>
+static hipError_t launch_merge_rows(const FwdArgs& a, hipStream_t stream) {
     const FwdSmall sm{a.cu_seqlens, a.num_seqs, a.plan};
-    dim3 grid((unsigned)(a.max_items * a.num_q_heads * (FWD_TILE_Q / kMergeRows))), block(256);
+    dim3 grid((unsigned)(a.max_items * a.num_q_heads * (FWD_TILE_Q / ROWS))), block(256);
     if (a.causal)
-        hipLaunchKernelGGL((fwd_merge_small<D, true>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
+        hipLaunchKernelGGL((fwd_merge_small<D, true, ROWS>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
                            sm, a.total_tokens, a.num_q_heads);
     else
-        hipLaunchKernelGGL((fwd_merge_small<D, false>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
+        hipLaunchKernelGGL((fwd_merge_small<D, false, ROWS>), grid, block, 0, stream, a.part_o, a.part_lse, (__bf16*)a.o, a.lse,
                            sm, a.total_tokens, a.num_q_heads);
     return hipGetLastError();
+}
+// Rows per workgroup of the merge, as of the backward's sums: at 32 every thread merges two pieces one after the other, a
+// memory round trip each, which is most of the kernel while there are no more than four such workgroups to a CU; beyond, above
+// all with samples among them that are not cut, it is the rate at which workgroups start and find their tile.  Measured at 16 /
+// 32, us: 25 tiles of 128 and 96 6.2 / 8.0 and 6.2 / 7.7, 128 of 128 9.2 / 9.7, 228 of 80 9.9 / 10.2, 240 of 64 8.6 / 8.2; 276 of
+// 80 10.9 / 10.7, 318 of 80 14.3 / 14.5; several samples: 294 of 64 8.6 / 7.7, 308 of 96 8.5 / 7.3, 322 and 384 of 128 12.3 / 10.2
+// and 10.6 / 8.0, 372 of 64 9.1 / 7.2.  (One kernel with the rows an argument is 2-5 % slower than either.)
+template <int D>
+static hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream) {
+    return 4 * a.max_items * a.num_q_heads <= 1024 ? launch_merge_rows<D, 16>(a, stream) : launch_merge_rows<D, 32>(a, stream);
 }
 
 hipError_t launch_fwd_merge_small(const FwdArgs& a, hipStream_t stream) {

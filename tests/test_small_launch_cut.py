@@ -3,6 +3,7 @@ threads, and with margins around every buffer they write."""
 import pytest
 import torch
 
+from tests._util import assert_close
 from tests.test_small_launch_contract import _cu, _qkv
 
 pytestmark = pytest.mark.gpu
@@ -108,3 +109,25 @@ def test_margins_around_the_buffers_of_a_cut_step(lengths, Hq, Hkv, D, causal):
     ref = binding.varlen_attn_fwd(q, k, v, cu, causal, sc, max_seqlen=hint)
     ref += binding.varlen_attn_bwd(do, q, k, v, *ref, cu, causal, sc, max_seqlen=hint)
     assert all(torch.equal(a, b) for a, b in zip(out.values(), ref))
+
+
+@pytest.mark.parametrize("D", [64, 80, 96, 128])
+@pytest.mark.parametrize("Hq,tiles", [(2, 128), (4, 256), (4, 260)])  # up to 256 16 rows to a workgroup of the merge, beyond 32
+def test_merge_on_both_sides_of_its_rows(D, Hq, tiles):
+    """Every row of a cut forward, long samples and short ones beside them, against attention in 64 bits."""
+    from paper_2605_08962_amd import binding
+    lengths = [3500] + [1 + 37 * i % 130 for i in range(tiles // Hq - 48)]
+    lengths.insert(1, 46 * 128 + 77 - sum(lengths))
+    T, sc, hint = sum(lengths), D ** -0.5, 3500
+    assert (T // 128 + len(lengths)) * Hq == tiles and 1000 < lengths[1] < 3500
+    q, k, v = _qkv(T, Hq, 1, D, T + D)
+    o, lse = binding.varlen_attn_fwd(q, k, v, _cu(*lengths), False, sc, max_seqlen=hint)
+    assert not torch.equal(o, binding.varlen_attn_fwd(q, k, v, _cu(*lengths), False, sc, max_seqlen=hint, kv_splits=1)[0])
+    q, k, v, o, lse = (x.double().cpu() for x in (q, k, v, o, lse))
+    at = 0
+    for n in lengths:
+        s = sc * q[at:at + n].transpose(0, 1) @ k[at:at + n, 0].T
+        assert float((lse[:, at:at + n] - torch.logsumexp(s, -1)).abs().max()) <= 1e-3
+        want = (torch.softmax(s, -1) @ v[at:at + n, 0]).transpose(0, 1)
+        assert_close(f"O of the sample at {at}", o[at:at + n].numpy(), want.numpy(), allow_output_rounding=True)
+        at += n
