@@ -133,8 +133,16 @@ struct PackedLdsTile {
     __host__ __device__ __forceinline__ static constexpr bool locate(int p, int& r, int& c) {
         const int seg = p >> 4, b = (p >> 2) & 3, e = p & 3;
         int a = 0;
-        if (seg < 4 * FULL) { a = seg / FULL; c = 4 * (seg % FULL) + ((e - a) & 3); }
-        else { c = seg; a = (e - c) & 3; }
+        if (CHUNKS % 4 == 0) {
+            a = seg / FULL; c = 4 * (seg % FULL) + ((e - a) & 3);
+        } else {
+            // Unsigned and by selects: 30 to 100 instructions less at the start of every workgroup than with branches.  Few-token
+            // samples at head_dim 80 are little else, us: 200 of 5..25 tokens, 16 heads, causal, forward 23.5 -> 22.8, dQ 29.0 ->
+            // 28.6, dK/dV 36.1 -> 35.6; 28 of them, 32/16 heads, 11.2 -> 10.9, 11.6 -> 11.4, 10.4 -> 10.3.
+            const unsigned s = (unsigned)p >> 4;
+            a = s >= 4 * FULL ? (e - seg) & 3 : (int)(s / FULL);
+            c = s >= 4 * FULL ? seg : (int)(4 * (s % FULL)) + ((e - a) & 3);
+        }
         r = 4 * a + b;
         return true;
     }
@@ -327,9 +335,9 @@ struct TileDma {
                 T::locate(p % T::BLOCK_POS, r, c);
                 row = 16 * (wave * (64 * NI / T::BLOCK_POS) + p / T::BLOCK_POS) + r;
             } else {
-                const int p = 64 * piece(wave, i) + lane;  // 16-byte position inside the tile
-                T::locate(p % T::BLOCK_POS, r, c);
-                row = 16 * (p / T::BLOCK_POS) + r;
+                const unsigned p = 64 * piece(wave, i) + lane;  // 16-byte position inside the tile
+                T::locate((int)(p % T::BLOCK_POS), r, c);
+                row = (int)(16 * (p / T::BLOCK_POS)) + r;
             }
             full[i] = (uint32_t)row * row_bytes + c * 16;
             last[i] = (uint32_t)min(row, L - 1 - last_r0) * row_bytes + c * 16;

@@ -378,8 +378,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     const bool ragged_sample = (L % C::BKV) != 0;
     const int last_tile = (L + C::BKV - 1) / C::BKV - 1;  // the tile holding the sample's end
     auto tile_ptr = [&](const unsigned char* base, int j) { return base + (size_t)min(j, je - 1) * tile_bytes; };
-    auto load_tile = [&](const unsigned char* base, int j, uint32_t lds_tile) {
-        dma.issue_tile(tile_ptr(base, j), ragged_sample && min(j, je - 1) == last_tile, lds_tile, w, base == vbase);
+    auto load_tile = [&](const unsigned char* base, int j, uint32_t lds_tile, bool second) {
+        dma.issue_tile(tile_ptr(base, j), ragged_sample && min(j, je - 1) == last_tile, lds_tile, w, second);
     };
     // per-lane LDS offsets: K rows read along the row (A operand of S^T), V read down the columns
     int kaddr[C::KS], vaddr[C::DB][2];
@@ -405,8 +405,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     // along with the rest it made the start of every workgroup longer (64..1024-token samples, 16 heads of 96, 441 -> 433 us, of
     // 80 384 -> 381).
     // (slots: the first tile, which sets the reference maximum, ends on the pair of slots that the unrolled loop starts with)
-    load_tile(kbase, jb, lds0 + 2 * C::TILE);
-    load_tile(vbase, jb, lds0 + 4 * C::TILE);
+    load_tile(kbase, jb, lds0 + 2 * C::TILE, false);
+    load_tile(vbase, jb, lds0 + 4 * C::TILE, true);
     bf16x8 qf[C::KS];
     {
         const __bf16* qp = Q + ((size_t)(sb + (qvalid ? qrow : 0)) * Hq + h) * D + 8 * hh;
@@ -418,7 +418,7 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     }
     wait_vmcnt<0>();
     wg_barrier();
-    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0);
+    if (!LEAN || jb + 1 < je) load_tile(kbase, jb + 1, lds0, false);
 
     int kslot = 2;  // (j - jb + 2) % 3
     int vslot = 1;  // (j - jb + 1) % 2
