@@ -16,7 +16,7 @@
 // depend on scheduling order; it recomputes S and dP once more than a fused kernel would.
 //
 // Staging is the forward's: 64-row tiles go straight from HBM/L2 into XOR-swizzled LDS tiles with
-// direct-to-LDS loads, three stages deep, one barrier per step, completion tracked with vmcnt.
+// direct-to-LDS loads, two (dQ), three or four (dK/dV) stages deep, one barrier per step, completion tracked with vmcnt.
 //
 // The file is compiled in five parts (VA_BWD_PART), each under the instruction-scheduling strategy of the compiler that
 // measured best for its kernels (build.py): 1 dK/dV at head_dim 128, causal; 2 dQ; 3 dK/dV at 80; 4 dK/dV at 96, and at 128
@@ -343,8 +343,8 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     // Mask-free steps whose loads stay inside the head take pointers by addition and no choice of offsets (15 scalar and 6
     // vector instructions fewer per step; head_dim 80 spills 11 registers in the loop's second copy and goes without); at
     // head_dim 64 whole rounds of the stages are written out besides, their LDS addresses constants (elsewhere the copies cost
-    // registers the kernel does not have; slices take a handful of steps, for which less code is better).  Measured: 64 ViT samples, 16 heads of 64 5195 -> 5144 us, of 96 8453 -> 8385; LLM
-    // batch at 96 1926 -> 1895; at 128 even.
+    // registers the kernel does not have; slices take a handful of steps, for which less code is better).  Measured: 64 ViT
+    // samples, 16 heads of 64 5149 -> 5071 us, of 96 8453 -> 8385; LLM batch at 96 1926 -> 1895; at 128 even.
     constexpr bool UNROLLED = D == 64 && OB == C::DB;
     constexpr bool STEADY = D != 80 && OB == C::DB;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
@@ -540,7 +540,7 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
     // steady_tag: the step it loads is neither the last of its head nor of the chunk
     auto phased = [&](auto stage_tag, auto steady_tag) {
         constexpr int KNOWN = decltype(stage_tag)::value;
-        constexpr bool STEADY = decltype(steady_tag)::value;
+        constexpr bool IN_HEAD = decltype(steady_tag)::value;
         VA_DKDV_SYNC()
         const int si = KNOWN >= 0 ? KNOWN : stage_i;
         const unsigned char* cur = lds + si * STAGE;
@@ -548,14 +548,14 @@ dkdv_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __
         // half 0 (the scalar bookkeeping of this step's loads runs behind its MFMAs)
         dkdv_load_lse<D, 0>(cur, lv, hh);
         dkdv_run_S<D>(fa, kf, s);
-        if constexpr (STEADY) {
+        if constexpr (IN_HEAD) {
             iss_q = nxt_q; iss_do = nxt_do; iss_st = nxt_st;
             iss_lds = lds0 + (KNOWN >= 0 ? (KNOWN + NST - 1) % NST : stage_i == 0 ? NST - 1 : stage_i - 1) * STAGE;
             nxt_q += step_q; nxt_do += step_q; nxt_st += step_st;
         } else {
             begin_issue();
         }
-        const bool ragged = !STEADY && iss_ragged;
+        const bool ragged = !IN_HEAD && iss_ragged;
         __builtin_amdgcn_sched_barrier(0);
         VA_DKDV_ISSUE_SLOT(0)
         VA_DKDV_ISSUE_SLOT(1)

@@ -302,7 +302,7 @@ __host__ __device__ __forceinline__ int short_rotated_head(int hp, int item, int
 __device__ __forceinline__ int uniform_wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // Per-lane source offsets of the direct-to-LDS loads that fill one LdsTile of ROWS rows of a
-// [rows, heads, D] tensor, split over the NW waves of the workgroup.  The offsets are relative to
+// [rows, heads, D] tensor, split over the four waves of the workgroup.  The offsets are relative to
 // the tile's first row; they are computed once per kernel, so that issuing a tile costs no vector
 // ALU work.  `last` holds the offsets for the sample's ragged last tile, where rows past the sample
 // end re-read its last row (finite data that the caller masks).
@@ -313,17 +313,17 @@ __device__ __forceinline__ int uniform_wave_id() { return __builtin_amdgcn_readf
 // something.  One block of 16 rows per wave took six loads for the pair instead of five at head_dim 80, the third of each
 // half empty, and at 96, in rows padded to 256 bytes, eight instead of six.  64 ViT samples, 16 heads of 96: forward 4548 ->
 // 4238 us, dQ 6215 -> 5858, dK/dV 10129 -> 9725; at head_dim 80, 256 samples of 64..1024 tokens, dQ 632 -> 615, the others 0.6 %.)
-template <int D, int ROWS, int NW = 4>
+template <int D, int ROWS>
 struct TileDma {
     using T = LdsTile<D>;
+    static constexpr int WAVES = 4;
     static constexpr int PIECES = ROWS / 16 * T::BLOCK_POS / 64;
-    static constexpr int NI = PIECES / NW;                     // loads per wave per tile, without
-    static constexpr int EXTRA = PIECES % NW ? 1 : 0;          // the one per pair of tiles
-    static_assert(ROWS % 16 == 0 && ROWS / 16 * T::BLOCK_POS % 64 == 0 && (PIECES % NW == 0 || PIECES % NW == 2) && NW >= 4,
-                  "pieces of a tile");
+    static constexpr int NI = PIECES / WAVES;                  // loads per wave per tile, without
+    static constexpr int EXTRA = PIECES % WAVES ? 1 : 0;       // the one per pair of tiles
+    static_assert(ROWS % 16 == 0 && ROWS / 16 * T::BLOCK_POS % 64 == 0 && PIECES % WAVES % 2 == 0, "pieces of a tile");
     uint32_t full[NI + EXTRA], last[NI + EXTRA];
     // Piece that load i of a wave fills (i == NI: the extra one).
-    __device__ __forceinline__ static int piece(int wave, int i) { return i < NI ? wave * NI + i : NW * NI + (wave & 1); }
+    __device__ __forceinline__ static int piece(int wave, int i) { return i < NI ? wave * NI + i : WAVES * NI + (wave & 1); }
     // row_bytes: bytes between consecutive rows of the tensor; L: rows in the sample
     __device__ __forceinline__ void init(uint32_t row_bytes, int L, int wave, int lane) {
         const int last_r0 = (L - 1) / ROWS * ROWS;
@@ -362,7 +362,6 @@ struct TileDma {
     // The extra load of a pair of tiles, without a branch.
     __device__ __forceinline__ void issue_extra(const unsigned char* first, const unsigned char* second, bool first_ragged,
                                                 bool second_ragged, uint32_t first_tile, uint32_t second_tile, int wave) const {
-        static_assert(NW == 4 || !EXTRA, "every wave has one");
         const bool s = extra_is_second(wave);
         if (EXTRA) issue_one(NI, s ? second : first, s ? second_ragged : first_ragged, s ? second_tile : first_tile, wave);
     }

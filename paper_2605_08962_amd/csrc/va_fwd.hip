@@ -59,8 +59,9 @@ __device__ __forceinline__ void tile_step(const unsigned char* kb, const unsigne
     // SKIP: blocks of 32 keys that no row of this wave sees, past the sample's end or above the diagonal, leave out their
     // products, which would be of zeros, each behind a wave-uniform branch (with two blocks to a tile the first is always
     // computed: a branch around it cost the head_dim 64 kernel 7 spilled registers).  Measured: 64 ViT samples, 16 heads
-    // of 64, 2878 -> 2844 us (four runs of each in turn, which differ by 4); causal, 64..600 tokens, 16 heads of 64, lean form, 249 -> 232 us (four workgroups per CU
-    // now instead of three); no difference to the lean form at head_dim 64 without the causal mask, which goes without.
+    // of 64, 2878 -> 2844 us (four runs of each in turn, which differ by 4); causal, 64..600 tokens, 16 heads of 64, lean form,
+    // 249 -> 232 us (four workgroups per CU now instead of three); no difference to the lean form at head_dim 64 without the
+    // causal mask, which goes without.
     bool dead[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -525,7 +526,8 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
             wg_barrier();
             ++j;
         };
-        // Step I of a round; false if the reference maximum has to move first (its V loads are issued then, nothing else done).
+        // Step I of a round; false if the reference maximum has to move first: then its loads of slots 0 and 1 are issued (all of
+        // V's, and the pair's left-over one) and nothing else is done.
         auto round_step = [&](auto tag) {
             constexpr int I = decltype(tag)::value;
             auto issue_now = [&](int slot) { issue_whole(slot, lds0 + (3 + (I + 1) % 2) * C::TILE, lds0 + (I + 2) % 3 * C::TILE); };
