@@ -190,7 +190,10 @@ va::SmallPlan small_plan(const varlen_attn_params* p, int tile_rows, int partner
 // epilogue together 6-8 us each; parts at 5 TB/s.  Fitted to the times of 460 random batches at every head_dim, uncut and
 // cut into 256 to 1536 workgroups, the steps take 0.65-0.9 us (forward), 0.75-1.2 (dQ) and 0.85-1.4 (dK/dV), share 0.3-0.6,
 // fixed 5-8 (forward at 128: 15); with these constants the choice is on average 3 % off the best one tried, and in 1 of 60
-// cases more than 5 % behind the uncut launch.
+// cases more than 5 % behind the uncut launch.  Fitted before the kernels' mask-free steps lost their bounds and branches, and the
+// merges half their rows; since then 240 random launches of samples above 1024 tokens, planned against kv_splits = 1: forward 0.68,
+// backward 0.60 of the time on average, 8 of the 480 more than 5 % behind (at worst a forward of five samples of 5528 tokens, 3
+// heads of 128, causal, 138 -> 166 us; a backward of five samples of up to 1085, 8 heads of 128, 61 -> 70).
 SmallCost fwd_cost(int head_dim) {
     return head_dim == 128 ? SmallCost{va::fwd_small_slots(128) / 256, 0.37f, 8.f, 8.f, 4.f, 0}
                            : SmallCost{va::fwd_small_slots(head_dim) / 256, 0.37f, 6.f, 4.f, 4.f, 0};

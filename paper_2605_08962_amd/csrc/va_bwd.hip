@@ -311,6 +311,8 @@ struct DkdvSmall {
     SmallPlan plan;
     float *part_dk, *part_dv;  // fp32 [chunks, T, Hkv, D]
 };
+// (Spilled: at 128 under the causal mask one vector register, into the accumulation half, read back three times a step; at 80
+// five in the small form without the mask and two in the general one under it, outside the loops.)
 template <int D>
 constexpr int kDkdvWgsPerCu = D <= 80 ? 2 : 1;
 
@@ -828,7 +830,7 @@ __device__ __forceinline__ void dq_plain_step(const unsigned char* kt, const uns
         // 64, 64..1024 tokens, 313 -> 310; six causal samples of 30..200 tokens 13.8 -> 12.6).
         if (MASKED && CAUSAL && kv0 + 32 * b > __builtin_amdgcn_readfirstlane(qrow) + 31) break;
         // The second block's operand reads stay behind the first block: mixed, dQ took 8 % longer at head_dim 128, 3 % at 64
-        // (three workgroups per CU), about the same at 96.  Head_dim 80 has the registers (256 of 256): 0.6 % faster mixed on
+        // (three workgroups per CU), about the same at 96.  Head_dim 80 has the registers (240 of 256): 0.6 % faster mixed on
         // 65536 tokens, 1.5 % on 64..1024.
         if (b && D != 80) __builtin_amdgcn_sched_barrier(0);
         f32x16 s, dp;
@@ -1122,8 +1124,9 @@ static hipError_t launch_sum_d(const BwdArgs& a, hipStream_t stream) {
     const int tiles_kv = a.plan_kv.max_chunks > 1 ? (int)(a.max_items_kv * a.num_kv_heads) : 0;
     // Rows per workgroup: every thread sums two or four pieces one after the other at 32, a memory round trip each, which is most
     // of the kernel while there are no more than four such workgroups to a CU; beyond, fewer workgroups find their tile faster.
-    // Measured at 32 / 16: 4096 tokens, 2 heads of 128, causal, 10.4 / 9.4 us, 2048 tokens 8.0 / 6.9 us; 8191 tokens, 4 query heads
-    // on one of 128, 12.8 / 14.2.
+    // Measured at 16 / 32, us (70 random cut backwards): workgroups of 32 up to 500 6.1 / 6.5 to 11.8 / 12.5, 5 to 27 % for 16; from
+    // there to 1008 even, 7.2 / 7.4, 14.2 / 14.9, 12.1 / 11.7; 1032 to 1600 11.8 / 11.7, 17.3 / 17.3, 14.2 / 13.8; beyond, one sample
+    // 16.5 / 15.7, 18.0 / 16.9, with short samples among them 11.7 / 9.4, 20.0 / 15.4, 17.7 / 12.7.
     const int rows = 4 * (tiles_q + tiles_kv) <= 1024 ? 16 : 32;
     const int wgs_q = tiles_q * (BWD_TILE_Q / rows), wgs_kv = tiles_kv * (BWD_TILE_KV / rows);
     auto dq = (__bf16*)a.dq; auto dk = (__bf16*)a.dk; auto dv = (__bf16*)a.dv;

@@ -243,9 +243,15 @@ __device__ __forceinline__ bool tile_step_trusting(const unsigned char* kb, cons
 }
 
 // Workgroups per CU the kernel is compiled for (registers) and its LDS allows.  At head_dim 64 the general
-// form fits four (126 registers, 40 KB) and needs them: held to three by LDS padding it measured 12 % slower on
-// 8192-token samples, to two 18 %.  So does the lean form (126 registers; 128 and one spilled under the causal mask,
-// where it measured 7 % faster than three workgroups with 149).
+// form fits four (128 registers, 40 KB) and needs them: held to three by LDS padding it measured 12 % slower on
+// 8192-token samples, to two 18 %.  So does the lean form (128 registers; 127 under the causal mask, where it measured 7 %
+// faster than three workgroups with 149).  At 128 the steady loop leaves 168 registers short of one or two in the small forms
+// and in the causal general and lean ones: those values go to scratch before the loops and come back behind them (the loop's
+// gains, see there, are with that).
+// The small form at 64 without the mask came down to 127 registers with the steady loop, so that a CU takes four; the plans
+// (va_api.hip) still reckon with three.  With four here as well 160 random launches took the same time, 0.1 % less; held to three
+// by 1 KB more of LDS, cut launches of several samples, whose long chunks then spread more evenly at times and less so at others,
+// took 0.9 % longer on average (284 of them, from 11 % less to 17 % more).
 template <int D, bool CAUSAL>
 constexpr int kFwdWgsPerCu = D == 64 ? 4 : (D <= 80 || D == 128) ? 3 : 2;
 template <int D>
@@ -287,8 +293,9 @@ __device__ __forceinline__ void fwd_work_item(unsigned wid, unsigned char* lds, 
     using C = FwdCfg<D>;
     using LT = LdsTile<D>;
     constexpr bool LEAN = MODE != FWD_GENERAL;
-    // the mask-free loop's forms (see there): short samples at head_dim 64 do better with less code, and whole rounds of the
-    // LDS slots take registers that not every form has
+    // the mask-free loop's forms (see there): short samples at head_dim 64 do better with less code (steady, 40 batches of samples
+    // of 20..855 tokens took 0.7 % longer without the mask, 1.9 % under it), and whole rounds of the LDS slots take registers
+    // that not every form has
     constexpr bool STEADY = !(MODE == FWD_LEAN && D == 64);
     constexpr bool UNROLL = MODE == FWD_GENERAL || (MODE == FWD_SMALL && D > 80);
     constexpr bool SKIP = !(MODE == FWD_LEAN && D == 64 && !CAUSAL);  // see tile_step
